@@ -18,7 +18,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <mutex>
 #include <new>
 #include <vector>
 
@@ -1910,117 +1909,61 @@ struct lbib_mlp {
   hipStream_t stream = nullptr;
   int bmax = 0;
   long long t = 0;  // Adam steps taken
-  size_t off_p, off_g, off_m, off_v, off_z1, off_a1, off_z2, off_a2, off_y, off_dy, off_d1, off_d2, off_part;
+  size_t off_p, off_g, off_m, off_v, off_part, off_lpart;
   template <typename T>
   T* at(size_t o) const { return reinterpret_cast<T*>(ws + o); }
 };
 
 namespace {
 
+// row tiles of a batch and workgroups of a training pass over it
+int mlp_tiles(int B) { return (B + MLP_ROWS - 1) / MLP_ROWS; }
+int mlp_parts(int B) { return std::min(mlp_tiles(B), MLP_PARTS); }
+
 size_t mlp_layout(lbib_mlp* h, int B) {
   Carver c{nullptr};
   const size_t np = (size_t)MLP_NPARAM * 4;
   const size_t o_p = c.take(np), o_g = c.take(np), o_m = c.take(np), o_v = c.take(np);
-  const size_t hid = (size_t)B * MLP_H * 4, out = (size_t)B * MLP_OUT * 4;
-  const size_t o_z1 = c.take(hid), o_a1 = c.take(hid), o_z2 = c.take(hid), o_a2 = c.take(hid);
-  const size_t o_y = c.take(out), o_dy = c.take(out), o_d1 = c.take(hid), o_d2 = c.take(hid);
-  const size_t o_part = c.take(((size_t)B * MLP_OUT / 256 + 1) * 8);
+  const size_t o_part = c.take((size_t)mlp_parts(B) * np), o_lpart = c.take((size_t)mlp_parts(B) * 8);
   if (h) {
     h->off_p = o_p;
     h->off_g = o_g;
     h->off_m = o_m;
     h->off_v = o_v;
-    h->off_z1 = o_z1;
-    h->off_a1 = o_a1;
-    h->off_z2 = o_z2;
-    h->off_a2 = o_a2;
-    h->off_y = o_y;
-    h->off_dy = o_dy;
-    h->off_d1 = o_d1;
-    h->off_d2 = o_d2;
     h->off_part = o_part;
+    h->off_lpart = o_lpart;
   }
   return c.off;
 }
 
-struct MlpParams {
-  const float *W1, *b1, *W2, *b2, *W3, *b3;
-};
-template <typename T>
-void mlp_split(T* p, T*& W1, T*& b1, T*& W2, T*& b2, T*& W3, T*& b3) {
-  W1 = p;
-  b1 = W1 + MLP_H * MLP_IN;
-  W2 = b1 + MLP_H;
-  b2 = W2 + MLP_H * MLP_H;
-  W3 = b2 + MLP_H;
-  b3 = W3 + MLP_OUT * MLP_H;
+void mlp_forward(const float* prm, const float* X, int B, float* Y, hipStream_t st) {
+  hipLaunchKernelGGL(k_mlp<false>, dim3(mlp_tiles(B)), dim3(256), 0, st, prm, X, (const float*)nullptr, B, 0.0f, Y,
+                     (float*)nullptr, (double*)nullptr);
 }
 
-dim3 gemm_grid(int M, int N) { return dim3((N + 63) / 64, (M + 63) / 64); }
-
-// the three layers on stream st; Z1, Z2 (pre-activations, for the backward
-// pass) may be null
-void mlp_forward_raw(const float* prm, const float* X, int B, float* Y, float* Z1, float* A1, float* Z2,
-                     float* A2, hipStream_t st) {
-  const float *W1, *b1, *W2, *b2, *W3, *b3;
-  mlp_split(prm, W1, b1, W2, b2, W3, b3);
-  hipLaunchKernelGGL(k_gemm<EPI_BIAS_GELU>, gemm_grid(B, MLP_H), dim3(256), 0, st, X, MLP_IN, 1, W1, MLP_IN, 1, B,
-                     MLP_H, MLP_IN, b1, (const float*)nullptr, Z1, A1);
-  hipLaunchKernelGGL(k_gemm<EPI_BIAS_GELU>, gemm_grid(B, MLP_H), dim3(256), 0, st, (const float*)A1, MLP_H, 1, W2,
-                     MLP_H, 1, B, MLP_H, MLP_H, b2, (const float*)nullptr, Z2, A2);
-  hipLaunchKernelGGL(k_gemm<EPI_BIAS>, gemm_grid(B, MLP_OUT), dim3(256), 0, st, (const float*)A2, MLP_H, 1, W3,
-                     MLP_H, 1, B, MLP_OUT, MLP_H, b3, (const float*)nullptr, (float*)nullptr, Y);
-}
-
-void mlp_forward(lbib_mlp* h, const float* X, int B, float* Y) {
-  mlp_forward_raw(h->at<float>(h->off_p), X, B, Y, h->at<float>(h->off_z1), h->at<float>(h->off_a1),
-                  h->at<float>(h->off_z2), h->at<float>(h->off_a2), h->stream);
-}
-
-// forward + loss partials + gradient into off_g
+// forward + loss partials + partial gradients
 void mlp_backward(lbib_mlp* h, const float* X, const float* T, int B) {
-  float *W1, *b1, *W2, *b2, *W3, *b3, *gW1, *gb1, *gW2, *gb2, *gW3, *gb3;
-  mlp_split(h->at<float>(h->off_p), W1, b1, W2, b2, W3, b3);
-  mlp_split(h->at<float>(h->off_g), gW1, gb1, gW2, gb2, gW3, gb3);
-  float* Y = h->at<float>(h->off_y);
-  float* dY = h->at<float>(h->off_dy);
-  float *Z1 = h->at<float>(h->off_z1), *A1 = h->at<float>(h->off_a1);
-  float *Z2 = h->at<float>(h->off_z2), *A2 = h->at<float>(h->off_a2);
-  float *D1 = h->at<float>(h->off_d1), *D2 = h->at<float>(h->off_d2);
-  mlp_forward(h, X, B, Y);
-  const long long n = (long long)B * MLP_OUT;
-  hipLaunchKernelGGL(k_mse, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, h->stream, (const float*)Y, T, n,
-                     1.0f / (float)B, dY, h->at<double>(h->off_part));
-  // layer 3: dW3 = dY^T A2, db3, dZ2 = (dY W3) * GELU'(Z2)
-  hipLaunchKernelGGL(k_gemm<EPI_NONE>, gemm_grid(MLP_OUT, MLP_H), dim3(256), 0, h->stream, (const float*)dY, 1,
-                     MLP_OUT, (const float*)A2, 1, MLP_H, MLP_OUT, MLP_H, B, (const float*)nullptr,
-                     (const float*)nullptr, (float*)nullptr, gW3);
-  hipLaunchKernelGGL(k_colsum, dim3(1), dim3(128), 0, h->stream, (const float*)dY, B, MLP_OUT, gb3);
-  hipLaunchKernelGGL(k_gemm<EPI_GELU_GRAD>, gemm_grid(B, MLP_H), dim3(256), 0, h->stream, (const float*)dY,
-                     MLP_OUT, 1, (const float*)W3, 1, MLP_H, B, MLP_H, MLP_OUT, (const float*)nullptr,
-                     (const float*)Z2, (float*)nullptr, D2);
-  // layer 2
-  hipLaunchKernelGGL(k_gemm<EPI_NONE>, gemm_grid(MLP_H, MLP_H), dim3(256), 0, h->stream, (const float*)D2, 1,
-                     MLP_H, (const float*)A1, 1, MLP_H, MLP_H, MLP_H, B, (const float*)nullptr,
-                     (const float*)nullptr, (float*)nullptr, gW2);
-  hipLaunchKernelGGL(k_colsum, dim3(1), dim3(128), 0, h->stream, (const float*)D2, B, MLP_H, gb2);
-  hipLaunchKernelGGL(k_gemm<EPI_GELU_GRAD>, gemm_grid(B, MLP_H), dim3(256), 0, h->stream, (const float*)D2,
-                     MLP_H, 1, (const float*)W2, 1, MLP_H, B, MLP_H, MLP_H, (const float*)nullptr,
-                     (const float*)Z1, (float*)nullptr, D1);
-  // layer 1
-  hipLaunchKernelGGL(k_gemm<EPI_NONE>, gemm_grid(MLP_H, MLP_IN), dim3(256), 0, h->stream, (const float*)D1, 1,
-                     MLP_H, X, 1, MLP_IN, MLP_H, MLP_IN, B, (const float*)nullptr, (const float*)nullptr,
-                     (float*)nullptr, gW1);
-  hipLaunchKernelGGL(k_colsum, dim3(1), dim3(128), 0, h->stream, (const float*)D1, B, MLP_H, gb1);
+  hipLaunchKernelGGL(k_mlp<true>, dim3(mlp_parts(B)), dim3(256), 0, h->stream, (const float*)h->at<float>(h->off_p),
+                     X, T, B, 1.0f / (float)B, (float*)nullptr, h->at<float>(h->off_part),
+                     h->at<double>(h->off_lpart));
+}
+
+// the gradient into off_g, with ADAM the update too
+template <bool ADAM>
+void mlp_reduce(lbib_mlp* h, int B, float lr, float beta1, float beta2, float eps, float c1, float c2) {
+  hipLaunchKernelGGL(k_mlp_grad<ADAM>, dim3((MLP_NPARAM + 63) / 64), dim3(256), 0, h->stream,
+                     (const float*)h->at<float>(h->off_part), mlp_parts(B), h->at<float>(h->off_g),
+                     h->at<float>(h->off_p), h->at<float>(h->off_m), h->at<float>(h->off_v), lr, beta1, beta2, eps,
+                     c1, c2);
 }
 
 int mlp_loss(lbib_mlp* h, int B, double* loss) {
-  const int nb = (int)(((long long)B * MLP_OUT + 255) / 256);
-  std::vector<double> part(nb);
-  HIPCHK(hipMemcpyAsync(part.data(), h->ws + h->off_part, (size_t)nb * 8, hipMemcpyDeviceToHost, h->stream));
+  double part[MLP_PARTS];
+  const int nb = mlp_parts(B);
+  HIPCHK(hipMemcpyAsync(part, h->ws + h->off_lpart, (size_t)nb * 8, hipMemcpyDeviceToHost, h->stream));
   HIPCHK(hipStreamSynchronize(h->stream));
   double s = 0.0;
-  for (double v : part) s += v;
+  for (int k = 0; k < nb; k++) s += part[k];
   *loss = 0.5 * s / B;
   return LBIB_OK;
 }
@@ -2078,13 +2021,14 @@ int lbib_mlp_get_params(lbib_mlp* h, float* host) {
 
 int lbib_mlp_forward(lbib_mlp* h, const float* x_dev, int B, float* y_dev) {
   if (!h || !x_dev || !y_dev || B < 1 || B > h->bmax) return LBIB_EINVAL;
-  mlp_forward(h, x_dev, B, y_dev);
+  mlp_forward(h->at<float>(h->off_p), x_dev, B, y_dev, h->stream);
   return hipGetLastError() == hipSuccess ? LBIB_OK : LBIB_EHIP;
 }
 
 int lbib_mlp_gradient(lbib_mlp* h, const float* x_dev, const float* t_dev, int B, double* loss, float* grad_host) {
   if (!h || !x_dev || !t_dev || B < 1 || B > h->bmax) return LBIB_EINVAL;
   mlp_backward(h, x_dev, t_dev, B);
+  mlp_reduce<false>(h, B, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f);
   if (hipGetLastError() != hipSuccess) return LBIB_EHIP;
   if (grad_host) {
     HIPCHK(hipMemcpyAsync(grad_host, h->ws + h->off_g, (size_t)MLP_NPARAM * 4, hipMemcpyDeviceToHost, h->stream));
@@ -2102,9 +2046,7 @@ int lbib_mlp_adam_step(lbib_mlp* h, const float* x_dev, const float* t_dev, int 
   h->t += 1;
   const float c1 = (float)(1.0 - std::pow((double)beta1, (double)h->t));
   const float c2 = (float)(1.0 - std::pow((double)beta2, (double)h->t));
-  hipLaunchKernelGGL(k_adam, dim3((MLP_NPARAM + 255) / 256), dim3(256), 0, h->stream, h->at<float>(h->off_p),
-                     (const float*)h->at<float>(h->off_g), h->at<float>(h->off_m), h->at<float>(h->off_v),
-                     MLP_NPARAM, lr, beta1, beta2, eps, c1, c2);
+  mlp_reduce<true>(h, B, lr, beta1, beta2, eps, c1, c2);
   if (hipGetLastError() != hipSuccess) return LBIB_EHIP;
   if (loss) return mlp_loss(h, B, loss);
   return LBIB_OK;
@@ -2116,44 +2058,13 @@ void lbib_mlp_destroy(lbib_mlp* h) { delete h; }
 
 // ---------------------------------------------------------------------------
 // forward pass without a workspace, for callers that cannot allocate: the
-// hidden activations live in a fixed device array of the library.  The
-// array's name is a host-side stand-in in host code; its device address is
-// looked up once per device and only that address is passed to kernels.
+// hidden activations never leave a workgroup's LDS
 constexpr int MLP_NOALLOC_ROWS = 4096;
-static __device__ __align__(256) float scratch[2 * MLP_NOALLOC_ROWS * MLP_H];
-
-namespace {
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mu;
-float* g_scratch[kMaxDevices] = {};  // device address of scratch, per device
-
-// address of the current device's scratch (looked up on the first call made
-// with that device current)
-int scratch_address(float** out) {
-  int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess) return LBIB_EHIP;
-  if (dev < 0 || dev >= kMaxDevices) return LBIB_EINVAL;
-  std::lock_guard<std::mutex> lock(g_scratch_mu);
-  if (!g_scratch[dev]) {
-    void* ptr = nullptr;
-    if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return LBIB_EHIP;
-    g_scratch[dev] = static_cast<float*>(ptr);
-  }
-  *out = g_scratch[dev];
-  return LBIB_OK;
-}
-}  // namespace
 
 extern "C" int lbib_mlp_forward_noalloc(const float* params_dev, const float* x_dev, int B, float* y_dev,
                                         void* hip_stream) {
   if (!params_dev || !x_dev || !y_dev || B < 1) return LBIB_EINVAL;
   if (B > MLP_NOALLOC_ROWS) return LBIB_ENOMEM;
-  float* base = nullptr;
-  const int rc = scratch_address(&base);
-  if (rc) return rc;
-  // A1 and A2 are written in full before they are read: nothing to clear
-  float* A1 = base;
-  float* A2 = base + (size_t)MLP_NOALLOC_ROWS * MLP_H;
-  mlp_forward_raw(params_dev, x_dev, B, y_dev, nullptr, A1, nullptr, A2, (hipStream_t)hip_stream);
+  mlp_forward(params_dev, x_dev, B, y_dev, (hipStream_t)hip_stream);
   return hipGetLastError() == hipSuccess ? LBIB_OK : LBIB_EHIP;
 }
