@@ -200,13 +200,12 @@ int lbib_timing_enable(lbib_sim* s, int on);
 int lbib_timing_read(lbib_sim* s, double* ms, int n, int* steps);
 
 /* Launch shape of the fused lattice kernel (a tuning knob; results do not
-   depend on it): D2Q9, block_x lanes per workgroup (64, 128, 192 or 256;
-   block_x - 4 interior columns); D3Q19, block_x the x extent of a
+   depend on it): D3Q19, block_x the x extent of a
    workgroup's tile of 256 nodes (16, 32 (the default) or 64; the y extent
-   is 256 / block_x); seg rows (D3Q19: planes) per workgroup, nxcd the number of L2 domains
-   workgroups are dealt to in turn, ring the rows held in registers (3, or 4
-   to load the next row while the current ones are computed).  0 keeps the
-   current value; seg = -1 returns to the automatic choice (as many
+   is 256 / block_x); D2Q9, block_x one of 64, 128, 192 or 256 and ring 3 or
+   4, accepted and reported without effect (a workgroup is one wave, which
+   holds three rows); seg rows (D3Q19: planes) per workgroup, nxcd the number of L2 domains
+   workgroups are dealt to in turn.  0 keeps the current value; seg = -1 returns to the automatic choice (as many
    workgroups as fit on the GPU at once, so none waits for a second round),
    nxcd = -1 to the automatic dealing (eight domains, the XCDs of the
    MI355X, so that workgroups sharing halo rows or lines meet in one L2).  A value
@@ -304,9 +303,9 @@ void lbib_destroy(lbib_sim* s);
 /* ------------------------------------------------------------------------
    Batches: n independent D2Q9 simulations (FP32 storage, n <= 256) in one
    workspace, stepped together.  Each phase of a step is one launch over all
-   members (the lattice update one launch per size class: lattice width
-   <= 128, <= 256, larger), and the step is captured once per buffer parity
-   in a hipGraph and replayed (on a stream that can be captured, i.e. not
+   members (the lattice update one more for members with a relaxation time
+   other than 1), and the step is captured once per buffer parity and form of
+   the state in a hipGraph and replayed (on a stream that can be captured, i.e. not
    the legacy default stream; otherwise the launches are enqueued directly).
    Every member gives the same results, bit for bit, as the same
    simulation created alone.
@@ -330,9 +329,9 @@ int lbib_batch_create(int n, const lbib_params* params, void* dev_workspace, siz
 int lbib_batch_member(lbib_sim* batch, int k, lbib_sim** member);
 
 /* Lattice-kernel shape of size class size_class (0: width <= 128, 1:
-   <= 256, 2: wider; -1: all): lanes per workgroup (64, 128, 192, 256), rows per
-   work item (-1: automatic, one resident round of the class's items) and
-   register ring depth (3 or 4); 0 keeps a value.  get_launch also returns
+   <= 256, 2: wider; -1: all): rows per work item (-1: automatic, one
+   resident round of the batch's items); lanes (64, 128, 192, 256) and ring (3
+   or 4) are accepted and reported without effect; 0 keeps a value.  get_launch also returns
    the number of members in the class, and the rows in use once the batch
    has stepped. */
 int lbib_batch_set_launch(lbib_sim* batch, int size_class, int block_x, int seg, int ring);

@@ -1,8 +1,8 @@
 """Launch-shape autotuner for batched D2Q9 simulations.
 
 For every size class present in a batch (lattice width <= 128, <= 256,
-wider) it times candidate shapes of the batched lattice kernel -- lanes per
-workgroup, rows per work item, register ring depth -- for about twenty steps
+wider) it times candidate shapes of the batched lattice kernel -- the rows per
+work item -- for about twenty steps
 on a throwaway batch of the same workloads, one class at a time with the
 other classes fixed, and keeps the fastest.  Results are cached as JSON keyed
 by GPU architecture, lattice, storage and size class, so a later batch on the
@@ -16,7 +16,8 @@ import time
 
 from . import lbib
 
-CANDIDATES = [(bx, seg, ring) for bx in (64, 128, 192, 256) for ring in (3, 4) for seg in (-1, 16, 48)]
+# a strip is one wave wide whatever the lanes and the ring: the rows decide
+CANDIDATES = [(64, seg, 3) for seg in (-1, 4, 8, 12, 16, 24, 32, 48)]
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "lbib", "autotune.json")
 
 

@@ -4,10 +4,10 @@
 // walks a queue of work items (a membrane, an active tile, a marker, a
 // (strip, segment) of a lattice) spread over the members, finds the member
 // of each item by binary search over prefix sums, and runs the same device
-// code the single-simulation kernels run.  The lattice kernel runs once per
-// size class, since the strip width (lanes per workgroup) is chosen per
-// class, with one (strip, segment) item per workgroup.  All members advance
-// with the same buffer parity.
+// code the single-simulation kernels run.  The lattice kernel has one (strip,
+// segment) item per wave; members that relax (some tau not 1) run in a launch
+// of their own.  All members advance with the same buffer parity and hold the
+// same form of the state (populations, or Macro2 between the steps of a call).
 #pragma once
 #include "common.h"
 #include "k_ibm.h"
@@ -17,10 +17,12 @@ namespace lb {
 
 constexpr int BATCH_MAX = 256;  // members per batch
 
-template <class St>
+template <class St, typename R>
 struct BMember {
-  LBParams P;  // strips and segments for the member's size class
-  St a, b;     // population buffers (parity 0 reads a, writes b)
+  LBParams P;     // segments for the member's size class
+  int nstrip[2];  // strips when the step reads populations, and when it reads Macro2
+  St a, b;        // population buffers (parity 0 reads a, writes b)
+  MacroStore2<R> ma, mb;  // the same memory between the steps of a call
   MemDev md;
   TileMap tm;
   CoupArgs ca;
@@ -32,6 +34,15 @@ struct BMember {
 // The member descriptors live in global memory; every kernel copies the one
 // it works on into registers first, so the stores of the step cannot be
 // taken to alias it (which would force a reload after each store).
+
+// the buffer a step reads (or, dst, writes) at a parity, in the form MACRO
+template <bool MACRO, class St, typename R>
+__device__ __forceinline__ auto batch_buffer(const BMember<St, R>& t, bool second) {
+  if constexpr (MACRO)
+    return second ? t.mb : t.ma;
+  else
+    return second ? t.b : t.a;
+}
 
 // index i in [0, n) with pre[i] <= v < pre[i + 1]
 __device__ __forceinline__ int prefix_find(const int* pre, int n, int v) {
@@ -46,8 +57,8 @@ __device__ __forceinline__ int prefix_find(const int* pre, int n, int v) {
   return lo;
 }
 
-template <class St>
-__global__ void kb_begin(BMember<St>* T, int n) {
+template <class St, typename R>
+__global__ void kb_begin(BMember<St, R>* T, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) {
     int* ts = T[i].tm.tstate;
@@ -57,8 +68,8 @@ __global__ void kb_begin(BMember<St>* T, int n) {
 }
 
 // one workgroup per (member, membrane)
-template <class St, int NT>
-__global__ __launch_bounds__(NT) void kb_tiles(const BMember<St>* T, const int2* mems) {
+template <class St, typename R, int NT>
+__global__ __launch_bounds__(NT) void kb_tiles(const BMember<St, R>* T, const int2* mems) {
   const int2 e = mems[blockIdx.x];
   const MemDev md = T[e.x].md;
   const TileMap tm = T[e.x].tm;
@@ -68,8 +79,8 @@ __global__ __launch_bounds__(NT) void kb_tiles(const BMember<St>* T, const int2*
 }
 
 // persistent: the active tiles of all members
-template <class St, typename R, int NT>
-__global__ __launch_bounds__(NT, 2) void kb_coupling2d(const BMember<St>* T, int n, int parity) {
+template <class St, typename R, int NT, bool MACRO>
+__global__ __launch_bounds__(NT, 2) void kb_coupling2d(const BMember<St, R>* T, int n, int parity) {
   __shared__ int s_pre[BATCH_MAX + 1];
   for (int i = threadIdx.x; i < n; i += NT) s_pre[i + 1] = T[i].tm.tstate[0];
   if (threadIdx.x == 0) s_pre[0] = 0;
@@ -84,14 +95,14 @@ __global__ __launch_bounds__(NT, 2) void kb_coupling2d(const BMember<St>* T, int
     const TileMap tm = T[i].tm;
     const CoupArgs ca = T[i].ca;
     double* Ifield = T[i].Ifield;
-    const St cur = parity ? T[i].b : T[i].a;
-    coupling2d_tile<St, R, NT>(md, tm, ca, Ifield, cur, item - s_pre[i]);
+    const auto cur = batch_buffer<MACRO>(T[i], parity != 0);
+    coupling2d_tile<decltype(cur), R, NT>(md, tm, ca, Ifield, cur, item - s_pre[i]);
   }
 }
 
 // markers of all members (mpre: marker prefix, n + 1 entries)
-template <class St>
-__global__ void kb_forcespread2d(const BMember<St>* T, const int* __restrict__ mpre, int n) {
+template <class St, typename R>
+__global__ void kb_forcespread2d(const BMember<St, R>* T, const int* __restrict__ mpre, int n) {
   const int tid = blockIdx.x * blockDim.x + threadIdx.x;
   const int gf = tid >> 4, k = tid & 15;
   const bool live = gf < mpre[n];
@@ -102,8 +113,8 @@ __global__ void kb_forcespread2d(const BMember<St>* T, const int* __restrict__ m
   forcespread2d_run(md, fib, nx, ny, wy, live ? gf - mpre[i] : 0, k, live);
 }
 
-template <class St, typename R>
-__global__ void kb_interp2d(const BMember<St>* T, const int* __restrict__ mpre, int n, int parity) {
+template <class St, typename R, bool MACRO>
+__global__ void kb_interp2d(const BMember<St, R>* T, const int* __restrict__ mpre, int n, int parity) {
   const int tid = blockIdx.x * blockDim.x + threadIdx.x;
   const int gf = tid >> 4, k = tid & 15;
   const bool live = gf < mpre[n];
@@ -112,38 +123,35 @@ __global__ void kb_interp2d(const BMember<St>* T, const int* __restrict__ mpre, 
   const LBParams P = T[i].P;
   const double* force = T[i].force;
   // after the lattice update the current state is in the buffer written
-  const St cur = parity ? T[i].a : T[i].b;
-  interp2d_run<St, R>(md, cur, P, force, live ? gf - mpre[i] : 0, k, live);
+  const auto cur = batch_buffer<MACRO>(T[i], parity == 0);
+  interp2d_run<decltype(cur), R>(md, cur, P, force, live ? gf - mpre[i] : 0, k, live);
 }
 
-// one workgroup per (strip, segment) item of the members of one size class
-// (cm: their member ids, bpre: item prefix, ncm + 1 entries)
-template <class St, typename R, int BX, int NS, int WPE, int FORM = 0>
-__global__ __launch_bounds__(BX, WPE) void kb_lb2d(const BMember<St>* T, const int* __restrict__ cm,
-                                                   const int* __restrict__ bpre, int ncm, int parity) {
-  // one work item per workgroup: without a loop over items the kernel
-  // fits the single kernel's register budget (three waves per SIMD)
-  const int total = bpre[ncm];
-  {
-    if ((int)blockIdx.x >= total) return;
-    // items dealt to the eight XCDs in contiguous runs, so the neighbouring
-    // segments of a member share their halo rows in one L2
-    const int item = (int)gridDim.x == total ? dealt_index((int)blockIdx.x, total, 8) : (int)blockIdx.x;
-    const int q = prefix_find(bpre, ncm, item);
-    const int i = cm[q];
-    const LBParams P = T[i].P;
-    const St src = parity ? T[i].b : T[i].a, dst = parity ? T[i].a : T[i].b;
-    const int* tflag = T[i].tm.tflag;
-    const int* tstate = T[i].tm.tstate;
-    const double* Ifield = T[i].Ifield;
-    long long* fib = T[i].fib;
-    double* force = T[i].force;
-    int strip, sgm;
-    strip_segment(item - bpre[q], P.nstrip, P.nseg, 1, strip, sgm);
-    const int y0 = sgm * P.seg, y1 = min(y0 + P.seg, P.ny);
-    lb2d_run<St, R, BX, NS, FORM>(src, dst, P, strip, y0, y1, (sgm & 1) ? -1 : 1, tflag, tstate, Ifield, fib,
-                                  force);
-  }
+// one wave per (strip, segment) item of the members listed in cm (bpre: item
+// prefix, ncm + 1 entries)
+template <class St, typename R, int FORM, bool SM, bool DM, bool RELAX>
+__global__ __launch_bounds__(64, (step2d_waves<R, RELAX>())) void kb_lb2d(const BMember<St, R>* T,
+                                                                         const int* __restrict__ cm,
+                                                                         const int* __restrict__ bpre, int ncm,
+                                                                         int parity) {
+  // items dealt to the eight XCDs in contiguous runs, so the neighbouring
+  // segments of a member share their halo rows in one L2
+  const int item = dealt_index((int)blockIdx.x, (int)gridDim.x, 8);
+  const int q = prefix_find(bpre, ncm, item);
+  const int i = cm[q];
+  const LBParams P = T[i].P;
+  const auto src = batch_buffer<SM>(T[i], parity != 0);
+  const auto dst = batch_buffer<DM>(T[i], parity == 0);
+  const int* tflag = T[i].tm.tflag;
+  const int* tstate = T[i].tm.tstate;
+  const double* Ifield = T[i].Ifield;
+  long long* fib = T[i].fib;
+  double* force = T[i].force;
+  int strip, sgm;
+  strip_segment(item - bpre[q], T[i].nstrip[SM], P.nseg, 1, strip, sgm);
+  const int y0 = sgm * P.seg, y1 = min(y0 + P.seg, P.ny);
+  step2d_run<St, R, FORM, decltype(src), decltype(dst), RELAX>(src, dst, P, strip, y0, y1, tflag, tstate,
+                                                               Ifield, fib, force);
 }
 
 }  // namespace lb

@@ -532,7 +532,7 @@ __device__ __forceinline__ void coupling2d_tile(const MemDev& md, const TileMap&
         const bool back = L::cy[i] > 0 ? wlo : (L::cy[i] < 0 ? whi : false);
         const long long row = L::cy[i] > 0 ? rlo : (L::cy[i] < 0 ? rhi : cnode - xc);
         const int col = L::cx[i] > 0 ? xlo : (L::cx[i] < 0 ? xhi : xc);
-        hmov[i - 1] = cur.template load<R>(2, back ? L::opp[i] : i, back ? cnode : row + col);
+        hmov[i - 1] = cur.template pull<R>(2, i, back, back ? cnode : row + col);
       }
     }
     const double xt = tx * TILE2 + 0.5 * (TILE2 - 1), yt = ty * TILE2 + 0.5 * (TILE2 - 1);
@@ -1328,7 +1328,7 @@ __device__ __forceinline__ void interp2d_run(const MemDev& md, const St& cur, co
         const bool back = L::cy[i] > 0 ? wlo : (L::cy[i] < 0 ? whi : false);
         const long long row = L::cy[i] > 0 ? rlo : (L::cy[i] < 0 ? rhi : node - xw);
         const int col = L::cx[i] > 0 ? xlo : (L::cx[i] < 0 ? xhi : xw);
-        const double v = (double)cur.template load<R>(0, back ? L::opp[i] : i, back ? node : row + col);
+        const double v = (double)cur.template pull<R>(0, i, back, back ? node : row + col);
         d += v;
         jx += L::cx[i] * v;
         jy += L::cy[i] * v;

@@ -1,30 +1,44 @@
 // k_lb.h -- the fused lattice-Boltzmann step (Sec. 3.1) for D2Q9.
 //
-// One kernel does, per node and time step: pull-streaming of f, g, h, the
-// moments of eq. MomentsDFs, the Laplacians of rho, phi, psi, the chemical
-// potentials of Appendix A (with the coupling term of Sec. 3.1), their
-// gradients, the force of eqs. ForcingTermLBE / ForceFE plus the spread
+// One kernel does, per node and time step: streaming of f, g, h, the moments
+// of eq. MomentsDFs, the Laplacians and gradients of the concentrations, the
+// chemical potentials and pressure tensor of Appendix A (with the coupling
+// term of Sec. 3.1), the force of eqs. ForcingTermLBE / ForceFE plus the spread
 // membrane force, the velocities of eqs. ActualFluidVel / VelCorrection and
-// the BGK + exact-difference collision of eq. LBE, writing the post-collision
-// populations.  Populations are read once and written once per step.
+// the BGK + exact-difference collision of eq. LBE.
 //
-// Dependency chain: the collision at row c needs grad mu at c, i.e. mu on
-// rows c-1..c+1, i.e. moments on rows c-2..c+2.  A workgroup owns a strip of
-// BX-4 interior columns (BX lanes, two halo columns each side) and marches
-// along a segment of rows (up or down) with a three-stage software pipeline:
-//   iteration k:  M  pull row r into registers, moments -> LDS ring
-//                 U  mu on the previous row from the moment ring -> LDS ring
-//                 C  collide the row before that with the populations pulled
-//                    two iterations earlier (still in registers) and store.
-// Halo columns are recomputed by the neighbouring strip; halo rows only at
-// segment ends.  Registers hold three rows of populations; the loop is
-// unrolled by three so every register index is a compile-time constant.
+// Dependency chain: the collision at row c needs the divergence of the
+// pressure tensor there, i.e. the tensor on rows c-1..c+1, i.e. moments on
+// rows c-2..c+2.  A wave owns a strip of 64 columns and marches up a segment
+// of rows; per iteration it takes one row in and does
+//   M  the moments of a row
+//   U  potentials and tensor of the row below it
+//   C  force and collision of the row below that.
+// A lane keeps its own column of every stencil in registers (each 3 x 3
+// stencil is a sum over the three rows of a row's own combination of its
+// west, centre and east values) and takes its west and east neighbours' values
+// by lane shifts, so a row needs no LDS and no barrier, and waves run
+// independently of each other.  Columns at the strip's ends and rows beyond
+// the segment's ends are formed by two waves.
 //
-// Precision: moving populations and their collision use the storage's real
-// type R (FP32 or FP64).  Moments, chemical potentials, their stencils and
-// the force are FP64: the chemical potential is a sum of terms much larger
-// than itself near interfaces, and its Laplacian/gradient chain would turn
-// single-precision rounding of phi and psi into force noise.
+// Two forms of the state.  Between calls the state is the populations after
+// collision.  With tau = tau_phi = tau_psi = 1 (Sec. 3.1's choice, and the
+// default) a collision replaces every population by its equilibrium, so
+// the populations of a node are a function of nine of its numbers: density,
+// u + delta u, v, Gamma mu and the order parameters (Macro2).  The steps
+// inside a call of several then read and write those, 44 bytes per node
+// instead of 116 in FP32, and every node's populations are evaluated (and
+// rounded to the storage format) where they stream from: the call's first
+// step reads populations, its last one writes them, and any division of the
+// same steps into calls gives the same bits.
+//
+// Precision: populations and their equilibria use the storage's real type R
+// (FP32 or FP64).  Moments, chemical potentials, their stencils and the force
+// are FP64: the chemical potential is a sum of terms much larger than itself
+// near interfaces, and its Laplacian/gradient chain would turn
+// single-precision rounding of phi and psi into force noise.  Products and
+// sums are written as the fused operations they are, with the compiler's own
+// contraction off, so every kernel rounds alike.
 #pragma once
 #include <type_traits>
 
@@ -217,337 +231,666 @@ __device__ __forceinline__ void moments9(const R* pf, const R* pg, const R* ph, 
   psi = h0 + (double)sh;
 }
 
-// NS = 3: each iteration pulls its row and then waits for it.  NS = 4: the
-// row of the next iteration is pulled at the start of this one (a register
-// ring of four rows), so the loads of one row are in flight while the
-// previous rows are computed.  WPE: waves per SIMD the register budget is
-// sized for.
-// One (strip, segment) of the lattice: the whole march of a workgroup.
+// the same in the order in which the rows' shares of a march add up, which a
+// mirror in y leaves alone bit for bit (ghost rows beyond a wall are the
+// lattice mirrored)
+template <typename R>
+__device__ __forceinline__ void moments9m(const R* f, const R* g, const R* h, double g0, double h0, R& d, R& jx,
+                                          R& jy, double& phi, double& psi) {
+  const R n = f[3] + (f[5] + f[7]), s = f[4] + (f[6] + f[8]);
+  d = (f[0] + (f[1] + f[2])) + (n + s);
+  jx = (f[1] - f[2]) + ((f[5] - f[7]) + (f[8] - f[6]));
+  jy = n - s;
+  phi = g0 + (double)((g[1] + g[2]) + ((g[3] + (g[5] + g[7])) + (g[4] + (g[6] + g[8]))));
+  psi = h0 + (double)((h[1] + h[2]) + ((h[3] + (h[5] + h[7])) + (h[4] + (h[6] + h[8]))));
+}
+
+// ---------------------------------------------------------------------------
+// equilibria
+
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// 1/x to the last bit or so: the hardware's estimate and two Newton steps
+__device__ __forceinline__ double recip(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma_(fma_(-x, r, 1.0), r, r);
+  return fma_(fma_(-x, r, 1.0), r, r);
+}
+
+// value of the lane to the west (lane - 1) or east (lane + 1) within the
+// wave; the lanes at the ends get 0
+template <int CTRL>
+__device__ __forceinline__ int lane_mov(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ float lane_mov(float v) {
+  return __builtin_bit_cast(float, lane_mov<CTRL>(__builtin_bit_cast(int, v)));
+}
+template <int CTRL>
+__device__ __forceinline__ double lane_mov(double v) {
+  const long long b = __builtin_bit_cast(long long, v);
+  const unsigned lo = (unsigned)lane_mov<CTRL>((int)b), hi = (unsigned)lane_mov<CTRL>((int)(b >> 32));
+  return __builtin_bit_cast(double, (long long)(((unsigned long long)hi << 32) | lo));
+}
+template <typename T>
+__device__ __forceinline__ T west(T v) { return lane_mov<0x138>(v); }  // wave_shr:1
+template <typename T>
+__device__ __forceinline__ T east(T v) { return lane_mov<0x130>(v); }  // wave_shl:1
+
+// What the populations of a node after a collision with tau = 1 depend on:
+// dr = rho - rho0, w = u + delta u, v = u + delta u / 2, gm = 3 Gamma_phi
+// mu_phi, hm = 3 Gamma_psi mu_psi, and the order parameters.  (For f the
+// equilibrium at u and the exact-difference term add to the equilibrium at
+// u + delta u.)
+template <typename R>
+struct Macro2 {
+  R dr, wx, wy, vx, vy, gm, hm;
+  double phi, psi;
+};
+
+// the pressure shift of component densities (zero for equal ones), eq.
+// MassDensity: w_i sp joins every moving population of f, -(1 - w_0) sp the rest one
+template <typename R>
+__device__ __forceinline__ R eq_shift(double p0, double p1, double phi, double psi) {
+#pragma clang fp contract(off)
+  return (R)(-fma_(p0, phi, p1 * psi));
+}
+
+// The two populations along +-c of a set whose rest population closes the sum
+// in FP64 (g, h): a (1 + 3 c.u + ..) + b with c.u = cu, q = -3/2 u^2, a3 = 3 a.
+template <typename R>
+__device__ __forceinline__ void eq_pair(R a, R a3, R b, R q, R cu, R& fp, R& fm) {
+#pragma clang fp contract(off)
+  const R base = fma_(a, fma_(R(4.5) * cu, cu, q), b);
+  fp = fma_(a3, cu, base);
+  fm = fma_(-a3, cu, base);
+}
+
+// The same for f, whose rounding is the node's mass and moves the fluid: the
+// weight multiplies last, so no rounding is shared by the populations.
+template <typename R>
+__device__ __forceinline__ void eq_pair_f(R w, R rr, R drs, R q, R cu, R& fp, R& fm) {
+#pragma clang fp contract(off)
+  const R t = fma_(R(4.5) * cu, cu, q);
+  fp = w * fma_(rr, fma_(R(3), cu, t), drs);
+  fm = w * fma_(rr, fma_(R(-3), cu, t), drs);
+}
+
+// f_i^eq(rho, c) - w_i rho0 for all i
+template <typename R>
+__device__ __forceinline__ void eq9_f(R rho0, R dr, R sp, R cx, R cy, R* f) {
+#pragma clang fp contract(off)
+  using L = Lattice<9>;
+  const R rr = rho0 + dr, drs = dr + sp;
+  const R q = R(-1.5) * fma_(cx, cx, cy * cy);
+  f[0] = fma_(R(L::w(0)), fma_(rr, q, dr), -(R(1.0 - L::w(0)) * sp));
+  const R w1 = R(L::w(1)), w5 = R(L::w(5));
+  eq_pair_f(w1, rr, drs, q, cx, f[1], f[2]);
+  eq_pair_f(w1, rr, drs, q, cy, f[3], f[4]);
+  eq_pair_f(w5, rr, drs, q, cx + cy, f[5], f[6]);
+  eq_pair_f(w5, rr, drs, q, cx - cy, f[8], f[7]);
+}
+
+// the moving g_i^eq (order parameter ph, gm = 3 Gamma mu), i = 1..8, at v
+template <typename R>
+__device__ __forceinline__ void eq9_g(R ph, R gm, R cx, R cy, R* g) {
+#pragma clang fp contract(off)
+  using L = Lattice<9>;
+  const R q = R(-1.5) * fma_(cx, cx, cy * cy);
+  const R a1 = ph * R(L::w(1)), a13 = R(3) * a1, b1 = gm * R(L::w(1));
+  const R a5 = ph * R(L::w(5)), a53 = R(3) * a5, b5 = gm * R(L::w(5));
+  eq_pair(a1, a13, b1, q, cx, g[1], g[2]);
+  eq_pair(a1, a13, b1, q, cy, g[3], g[4]);
+  eq_pair(a5, a53, b5, q, cx + cy, g[5], g[6]);
+  eq_pair(a5, a53, b5, q, cx - cy, g[8], g[7]);
+}
+
+// one population of f or (F false) of g or h in the direction of population i
+// or (flip) its opposite: the same operations on the same values (a product
+// by +-1 or 0 is exact)
+template <bool F, typename R>
+__device__ __forceinline__ R eq9_one(R a, R b, int i, bool flip, R cx, R cy) {
+#pragma clang fp contract(off)
+  using L = Lattice<9>;
+  const R q = R(-1.5) * fma_(cx, cx, cy * cy), w = R(L::w(i));
+  const R cu = L::cx[i] * cx + L::cy[i] * cy;
+  const R t = fma_(R(4.5) * cu, cu, q);
+  if (F) return w * fma_(a, fma_(flip ? R(-3) : R(3), cu, t), b);
+  const R aw = a * w;
+  return fma_(flip ? -(R(3) * aw) : R(3) * aw, cu, fma_(aw, t, b * w));
+}
+
+// rest populations close the zeroth moments (eq. EDF, i = 0); the eight
+// moving ones are summed in FP64 in an order that a mirror in y leaves alone
+template <typename R>
+__device__ __forceinline__ double eq9_rest(double phi, const R* g) {
+#pragma clang fp contract(off)
+  return phi - ((((double)g[1] + (double)g[2]) + ((double)g[3] + (double)g[4])) +
+                (((double)g[5] + (double)g[8]) + ((double)g[6] + (double)g[7])));
+}
+
+// a node's populations
+template <typename R>
+__device__ __forceinline__ void macro_pops(R rho0, double p0, double p1, const Macro2<R>& s, R* pf, R* pg, R* ph,
+                                           double& g0, double& h0) {
+  eq9_f(rho0, s.dr, eq_shift<R>(p0, p1, s.phi, s.psi), s.wx, s.wy, pf);
+  eq9_g((R)s.phi, s.gm, s.vx, s.vy, pg);
+  eq9_g((R)s.psi, s.hm, s.vx, s.vy, ph);
+  g0 = eq9_rest(s.phi, pg);
+  h0 = eq9_rest(s.psi, ph);
+}
+
+// The state between the steps of one call (tau = 1): planes dr, wx, wy, vx,
+// vy, gm, hm in R and phi, psi in FP64.  Planes of one type stay below 4 GiB
+// (checked on the host), so a node is a 32-bit byte offset; a store to node
+// -1 is out of the buffer's range and dropped, so a store needs no branch.
+template <typename R>
+struct MacroStore2 {
+  R* p;
+  double* r;
+  unsigned N;
+  double rho0, p0, p1;
+  static constexpr bool kMacro = true;
+  static constexpr int kR = 7;
+  static constexpr long long bytes_per_node() { return kR * (long long)sizeof(R) + 16; }
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rp() const {
+    return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)(kR * N * (unsigned)sizeof(R)), 0x00020000);
+  }
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rr() const {
+    return __builtin_amdgcn_make_buffer_rsrc(r, 0, (int)(2 * N * 8u), 0x00020000);
+  }
+  __device__ __forceinline__ R get(int k, unsigned node) const {
+    if constexpr (sizeof(R) == 4)
+      return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(rp(), (int)(node * 4), (int)(k * N * 4), 0));
+    else
+      return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b64(rp(), (int)(node * 8), (int)(k * N * 8), 0));
+  }
+  __device__ __forceinline__ double getd(int k, unsigned node) const {
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rr(), (int)(node * 8), (int)(k * N * 8), 0));
+  }
+  __device__ __forceinline__ void put(int k, unsigned node, R v) const {
+    if constexpr (sizeof(R) == 4)
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rp(), (int)(node * 4), (int)(k * N * 4), 0);
+    else
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rp(), (int)(node * 8), (int)(k * N * 8), 0);
+  }
+  __device__ __forceinline__ void putd(int k, unsigned node, double v) const {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rr(), (int)(node * 8), (int)(k * N * 8), 0);
+  }
+  __device__ __forceinline__ Macro2<R> node(unsigned n) const {
+    return Macro2<R>{get(0, n), get(1, n), get(2, n), get(3, n), get(4, n), get(5, n), get(6, n), getd(0, n), getd(1, n)};
+  }
+  __device__ __forceinline__ void set_node(unsigned n, const Macro2<R>& s) const {
+    put(0, n, s.dr);
+    put(1, n, s.wx);
+    put(2, n, s.wy);
+    put(3, n, s.vx);
+    put(4, n, s.vy);
+    put(5, n, s.gm);
+    put(6, n, s.hm);
+    putd(0, n, s.phi);
+    putd(1, n, s.psi);
+  }
+  // single populations, for the kernels that read a few nodes near a membrane
+  template <typename T>
+  __device__ __forceinline__ T pull(int set, int i, bool flip, long long nd) const {
+#pragma clang fp contract(off)
+    const unsigned n = (unsigned)nd;
+    if (i == 0) return (T)rest(set, nd);
+    R v;
+    if (set == 0) {
+      const R dr = get(0, n);
+      v = eq9_one<true, R>((R)rho0 + dr, dr + eq_shift<R>(p0, p1, getd(0, n), getd(1, n)), i, flip, get(1, n), get(2, n));
+    } else {
+      v = eq9_one<false, R>((R)getd(set - 1, n), get(4 + set, n), i, flip, get(3, n), get(4, n));
+    }
+    return (T)v;
+  }
+  __device__ __forceinline__ double rest(int set, long long nd) const {
+    R pf[9], pg[9], ph[9];
+    double g0, h0;
+    macro_pops<R>((R)rho0, p0, p1, node((unsigned)nd), pf, pg, ph, g0, h0);
+    return set == 0 ? (double)pf[0] : (set == 1 ? g0 : h0);
+  }
+};
+
+// columns at each end of a wave's strip that the neighbouring strips form too:
+// the pressure tensor needs moments one column out, the force the tensor one
+// column out, and moments from Macro2 the populations one column out
+template <class Src>
+constexpr int strip_halo() {
+  return Src::kMacro ? 3 : 2;
+}
+// waves per SIMD the register budget is sized for
+template <typename R, bool RELAX>
+constexpr int step2d_waves() {
+  return sizeof(R) == 8 ? 1 : (RELAX ? 2 : 2);
+}
+
+// One (strip, rows [y0, y1)) of the lattice: the whole march of a wave.
 // FORM 0: the force of eq. ForceFE in its potential form, -sum q grad mu_q
 // over q = rho, phi, psi (eq. GradPT).  FORM 1: its divergence form,
 // -div P' - psi grad kappa_c (psi - I), with the non-ideal pressure tensor P'
-// of Appendix A formed per node in the U stage and its divergence taken in
-// the C stage (the two forms agree up to the discretisation error).
-template <class St, typename R, int BX, int NS, int FORM = 0>
-__device__ __forceinline__ void lb2d_run(const St& src, const St& dst, const LBParams& P, int strip, int y0,
-                                         int y1, int dir, const int* __restrict__ tflag,
-                                         const int* __restrict__ tstate, const double* __restrict__ Ifield,
-                                         long long* __restrict__ fib, double* __restrict__ force) {
-  static_assert(NS == 3 || NS == 4, "ring of three or four rows");
-  constexpr int W = BX - 4;
-  __shared__ double s_m[3][3][BX];  // moment ring [slot][drho, phi, psi][lane]
-  __shared__ double s_j[3][2][BX];  // momentum ring [slot][jx, jy][lane]
-  // chemical-potential ring [slot][mu_rho, mu_phi, mu_psi'][lane]; with
-  // FORM 1 its first field holds P'_xx instead of mu_rho
-  __shared__ double s_u[3][3][BX];
-  // FORM 1 only: [slot][P'_xy, P'_yy, kappa_c (psi - I)][lane]
-  __shared__ double s_p[3][3][FORM == 1 ? BX : 1];
-
-  const int j = threadIdx.x;
-  const int xc = strip * W - 2 + j;
+// of Appendix A (the two forms agree up to the discretisation error).
+// Src, Dst: St (populations) or MacroStore2.  RELAX: a collision needs the
+// populations that came in (some tau differs from 1, or the storage rounds
+// them to 16 bits); Src and Dst are St.
+template <class St, typename R, int FORM, class Src, class Dst, bool RELAX>
+__device__ __forceinline__ void step2d_run(const Src& src, const Dst& dst, const LBParams& P,
+                                           int strip, int y0, int y1, const int* __restrict__ tflag,
+                                           const int* __restrict__ tstate, const double* __restrict__ Ifield,
+                                           long long* __restrict__ fib, double* __restrict__ force) {
+#pragma clang fp contract(off)
+  constexpr bool SM = Src::kMacro, DM = Dst::kMacro;
+  static_assert(!RELAX || (!SM && !DM), "relaxation needs the populations");
+  constexpr int H = strip_halo<Src>();
+  constexpr int LAG = SM ? 1 : 0;  // rows between the row taken in and the row of the moments
+  const int j = threadIdx.x & 63;
+  const int xc = strip * (64 - 2 * H) - H + j;
   const int x = wrap(xc, P.nx);
-  const bool interior = (j >= 2) && (j < BX - 2) && (xc < P.nx);
-  const int K = (y1 - y0) + 4;
-  const int rbase = dir > 0 ? y0 - 2 : y1 + 1;
-
+  const bool interior = j >= H && j < 64 - H && xc < P.nx;
+  const int K = (y1 - y0) + 2 * H, rbase = y0 - H;
   const int stamp = tstate[1];  // tiles flagged with this step's stamp are active
   const int tsh = __builtin_ctz((unsigned)P.tile);  // log2 of the tile edge
-  R pf[NS][9], pg[NS][9], ph[NS][9];
-  double g0[NS], h0[NS];
-  // tile flag of the row in each register slot, loaded with the row; the
-  // membrane fields of rows k-1 and k-2 are then fetched at the start of
-  // iteration k, beside the pull, instead of after a dependent flag load
-  int tfl[NS];
-  // NS = 4: the membrane fields a row needs (profile field on the row of the
-  // chemical potential, spread force on the row of the collision) are
-  // fetched one iteration early, before that iteration's stores.  Waits
-  // count outstanding loads and stores in issue order, so fetched after the
-  // next row's prefetch they would make the wait for them a wait for the
-  // prefetch (and for the stores) as well.
-  // Two register slots, alternating with the row parity (the loop is
-  // unrolled by four), so no value is copied between registers while its
-  // load may still be in flight.
-  double Ipre_c[2] = {0.0, 0.0};
-  long long fb0_c[2] = {0, 0}, fb1_c[2] = {0, 0};
-  bool cact_c[2] = {false, false};
+  const int xt = x >> tsh;
+  const R rho0 = (R)P.rho0;
+  const double km[3] = {P.k1, P.k2, P.k3};
 
-  auto load_row = [&](auto slot_c, int k) {
-    constexpr int S = decltype(slot_c)::value;
-    const int ry = fd_row_near(rbase + dir * k, P.ny, P.wall_y);
-    pull9(src, P, x, ry, pf[S], pg[S], ph[S], g0[S], h0[S]);
-    tfl[S] = tflag[(ry >> tsh) * P.ntx + (x >> tsh)];
+  // the row taken in: loaded one iteration ahead of its use (RELAX: at its use)
+  Macro2<R> nxt = {};
+  R npf[9], npg[9], nph[9];
+  double ng0 = 0.0, nh0 = 0.0;
+  int nfl = 0;
+  // RELAX: populations of the last three rows
+  R kf[RELAX ? 3 : 1][9], kg[RELAX ? 3 : 1][9], kh[RELAX ? 3 : 1][9];
+  double kg0[RELAX ? 3 : 1], kh0[RELAX ? 3 : 1];
+  // SM: shares of the moments: what the last row taken in sends north (and what
+  // it would send back from a wall above it), what the row of the moments has
+  // received from below and from its own row
+  R sent[4] = {}, back[4] = {}, got[4] = {}, own[4] = {};
+  double own_g0 = 0.0, own_h0 = 0.0;
+  // moments of the last three rows: concentrations and their west-east sums
+  // (hs = (west - c) + (east - c)) and differences (hd = east - west)
+  double cq[3][3] = {}, hs[3][3] = {}, hd[3][3] = {}, mphi[3] = {};
+  R md[3] = {}, mjx[3] = {}, mjy[3] = {};
+  // stencils of the force, summed row by row (see the C stage)
+  double ax[3] = {}, px[3] = {}, ay[3][2] = {};
+  double fx0 = 0.0, fx1 = 0.0, fy0 = 0.0, fy1 = 0.0;
+  double mpC = 0.0, msC = 0.0;  // potentials of the C row
+  // active lanes of the rows taken in last, and the membrane fields fetched
+  // for the next iteration: profile field of its U row, spread force of its C row
+  unsigned long long act1 = 0, act2 = 0, act3 = 0;
+  double Inx = 0.0;
+  long long fb0n = 0, fb1n = 0;
+
+  auto load_row = [&](int k) {
+    const int ry = fd_row_near(rbase + k, P.ny, P.wall_y);
+    nfl = tflag[(ry >> tsh) * P.ntx + xt];
+    if constexpr (SM)
+      nxt = src.node((unsigned)(ry * P.nx + x));
+    else
+      pull9(src, P, x, ry, npf, npg, nph, ng0, nh0);
   };
 
-  auto body = [&](auto slot_c, int k) {
-    constexpr int S = decltype(slot_c)::value;   // slot of row k
-    constexpr int SN = (S + 1) % NS;             // slot of row k+1
-    constexpr int SC = (S + NS - 2) % NS;        // slot of row k-2 (collided now)
-    constexpr int SP = (S + NS - 1) % NS;        // slot of row k-1 (chemical potential now)
-    const int r = rbase + dir * k;               // row whose moments are formed now
-    if constexpr (NS == 4) {
-      // unconditional (the last iteration reloads its own row), so every
-      // path has the same loads in flight
-      load_row(std::integral_constant<int, SN>{}, min(k + 1, K - 1));
-    } else {
-      load_row(std::integral_constant<int, S>{}, k);
-    }
-    const int qy = fd_row_near(r - dir, P.ny, P.wall_y);  // row of the chemical potential
-    const int cy = r - 2 * dir;                      // row of the collision
-    double Ipre = 0.0;
-    long long fb0 = 0, fb1 = 0;
-    bool cact;
-    if constexpr (NS == 4) {
-      Ipre = Ipre_c[S & 1];
-      fb0 = fb0_c[S & 1];
-      fb1 = fb1_c[S & 1];
-      cact = cact_c[S & 1];
-    } else {
-      if (k >= 2 && j >= 1 && j < BX - 1 && tfl[SP] == stamp) Ipre = Ifield[(long long)qy * P.nx + x];
-      cact = k >= 4 && interior && tfl[SC] == stamp;
-      if (cact) {
-        const long long* fp = fib + 2 * ((long long)cy * P.nx + x);
-        fb0 = fp[0];
-        fb1 = fp[1];
+  // PH: iteration of the prologue (2 H of them, nothing to store yet), or 2 H
+  // and more: steady, PH % 3 the ring slot
+  auto body = [&](auto ph_c, int k) {
+#pragma clang fp contract(off)
+    constexpr int PH = decltype(ph_c)::value;
+    constexpr int S = PH % 3, SB = (PH + 2) % 3, SA = (PH + 1) % 3;  // slots of rows m, m - 1 (U), m - 2 (C)
+    constexpr bool doM = PH >= 2 * LAG, doU = PH >= 2 + 2 * LAG, doC = PH >= 4 + 2 * LAG;
+    const int r = rbase + k;
+    if constexpr (RELAX) load_row(k);
+    // ---- the row taken in
+    R pf[9], pg[9], ph[9];
+    double g0, h0;
+    const unsigned long long act0 = __ballot(nfl == stamp);
+    Macro2<R> s = nxt;
+    if constexpr (!SM) {
+#pragma unroll
+      for (int i = 0; i < 9; i++) {
+        pf[i] = npf[i];
+        pg[i] = i ? npg[i] : R(0);
+        ph[i] = i ? nph[i] : R(0);
+      }
+      g0 = ng0;
+      h0 = nh0;
+      if constexpr (RELAX) {
+#pragma unroll
+        for (int i = 0; i < 9; i++) {
+          kf[S][i] = pf[i];
+          kg[S][i] = pg[i];
+          kh[S][i] = ph[i];
+        }
+        kg0[S] = g0;
+        kh0[S] = h0;
       }
     }
-    // ---- M: moments of row r -> ring slot k%3
+    // ---- membrane fields of the next iteration's U and C rows
+    const double Icur = Inx;
+    const long long fb0 = fb0n, fb1 = fb1n;
+    const unsigned long long actC = SM ? act3 : act2;  // the C row's, r - H
     {
-      double d, jx, jy, phi, psi;
-      moments9(pf[S], pg[S], ph[S], g0[S], h0[S], d, jx, jy, phi, psi);
-      const int sl = k % 3;
-      s_m[sl][0][j] = d;
-      s_m[sl][1][j] = phi;
-      s_m[sl][2][j] = psi;
-      s_j[sl][0][j] = jx;
-      s_j[sl][1][j] = jy;
+      // next iteration: U row r - LAG (flags act1 when SM, act0 else), C row the one below it
+      const unsigned long long au = SM ? act1 : act0, ac = SM ? act2 : act1;
+      Inx = 0.0;
+      fb0n = fb1n = 0;
+      if (au | ac) {
+        const int ur = r - LAG;
+        if (PH + 1 >= 2 + 2 * LAG && (au >> j & 1))
+          Inx = Ifield[(long long)fd_row_near(ur, P.ny, P.wall_y) * P.nx + x];
+        if (PH + 1 >= 4 + 2 * LAG && (ac >> j & 1) && interior && k + 1 < K) {
+          const long long* fp = fib + 2 * ((long long)(ur - 1) * P.nx + x);
+          fb0n = fp[0];
+          fb1n = fp[1];
+        }
+      }
     }
-    __syncthreads();
-    // ---- U: chemical potentials on the previous row -> ring slot k%3
-    if (k >= 2 && j >= 1 && j < BX - 1) {
-      const int a = (k + 1) % 3, b = (k + 2) % 3, c = k % 3;  // rows r-2dir, r-dir, r
-      // rows a and c swap between up- and down-marching segments: each sum
-      // pairs them in one addition (IEEE addition is commutative), so every
-      // node gets the same rounding under any launch shape
-      double lap[3], ctr[3];
+    if constexpr (!RELAX) load_row(min(k + 1, K - 1));
+
+    // ---- M: moments of row m
+    R d = 0, jx = 0, jy = 0;
+    double phi = 0.0, psi = 0.0;
+    if constexpr (SM) {
+      if (P.wall_y && (r < 0 || r >= P.ny)) {  // a wall's ghost rows are mirrored
+        s.wy = -s.wy;
+        s.vy = -s.vy;
+      }
+      macro_pops<R>(rho0, P.psh[0], P.psh[1], s, pf, pg, ph, g0, h0);
+      // Row m = r - 1 receives its own row's populations 0, 1, 2, what the row
+      // below sent north (3, 5, 7) and what this row sends south (4, 6, 8):
+      // its moments are the sums of three rows' shares, each four numbers
+      // (f, the x momentum of f, g, h) formed as the row is taken in
+      const bool crossing = P.wall_y && (r == 0 || r == P.ny);  // a wall between rows r - 1 and r
+      R so[4], no[4];
+      if (crossing) {  // half-way bounce-back on both sides of it
+#pragma unroll
+        for (int e = 0; e < 4; e++) so[e] = back[e];
+        no[0] = pf[4] + (pf[6] + pf[8]);
+        no[1] = pf[6] - pf[8];
+        no[2] = pg[4] + (pg[6] + pg[8]);
+        no[3] = ph[4] + (ph[6] + ph[8]);
+      } else {
+        const R f6 = east(pf[6]), f8 = west(pf[8]);
+        so[0] = pf[4] + (f6 + f8);
+        so[1] = f8 - f6;
+        so[2] = pg[4] + (east(pg[6]) + west(pg[8]));
+        so[3] = ph[4] + (east(ph[6]) + west(ph[8]));
+#pragma unroll
+        for (int e = 0; e < 4; e++) no[e] = sent[e];
+      }
+      if constexpr (doM) {
+        d = own[0] + (got[0] + so[0]);
+        jx = own[1] + (got[1] + so[1]);
+        jy = got[0] - so[0];
+        phi = own_g0 + (double)(own[2] + (got[2] + so[2]));
+        psi = own_h0 + (double)(own[3] + (got[3] + so[3]));
+      }
+      const R f5 = west(pf[5]), f7 = east(pf[7]), f1 = west(pf[1]), f2 = east(pf[2]);
+      own[0] = pf[0] + (f1 + f2);
+      own[1] = f1 - f2;
+      own[2] = west(pg[1]) + east(pg[2]);
+      own[3] = west(ph[1]) + east(ph[2]);
+      sent[0] = pf[3] + (f5 + f7);
+      sent[1] = f5 - f7;
+      sent[2] = pg[3] + (west(pg[5]) + east(pg[7]));
+      sent[3] = ph[3] + (west(ph[5]) + east(ph[7]));
+      back[0] = pf[3] + (pf[5] + pf[7]);
+      back[1] = pf[7] - pf[5];
+      back[2] = pg[3] + (pg[5] + pg[7]);
+      back[3] = ph[3] + (ph[5] + ph[7]);
+#pragma unroll
+      for (int e = 0; e < 4; e++) got[e] = no[e];
+      own_g0 = g0;
+      own_h0 = h0;
+    } else if constexpr (RELAX) {
+      double dd, jxd, jyd;
+      moments9(pf, pg, ph, g0, h0, dd, jxd, jyd, phi, psi);  // sums in R
+      d = (R)dd;
+      jx = (R)jxd;
+      jy = (R)jyd;
+    } else {
+      moments9m(pf, pg, ph, g0, h0, d, jx, jy, phi, psi);
+    }
+    if constexpr (doM) {
+      const double rho = P.rho0 + (double)d;
+      const double C[3] = {fma_(P.cm[0][0], rho, fma_(P.cm[0][1], phi, P.cm[0][2] * psi)),
+                           fma_(P.cm[1][0], rho, fma_(P.cm[1][1], phi, P.cm[1][2] * psi)), psi};
 #pragma unroll
       for (int f = 0; f < 3; f++) {
-        const double q = s_m[b][f][j];
-        const double n4 = ((s_m[b][f][j - 1] - q) + (s_m[b][f][j + 1] - q)) +
-                          ((s_m[a][f][j] - q) + (s_m[c][f][j] - q));
-        const double n8 = ((s_m[a][f][j - 1] - q) + (s_m[a][f][j + 1] - q)) +
-                          ((s_m[c][f][j - 1] - q) + (s_m[c][f][j + 1] - q));
-        // lap q = 6 sum_i w_i (q(x + c_i) - q(x)) with the D2Q9 weights
-        lap[f] = (2.0 / 3.0) * n4 + (1.0 / 6.0) * n8;
-        ctr[f] = q;
+        const double e = east(C[f]), w = west(C[f]);
+        cq[S][f] = C[f];
+        hs[S][f] = (w - C[f]) + (e - C[f]);
+        hd[S][f] = e - w;
       }
-      double mr, mp, ms;
-      chem_pot(P, ctr[0], ctr[1], ctr[2], lap[0], lap[1], lap[2], Ipre, mr, mp, ms);
-      const int sl = k % 3;
-      if constexpr (FORM == 1) {
-        // gradients of rho, phi, psi on this row (north and south resolved
-        // by name, so both marching directions round alike)
-        const int sn = dir > 0 ? c : a, ss = dir > 0 ? a : c;
-        double gx[3], gy[3];
+      mphi[S] = phi;
+      md[S] = d;
+      mjx[S] = jx;
+      mjy[S] = jy;
+    }
+    if constexpr (doU) {
+      // ---- U: row m - 1, from the rows below (a), its own (b), above (c)
+      double lap[3], b[3], t1[3];
 #pragma unroll
-        for (int f = 0; f < 3; f++) {
-          const double e = s_m[b][f][j + 1], wv = s_m[b][f][j - 1];
-          const double nn = s_m[sn][f][j], so = s_m[ss][f][j];
-          const double ne = s_m[sn][f][j + 1], nw = s_m[sn][f][j - 1];
-          const double se = s_m[ss][f][j + 1], sw = s_m[ss][f][j - 1];
-          gx[f] = (1.0 / 3.0) * (e - wv) + (1.0 / 12.0) * ((ne - nw) + (se - sw));
-          gy[f] = (1.0 / 3.0) * (nn - so) + (1.0 / 12.0) * ((ne - se) + (nw - sw));
-        }
+      for (int f = 0; f < 3; f++) {
+        const double q = cq[SB][f];
+        // lap q = 6 sum_i w_i (q(x + c_i) - q(x)) with the D2Q9 weights
+        lap[f] = fma_(1.0 / 6.0, fma_(4.0, hs[SB][f], hs[SA][f] + hs[S][f]), (cq[SA][f] - q) + (cq[S][f] - q));
+        t1[f] = q * (1.0 - q);
+        b[f] = km[f] * fma_(-P.a2, lap[f], t1[f] * fma_(-2.0, q, 1.0));
+      }
+      const double kp = P.kc * (cq[SB][2] - Icur);
+      const double mp = fma_(P.cm[0][1], b[0], P.cm[1][1] * b[1]);
+      const double ms = fma_(P.cm[0][2], b[0], P.cm[1][2] * b[1]) + (b[2] + kp);
+      double Fx = 0.0, Fy = 0.0;
+      if constexpr (FORM == 1) {
         // P' in the concentrations C_m (eq. VariableTransform, or its form
         // with component densities), where the energy of eq. LandauFE is a
-        // sum of independent terms: for each m
-        // the bulk part C f_m'(C) - f_m(C) = kappa_m/2 C^2 (1-C)(1-3C) and the
-        // gradient part alpha^2 kappa_m (dC dC - (|grad C|^2/2 + C lap C) I)
-        double Cm[3], Xm[3], Ym[3], Lm[3];
-        conc3(P, P.rho0 + ctr[0], ctr[1], ctr[2], Cm);
-        conc3(P, gx[0], gx[1], gx[2], Xm);
-        conc3(P, gy[0], gy[1], gy[2], Ym);
-        conc3(P, lap[0], lap[1], lap[2], Lm);
-        const double km[3] = {P.k1, P.k2, P.k3};
-        double pb = 0.0, dd = 0.0, cl = 0.0, xy = 0.0;
+        // sum of independent terms: for each m the bulk part
+        // C f_m'(C) - f_m(C) = kappa_m/2 C^2 (1-C)(1-3C) and the gradient
+        // part alpha^2 kappa_m (dC dC - (|grad C|^2/2 + C lap C) I)
+        double iso = 0.0, dd = 0.0, xy = 0.0;
 #pragma unroll
-        for (int m = 0; m < 3; m++) {
-          const double C = Cm[m];
-          pb += km[m] * (C * C * (1.0 - C) * (1.0 - 3.0 * C));
-          dd += km[m] * (Xm[m] * Xm[m] - Ym[m] * Ym[m]);
-          cl += km[m] * (C * Lm[m]);
-          xy += km[m] * (Xm[m] * Ym[m]);
+        for (int f = 0; f < 3; f++) {
+          const double gx = (1.0 / 12.0) * fma_(4.0, hd[SB][f], hd[SA][f] + hd[S][f]);
+          const double gy = fma_(0.5, cq[S][f] - cq[SA][f], (1.0 / 12.0) * (hs[S][f] - hs[SA][f]));
+          const double C = cq[SB][f];
+          iso = fma_(km[f] * C, fma_(0.5 * t1[f], fma_(-3.0, C, 1.0), -(P.a2 * lap[f])), iso);
+          const double kx = km[f] * gx;
+          xy = fma_(kx, gy, xy);
+          dd = fma_(kx, gx, fma_(-(km[f] * gy), gy, dd));
         }
-        const double iso = 0.5 * pb - P.a2 * cl;
-        s_u[sl][0][j] = iso + 0.5 * P.a2 * dd;
-        s_p[sl][0][j] = P.a2 * xy;
-        s_p[sl][1][j] = iso - 0.5 * P.a2 * dd;
-        s_p[sl][2][j] = P.kc * (ctr[2] - Ipre);
-      } else {
-        s_u[sl][0][j] = mr;
-      }
-      s_u[sl][1][j] = mp;
-      s_u[sl][2][j] = ms;
-    }
-    __syncthreads();
-    if constexpr (NS == 4) {
-      // the next iteration's membrane fields: its chemical-potential row is
-      // row r (flag in slot S), its collision row r - dir (flag in slot SP)
-      constexpr int T = SN & 1;
-      const int k1 = k + 1;
-      Ipre_c[T] = 0.0;
-      if (k1 >= 2 && k1 < K && j >= 1 && j < BX - 1 && tfl[S] == stamp)
-        Ipre_c[T] = Ifield[(long long)fd_row_near(r, P.ny, P.wall_y) * P.nx + x];
-      cact_c[T] = k1 >= 4 && k1 < K && interior && tfl[SP] == stamp;
-      fb0_c[T] = 0;
-      fb1_c[T] = 0;
-      if (cact_c[T]) {
-        const long long* fp = fib + 2 * ((long long)(r - dir) * P.nx + x);
-        fb0_c[T] = fp[0];
-        fb1_c[T] = fp[1];
-      }
-    }
-    // ---- C: collide row r - 2 dir with the registers of slot SC
-    if (k >= 4 && interior) {
-      const int a = (k + 1) % 3, b = (k + 2) % 3, c = k % 3;  // mu rows cy-dir, cy, cy+dir
-      const int sn = dir > 0 ? c : a, ss = dir > 0 ? a : c;   // north (cy+1) and south (cy-1)
-      // moments of row cy were stored two iterations ago (slot (k-2)%3 = a)
-      const double d = s_m[a][0][j], phi = s_m[a][1][j], psi = s_m[a][2][j];
-      const double jx = s_j[a][0][j], jy = s_j[a][1][j];
-      double Fx, Fy;
-      if constexpr (FORM == 1) {
-        // -div P' - psi grad kappa_c (psi - I); the divergence of a tensor
-        // column by the same stencil as a gradient, 3 sum_i w_i c_i P(x + c_i)
-        double gx[4], gy[4];
-        const double* fld[4][3] = {{s_u[ss][0], s_u[b][0], s_u[sn][0]},
-                                   {s_p[ss][0], s_p[b][0], s_p[sn][0]},
-                                   {s_p[ss][1], s_p[b][1], s_p[sn][1]},
-                                   {s_p[ss][2], s_p[b][2], s_p[sn][2]}};
-#pragma unroll
-        for (int f = 0; f < 4; f++) {
-          const double *rs = fld[f][0], *rc = fld[f][1], *rn = fld[f][2];
-          const double e = rc[j + 1], wv = rc[j - 1];
-          const double nn = rn[j], so = rs[j];
-          const double ne = rn[j + 1], nw = rn[j - 1];
-          const double se = rs[j + 1], sw = rs[j - 1];
-          gx[f] = (1.0 / 3.0) * (e - wv) + (1.0 / 12.0) * ((ne - nw) + (se - sw));
-          gy[f] = (1.0 / 3.0) * (nn - so) + (1.0 / 12.0) * ((ne - se) + (nw - sw));
+        const double ha = 0.5 * P.a2;
+        const double Pxx = fma_(ha, dd, iso), Pyy = fma_(-ha, dd, iso), Pxy = P.a2 * xy;
+        // ---- C: -div P' - psi grad kappa_c (psi - I) at row m - 2; 12 times
+        // the stencil of a gradient, 3 sum_i w_i c_i q(x + c_i), summed over
+        // the rows: east - west of the row below, 4 times that of the own
+        // row, that of the row above; west + 4 centre + east above less below
+        const double xe = east(Pxx), xw = west(Pxx), me = east(Pxy), mw = west(Pxy), ye = east(Pyy),
+                     yw = west(Pyy), ke = east(kp), kw = west(kp);
+        const double hxx = xe - xw, hxy = me - mw, sxy = fma_(4.0, Pxy, me + mw), syy = fma_(4.0, Pyy, ye + yw);
+        const double hk = ke - kw, sk = fma_(4.0, kp, ke + kw);
+        if constexpr (doC) {
+          const double ps = cq[SA][2];
+          const double tx = fx0 + (hxx + sxy), ty = fy0 + (hxy + syy);
+          const double kx = ax[0] + hk, ky = sk - ay[0][0];
+          Fx = (-1.0 / 12.0) * fma_(ps, kx, tx);
+          Fy = (-1.0 / 12.0) * fma_(ps, ky, ty);
         }
-        Fx = -(gx[0] + gy[1]) - psi * gx[3];
-        Fy = -(gx[1] + gy[2]) - psi * gy[3];
+        fx0 = fma_(4.0, hxx, fx1);
+        fy0 = fma_(4.0, hxy, fy1);
+        fx1 = hxx - sxy;
+        fy1 = hxy - syy;
+        ax[0] = fma_(4.0, hk, px[0]);
+        px[0] = hk;
+        ay[0][0] = ay[0][1];
+        ay[0][1] = sk;
       } else {
-        // grad mu = 3 sum_i w_i c_i mu(x + c_i)
+        // ---- C: -(rho grad mu_rho + phi grad mu_phi + psi grad mu_psi) at
+        // row m - 2 (eqs. ForceFE, GradPT), summed over the rows as above
+        const double mr = fma_(P.cm[0][0], b[0], P.cm[1][0] * b[1]);
+        const double mu[3] = {mr, mp, ms};
         double gx[3], gy[3];
 #pragma unroll
         for (int f = 0; f < 3; f++) {
-          const double e = s_u[b][f][j + 1], wv = s_u[b][f][j - 1];
-          const double nn = s_u[sn][f][j], so = s_u[ss][f][j];
-          const double ne = s_u[sn][f][j + 1], nw = s_u[sn][f][j - 1];
-          const double se = s_u[ss][f][j + 1], sw = s_u[ss][f][j - 1];
-          gx[f] = (1.0 / 3.0) * (e - wv) + (1.0 / 12.0) * ((ne - nw) + (se - sw));
-          gy[f] = (1.0 / 3.0) * (nn - so) + (1.0 / 12.0) * ((ne - se) + (nw - sw));
+          const double e = east(mu[f]), w = west(mu[f]);
+          const double h = e - w, sm = fma_(4.0, mu[f], e + w);
+          gx[f] = ax[f] + h;
+          gy[f] = sm - ay[f][0];
+          ax[f] = fma_(4.0, h, px[f]);
+          px[f] = h;
+          ay[f][0] = ay[f][1];
+          ay[f][1] = sm;
         }
-        const double rho = P.rho0 + d;
-        // thermodynamic force, eq. ForceFE with eq. GradPT (potential form)
-        Fx = -(rho * gx[0] + phi * gx[1] + psi * gx[2]);
-        Fy = -(rho * gy[0] + phi * gy[1] + psi * gy[2]);
-      }
-      Fx += P.fext[0];  // f_ext of eq. ForcingTermLBE
-      Fy += P.fext[1];
-      const long long node = (long long)cy * P.nx + x;
-      if (cact) {
-        Fx += from_fix(fb0);
-        Fy += from_fix(fb1);
-        fib[2 * node] = 0;
-        fib[2 * node + 1] = 0;
-        force[2 * node] = Fx;
-        force[2 * node + 1] = Fy;
-      }
-      collide9(P, pf[SC], pg[SC], ph[SC], g0[SC], h0[SC], d, jx, jy, phi, psi, s_u[b][1][j],
-               s_u[b][2][j], Fx, Fy);
-      if constexpr (St::kQuantized) {
-        // moving populations are stored rounded; the rest population of the
-        // same set takes the rounding so the node's mass per set is exact
-        R ef = 0, eg = 0, eh = 0;
-#pragma unroll
-        for (int i = 1; i < 9; i++) {
-          const R qf = dst.quantize(pf[SC][i]), qg = dst.quantize(pg[SC][i]), qh = dst.quantize(ph[SC][i]);
-          ef += pf[SC][i] - qf;
-          eg += pg[SC][i] - qg;
-          eh += ph[SC][i] - qh;
-          pf[SC][i] = qf;
-          pg[SC][i] = qg;
-          ph[SC][i] = qh;
+        if constexpr (doC) {
+          const double rho = P.rho0 + (double)md[SA], ph_ = mphi[SA], ps = cq[SA][2];
+          Fx = (-1.0 / 12.0) * fma_(rho, gx[0], fma_(ph_, gx[1], ps * gx[2]));
+          Fy = (-1.0 / 12.0) * fma_(rho, gy[0], fma_(ph_, gy[1], ps * gy[2]));
         }
-        pf[SC][0] += ef;
-        g0[SC] += (double)eg;
-        h0[SC] += (double)eh;
       }
-      dst.template store<R>(0, 0, node, pf[SC][0]);
-      dst.store_rest(1, node, g0[SC]);
-      dst.store_rest(2, node, h0[SC]);
+      if constexpr (doC) {
+        Fx += P.fext[0];  // f_ext of eq. ForcingTermLBE
+        Fy += P.fext[1];
+        const int cy = r - H;  // the C row
+        const unsigned node = interior ? (unsigned)(cy * P.nx + x) : 0xffffffffu;
+        if (actC != 0) {
+          Fx += from_fix(fb0);
+          Fy += from_fix(fb1);
+          if (interior && (actC >> j & 1)) {
+            fib[2 * (long long)node] = 0;
+            fib[2 * (long long)node + 1] = 0;
+            force[2 * (long long)node] = Fx;
+            force[2 * (long long)node + 1] = Fy;
+          }
+        }
+        Macro2<R> o;
+        R qf[9], qg[9], qh[9];
+        double q0, r0;
+        if constexpr (RELAX) {
 #pragma unroll
-      for (int i = 1; i < 9; i++) {
-        dst.template store<R>(0, i, node, pf[SC][i]);
-        dst.template store<R>(1, i, node, pg[SC][i]);
-        dst.template store<R>(2, i, node, ph[SC][i]);
+          for (int i = 0; i < 9; i++) {
+            qf[i] = kf[SA][i];
+            qg[i] = kg[SA][i];
+            qh[i] = kh[SA][i];
+          }
+          q0 = kg0[SA];
+          r0 = kh0[SA];
+          collide9(P, qf, qg, qh, q0, r0, (double)md[SA], (double)mjx[SA], (double)mjy[SA], mphi[SA], cq[SA][2], mpC,
+                   msC, Fx, Fy);
+          if constexpr (St::kQuantized) {
+            // moving populations are stored rounded; the rest population of the
+            // same set takes the rounding so the node's mass per set is exact
+            R ef = 0, eg = 0, eh = 0;
+#pragma unroll
+            for (int i = 1; i < 9; i++) {
+              const R vf = dst.quantize(qf[i]), vg = dst.quantize(qg[i]), vh = dst.quantize(qh[i]);
+              ef += qf[i] - vf;
+              eg += qg[i] - vg;
+              eh += qh[i] - vh;
+              qf[i] = vf;
+              qg[i] = vg;
+              qh[i] = vh;
+            }
+            qf[0] += ef;
+            q0 += (double)eg;
+            r0 += (double)eh;
+          }
+        } else {
+          const double ir = recip(P.rho0 + (double)md[SA]);
+          const double jxd = (double)mjx[SA], jyd = (double)mjy[SA];
+          o.dr = md[SA];
+          o.wx = (R)((jxd + Fx) * ir);  // u + delta u, eq. VelCorrection
+          o.wy = (R)((jyd + Fy) * ir);
+          o.vx = (R)(fma_(0.5, Fx, jxd) * ir);  // eq. ActualFluidVel
+          o.vy = (R)(fma_(0.5, Fy, jyd) * ir);
+          o.gm = (R)(3.0 * P.gphi * mpC);
+          o.hm = (R)(3.0 * P.gpsi * msC);
+          o.phi = mphi[SA];
+          o.psi = cq[SA][2];
+          if constexpr (!DM) macro_pops<R>(rho0, P.psh[0], P.psh[1], o, qf, qg, qh, q0, r0);
+        }
+        if constexpr (DM) {
+          dst.set_node(node, o);
+        } else {
+          if (St::kDropsOutOfRange || interior) {
+            const long long nd = St::kDropsOutOfRange ? (long long)(int)node : (long long)node;
+            dst.template store<R>(0, 0, nd, qf[0]);
+            dst.store_rest(1, nd, q0);
+            dst.store_rest(2, nd, r0);
+#pragma unroll
+            for (int i = 1; i < 9; i++) {
+              dst.template store<R>(0, i, nd, qf[i]);
+              dst.template store<R>(1, i, nd, qg[i]);
+              dst.template store<R>(2, i, nd, qh[i]);
+            }
+          }
+        }
       }
+      mpC = mp;
+      msC = ms;
     }
+    act3 = act2;
+    act2 = act1;
+    act1 = act0;
   };
 
-  if constexpr (NS == 4) load_row(std::integral_constant<int, 0>{}, 0);
-  for (int kb = 0; kb < K; kb += NS) {
-    body(std::integral_constant<int, 0>{}, kb);
-    if (kb + 1 < K) body(std::integral_constant<int, 1>{}, kb + 1);
-    if (kb + 2 < K) body(std::integral_constant<int, 2>{}, kb + 2);
-    if constexpr (NS == 4)
-      if (kb + 3 < K) body(std::integral_constant<int, 3>{}, kb + 3);
+  if constexpr (!RELAX) load_row(0);
+  constexpr int PRO = 2 * H;  // iterations before the first collision
+  body(std::integral_constant<int, 0>{}, 0);
+  body(std::integral_constant<int, 1>{}, 1);
+  body(std::integral_constant<int, 2>{}, 2);
+  body(std::integral_constant<int, 3>{}, 3);
+  if constexpr (PRO == 6) {
+    body(std::integral_constant<int, 4>{}, 4);
+    body(std::integral_constant<int, 5>{}, 5);
+  }
+  for (int k = PRO; k < K; k += 3) {
+    body(std::integral_constant<int, PRO>{}, k);
+    if (k + 1 < K) body(std::integral_constant<int, PRO + 1>{}, k + 1);
+    if (k + 2 < K) body(std::integral_constant<int, PRO + 2>{}, k + 2);
   }
 }
 
-// does the (strip, rows [y0, y1)) region of a workgroup read any membrane
-// field, i.e. does an active tile cover a (row, lane) whose profile field or
-// spread force it reads?  (rows y0-1 .. y1 of lanes 1 .. BX-2; every thread
-// of the workgroup must call it)
-template <int BX>
+// does the (strip, rows [y0, y1)) region of a wave read any membrane field,
+// i.e. does an active tile cover a (row, lane) whose profile field or spread
+// force it reads?  (rows y0-1 .. y1 of the interior lanes and one more each side)
+template <int H>
 __device__ __forceinline__ bool region_active(const LBParams& P, const int* __restrict__ tflag, int stamp,
                                               int strip, int y0, int y1) {
-  const int j = threadIdx.x;
-  const int x = wrap(strip * (BX - 4) - 2 + j, P.nx);
+  const int j = threadIdx.x & 63;
+  const int x = wrap(strip * (64 - 2 * H) - H + j, P.nx);
   bool a = false;
-  if (j >= 1 && j < BX - 1)
+  if (j >= H - 1 && j < 65 - H)
     for (int r = y0 - 1; r <= y1; r++) a |= tflag[(fd_row(r, P.ny, P.wall_y) / P.tile) * P.ntx + x / P.tile] == stamp;
-  return __syncthreads_or(a) != 0;
+  return __ballot(a) != 0;
 }
 
-// The fused step over the whole lattice: one (strip, segment) per workgroup.
-template <class St, typename R, int BX, int NS, int WPE, int FORM = 0>
-__global__ __launch_bounds__(BX, WPE) void k_lb2d(St src, St dst, LBParams P,
-                                                  const int* __restrict__ tflag,
-                                                  const int* __restrict__ tstate,
-                                                  const double* __restrict__ Ifield,
-                                                  long long* __restrict__ fib,
-                                                  double* __restrict__ force) {
-  int strip, sgm;
-  strip_segment((int)blockIdx.x, P.nstrip, P.nseg, P.nxcd, strip, sgm);
-  const int y0 = sgm * P.seg, y1 = min(y0 + P.seg, P.ny);
-  // even segments march up, odd ones down: neighbouring segments then read
-  // the rows they share at the same time (both at their start or both at
-  // their end)
-  lb2d_run<St, R, BX, NS, FORM>(src, dst, P, strip, y0, y1, (sgm & 1) ? -1 : 1, tflag, tstate, Ifield, fib,
-                                force);
-}
-
-// The same step in two passes: mode 1 takes the (strip, segment) regions
-// that read no membrane field and may run beside the membrane kernels;
-// mode 2 takes the others after them, each segment cut into npiece pieces of
-// seg2 rows so that the few regions near the membranes still fill the GPU.
-template <class St, typename R, int BX, int NS, int WPE, int FORM = 0>
-__global__ __launch_bounds__(BX, WPE) void k_lb2d_part(St src, St dst, LBParams P,
-                                                       const int* __restrict__ tflag,
-                                                       const int* __restrict__ tstate,
-                                                       const double* __restrict__ Ifield,
-                                                       long long* __restrict__ fib,
-                                                       double* __restrict__ force) {
+// The step over the whole lattice, one (strip, segment) per wave.
+//
+// What bounds it, at 2048^2 with 16 capsules in FP32, divergence form: 232 B
+// per node from populations to populations took 246 us in a march of four
+// waves through LDS rings (two barriers a row, two waves per SIMD), against
+// 201 us for copying those bytes.  From Macro2 to Macro2 it moves 88 B per node
+// (76 us at the rate of a copy) and takes 114 us; the vector units, some 450
+// instructions a row of which 200 are FP64, are then busy for 60 to 70 us of
+// it.  227 registers leave two waves per SIMD.  A relaxing step keeps three
+// rows of populations as well (249 registers): 46 -> 42 us at 1000 x 777 in the
+// potential form, 243 -> 227 us at 2048^2 in FP16.
+//
+// P.mode: 0
+// every region; the same step in two passes: 1 the regions that read no
+// membrane field, which may run beside the membrane kernels, 2 the others
+// after them, each segment cut into npiece pieces of seg2 rows so that the few
+// regions near the membranes still fill the GPU.
+template <class St, typename R, int FORM, class Src, class Dst, bool RELAX>
+__global__ __launch_bounds__(64, (step2d_waves<R, RELAX>())) void k_lb2d(Src src, Dst dst, LBParams P,
+                                                                      const int* __restrict__ tflag,
+                                                                      const int* __restrict__ tstate,
+                                                                      const double* __restrict__ Ifield,
+                                                                      long long* __restrict__ fib,
+                                                                      double* __restrict__ force) {
   int strip, sgm, piece = 0;
   if (P.mode == 2) {
     piece = (int)blockIdx.x % P.npiece;
@@ -558,15 +901,15 @@ __global__ __launch_bounds__(BX, WPE) void k_lb2d_part(St src, St dst, LBParams 
     strip_segment((int)blockIdx.x, P.nstrip, P.nseg, P.nxcd, strip, sgm);
   }
   int y0 = sgm * P.seg, y1 = min(y0 + P.seg, P.ny);
-  if (region_active<BX>(P, tflag, tstate[1], strip, y0, y1) != (P.mode == 2)) return;
-  int dir = (sgm & 1) ? -1 : 1;
-  if (P.mode == 2) {
-    y0 += piece * P.seg2;
-    if (y0 >= y1) return;
-    y1 = min(y0 + P.seg2, y1);
-    dir = (piece & 1) ? -1 : 1;
+  if (P.mode != 0) {
+    if (region_active<strip_halo<Src>()>(P, tflag, tstate[1], strip, y0, y1) != (P.mode == 2)) return;
+    if (P.mode == 2) {
+      y0 += piece * P.seg2;
+      if (y0 >= y1) return;
+      y1 = min(y0 + P.seg2, y1);
+    }
   }
-  lb2d_run<St, R, BX, NS, FORM>(src, dst, P, strip, y0, y1, dir, tflag, tstate, Ifield, fib, force);
+  step2d_run<St, R, FORM, Src, Dst, RELAX>(src, dst, P, strip, y0, y1, tflag, tstate, Ifield, fib, force);
 }
 
 }  // namespace lb

@@ -244,7 +244,8 @@ struct lbib_sim {
   }
   virtual void setup() = 0;
   virtual int init(const double* stage_dev) = 0;
-  virtual int step() = 0;
+  // n steps; the count of completed steps advances with them
+  virtual int advance(int n) = 0;
   virtual int moments(double* out_dev) = 0;
   virtual int energy_nodes(double* part, long long* nblk) = 0;
   virtual int coupling(int want_force) = 0;
@@ -420,6 +421,18 @@ void fill_params(LBParams& P, const lbib_params& p, const Layout& L, long long N
   P.npiece = 1;
 }
 
+// workgroups of a kernel resident on the GPU at once
+int resident_blocks(const void* k, int threads) {
+  int per_cu = 0, ncu = 0, dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, threads, 0) != hipSuccess || per_cu <= 0 || ncu <= 0)
+    return 1024;
+  return per_cu * ncu;
+}
+
+constexpr int MIN_SEG2 = 4;  // fewest rows of a D2Q9 segment chosen automatically
+
 template <class St, typename R>
 struct Engine2D final : lbib_sim {
   LBParams P{};
@@ -461,16 +474,16 @@ struct Engine2D final : lbib_sim {
                        0, 2, map_reach(r_cut), stamp);
   }
   // profile field and coupling forces on the active tiles
-  void profile_pass(int want_force) {
+  template <class Src>
+  void profile_pass(int want_force, const Src& src) {
     const int grid = (int)std::min<long long>(std::max<long long>(L.ntiles, 1), 2048);
-    hipLaunchKernelGGL((k_coupling2d<St, R, COUP_THREADS>), dim3(grid), dim3(COUP_THREADS), 0, stream,
-                       memdev(), tilemap(), coup_args(want_force), at<double>(L.Ifield), store(cur),
-                       tile_count());
+    hipLaunchKernelGGL((k_coupling2d<Src, R, COUP_THREADS>), dim3(grid), dim3(COUP_THREADS), 0, stream,
+                       memdev(), tilemap(), coup_args(want_force), at<double>(L.Ifield), src, tile_count());
   }
   int coupling(int want_force) override {
     if (K == 0) return LBIB_OK;
     tiles_pass();
-    profile_pass(want_force);
+    profile_pass(want_force, store(cur));
     return hipGetLastError() == hipSuccess ? LBIB_OK : LBIB_EHIP;
   }
 
@@ -498,95 +511,87 @@ struct Engine2D final : lbib_sim {
   // bandwidth with each other and with the membrane kernels
   bool split_step() const { return K > 0 && overlap > 0; }
 
-  // kernel variant for the current (bx, ring, force form)
-  template <int WPE3, int FORM>
-  const void* lb_kernel_f() const {
-    if (ring == 4) {
-      if (bx == 128) return (const void*)&k_lb2d<St, R, 128, 4, 2, FORM>;
-      if (bx == 192) return (const void*)&k_lb2d<St, R, 192, 4, 2, FORM>;
-      if (bx == 256) return (const void*)&k_lb2d<St, R, 256, 4, 2, FORM>;
-      return (const void*)&k_lb2d<St, R, 64, 4, 2, FORM>;
-    }
-    if (bx == 128) return (const void*)&k_lb2d<St, R, 128, 3, WPE3, FORM>;
-    if (bx == 192) return (const void*)&k_lb2d<St, R, 192, 3, WPE3, FORM>;
-    if (bx == 256) return (const void*)&k_lb2d<St, R, 256, 3, WPE3, FORM>;
-    return (const void*)&k_lb2d<St, R, 64, 3, WPE3, FORM>;
+  // with tau = 1 throughout a collision leaves equilibria, and the steps inside
+  // a call can pass on Macro2 instead of populations; the 16-bit formats keep
+  // what a collision leaves of the populations' rounding
+  bool relaxes() const {
+    return St::kQuantized || p.tau != 1.0 || p.tau_phi != 1.0 || p.tau_psi != 1.0;
   }
-  // the divergence form keeps three more fields in LDS, which leaves room
-  // for two waves per SIMD: its register budget is sized for that
-  const void* lb_kernel() const { return force_form ? lb_kernel_f<2, 1>() : lb_kernel_f<3, 0>(); }
+  // ... where its planes can be addressed (below 4 GiB per type), fit the
+  // population buffers (they do but for a handful of nodes), and a wall's
+  // three ghost rows mirror rows of the lattice
+  bool macro_steps() const {
+    const long long rb = Mac::kR * N * (long long)sizeof(R);
+    return !relaxes() && rb < 0xfffffff0LL && 16 * N < 0xfffffff0LL && !(p.wall_y && p.ny < 3) &&
+           align_up((size_t)rb) + (size_t)(16 * N) <= L.pop_bytes + 2 * kAlign;
+  }
+  using Mac = MacroStore2<R>;
+  Mac macro(int which) const {
+    char* base = ws + L.pops[which];
+    return Mac{reinterpret_cast<R*>(base),
+               reinterpret_cast<double*>(base + align_up((size_t)(Mac::kR * N) * sizeof(R))), (unsigned)N, P.rho0,
+               P.psh[0], P.psh[1]};
+  }
 
-  // rows per workgroup: with seg = 0 (automatic), the whole lattice is cut
-  // into exactly as many (strip, segment) workgroups as can be resident at
-  // once, so no partial last round of workgroups stretches the launch
-  int pick_seg() const {
+  // waves of a lattice kernel resident at once (queried once per variant)
+  int lb_slots[2][2][2][2] = {};
+  template <int FORM, class Src, class Dst, bool RELAX>
+  int slots() {
+    int& v = lb_slots[FORM][Src::kMacro][Dst::kMacro][RELAX];
+    if (!v) v = resident_blocks((const void*)&k_lb2d<St, R, FORM, Src, Dst, RELAX>, 64);
+    return v;
+  }
+
+  // rows per wave: with seg = 0 (automatic), the whole lattice is cut into
+  // exactly as many (strip, segment) waves as can be resident at once, so no
+  // partial last round of waves stretches the launch
+  int pick_seg(int nstrip, int slots) const {
     if (seg > 0) return seg;
-    const int W = bx - 4;
-    const long long nstrip = (p.nx + W - 1) / W;
-    int per_cu = 0, ncu = 0, dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, lb_kernel(), bx, 0) != hipSuccess ||
-        per_cu <= 0 || ncu <= 0)
-      return std::max(4, std::min(p.ny, 16));
-    const long long slots = (long long)per_cu * ncu;
-    long long rows = std::max(4LL, std::min<long long>(p.ny, (p.ny * nstrip + slots - 1) / slots));
-    // rounding the segment count up can still leave a few workgroups over
+    long long rows = std::max<long long>(MIN_SEG2, std::min<long long>(p.ny, ((long long)p.ny * nstrip + slots - 1) / slots));
+    // rounding the segment count up can still leave a few waves over
     while (rows < p.ny && nstrip * ((p.ny + rows - 1) / rows) > slots) rows++;
-    return (int)rows;
+    return (int)std::min<long long>(rows, p.ny);
   }
 
   // the fused kernel on stream s over the whole lattice (mode 0), the
   // regions that read no membrane field (1) or the others in pieces (2)
-  void launch_lb(St src, St dst, hipStream_t s, int mode) {
-    P.seg = pick_seg();
-    const int W = bx - 4;
+  template <int FORM, class Src, class Dst, bool RELAX>
+  void launch_form(const Src& src, const Dst& dst, hipStream_t s, int mode) {
+    const int W = 64 - 2 * strip_halo<Src>();
     P.nstrip = (p.nx + W - 1) / W;
+    P.seg = pick_seg(P.nstrip, seg > 0 ? 1 : slots<FORM, Src, Dst, RELAX>());
     P.nseg = (p.ny + P.seg - 1) / P.seg;
     // automatic: eight L2 domains (the XCDs), so a segment's vertical
-    // neighbours, which read the same halo rows at the same time, sit in
-    // the same L2 (fetched bytes -15 % on the 2048^2 workload)
+    // neighbours, which read the same halo rows, sit in the same L2
     P.nxcd = nxcd > 0 ? nxcd : 8;
     P.mode = mode;
     P.npiece = mode == 2 ? (P.seg + 5) / 6 : 1;  // pieces of about five rows
     P.seg2 = (P.seg + P.npiece - 1) / P.npiece;
-    dim3 grid(P.nstrip * P.nseg * P.npiece);
-    const int* tf = at<int>(L.tflag);
-    const int* ts = at<int>(L.tstate);
-    const double* If = at<double>(L.Ifield);
-    long long* fib = at<long long>(L.fib);
-    double* frc = at<double>(L.force);
-    // (lanes, ring depth, waves per SIMD) variants of the fused kernel
-#define LB_LAUNCH(BXV, NSV, WPEV)                                                                  \
-  do {                                                                                             \
-    if (mode == 0 && force_form == 1)                                                              \
-      hipLaunchKernelGGL((k_lb2d<St, R, BXV, NSV, 2, 1>), grid, dim3(BXV), 0, s, src, dst, P, tf, ts, If, \
-                         fib, frc);                                                                \
-    else if (mode == 0)                                                                            \
-      hipLaunchKernelGGL((k_lb2d<St, R, BXV, NSV, WPEV>), grid, dim3(BXV), 0, s, src, dst, P, tf, ts, If, \
-                         fib, frc);                                                                \
-    else if (force_form == 1)                                                                      \
-      hipLaunchKernelGGL((k_lb2d_part<St, R, BXV, NSV, 2, 1>), grid, dim3(BXV), 0, s, src, dst, P, tf, ts, \
-                         If, fib, frc);                                                            \
-    else                                                                                           \
-      hipLaunchKernelGGL((k_lb2d_part<St, R, BXV, NSV, WPEV>), grid, dim3(BXV), 0, s, src, dst, P, tf, ts, \
-                         If, fib, frc);                                                            \
-  } while (0)
-    if (ring == 4) {
-      if (bx == 128) LB_LAUNCH(128, 4, 2);
-      else if (bx == 192) LB_LAUNCH(192, 4, 2);
-      else if (bx == 256) LB_LAUNCH(256, 4, 2);
-      else LB_LAUNCH(64, 4, 2);
-    } else {
-      if (bx == 128) LB_LAUNCH(128, 3, 3);
-      else if (bx == 192) LB_LAUNCH(192, 3, 3);
-      else if (bx == 256) LB_LAUNCH(256, 3, 3);
-      else LB_LAUNCH(64, 3, 3);
+    hipLaunchKernelGGL((k_lb2d<St, R, FORM, Src, Dst, RELAX>), dim3(P.nstrip * P.nseg * P.npiece), dim3(64), 0, s,
+                       src, dst, P, (const int*)at<int>(L.tflag), (const int*)at<int>(L.tstate),
+                       (const double*)at<double>(L.Ifield), at<long long>(L.fib), at<double>(L.force));
+  }
+  template <class Src, class Dst>
+  void launch_lb(const Src& src, const Dst& dst, hipStream_t s, int mode) {
+    if constexpr (!Src::kMacro && !Dst::kMacro)
+      if (relaxes()) {
+        if (force_form)
+          launch_form<1, Src, Dst, true>(src, dst, s, mode);
+        else
+          launch_form<0, Src, Dst, true>(src, dst, s, mode);
+        return;
+      }
+    if constexpr (!St::kQuantized) {
+      if (force_form)
+        launch_form<1, Src, Dst, false>(src, dst, s, mode);
+      else
+        launch_form<0, Src, Dst, false>(src, dst, s, mode);
     }
-#undef LB_LAUNCH
   }
 
-  int step() override {
+  // one step from src (the state at t, in buffer cur) to dst (buffer 1 - cur)
+  template <class Src, class Dst>
+  int step(const Src& src, const Dst& dst) {
     MemDev md = memdev();
     const int mb16 = (16 * M + 255) / 256;  // sixteen lanes per marker
     const bool split = split_step();
@@ -600,11 +605,11 @@ struct Engine2D final : lbib_sim {
         if (hipEventRecord(ev_fork, stream) != hipSuccess || hipStreamWaitEvent(side, ev_fork, 0) != hipSuccess)
           return LBIB_EHIP;
         hipEvent_t ta = tbeg(0, side);
-        launch_lb(store(cur), store(1 - cur), side, 1);
+        launch_lb(src, dst, side, 1);
         tend(0, ta, side);
         if (hipEventRecord(ev_join, side) != hipSuccess) return LBIB_EHIP;
       }
-      profile_pass(1);
+      profile_pass(1, src);
       tend(1, t0);
       t0 = tbeg(2);
       hipLaunchKernelGGL(k_forcespread2d, dim3(mb16), dim3(256), 0, stream, md, at<long long>(L.fib), p.nx,
@@ -612,16 +617,17 @@ struct Engine2D final : lbib_sim {
       tend(2, t0);
     }
     hipEvent_t t1 = tbeg(0);
-    launch_lb(store(cur), store(1 - cur), stream, split ? 2 : 0);
+    launch_lb(src, dst, stream, split ? 2 : 0);
     tend(0, t1);
     if (split && hipStreamWaitEvent(stream, ev_join, 0) != hipSuccess) return LBIB_EHIP;
     if (K > 0) {
       hipEvent_t t2 = tbeg(3);
-      hipLaunchKernelGGL((k_interp2d<St, R>), dim3(mb16), dim3(256), 0, stream, md, store(1 - cur), P,
+      hipLaunchKernelGGL((k_interp2d<Dst, R>), dim3(mb16), dim3(256), 0, stream, md, dst, P,
                          (const double*)at<double>(L.force));
       tend(3, t2);
     }
     cur = 1 - cur;
+    steps++;
     if (timing) {
       timed_steps++;
       if (ev_used > 4096) {
@@ -630,6 +636,23 @@ struct Engine2D final : lbib_sim {
       }
     }
     return hipGetLastError() == hipSuccess ? LBIB_OK : LBIB_EHIP;
+  }
+
+  // the first step of a call reads populations, the last one writes them;
+  // those between pass on Macro2 where they can (the population buffers hold it)
+  int advance(int n) override {
+    for (int k = 0; k < n; k++) {
+      int rc;
+      if constexpr (St::kQuantized) {
+        rc = step(store(cur), store(1 - cur));
+      } else {
+        const bool mac = n > 1 && macro_steps(), in = mac && k > 0, out = mac && k + 1 < n;
+        rc = in ? (out ? step(macro(cur), macro(1 - cur)) : step(macro(cur), store(1 - cur)))
+                : (out ? step(store(cur), macro(1 - cur)) : step(store(cur), store(1 - cur)));
+      }
+      if (rc) return rc;
+    }
+    return LBIB_OK;
   }
 
   int init(const double* st) override {
@@ -787,7 +810,16 @@ struct Engine3D final : lbib_sim {
 #undef LB3_LAUNCH
   }
 
-  int step() override {
+  int advance(int n) override {
+    for (int k = 0; k < n; k++) {
+      const int rc = step();
+      if (rc) return rc;
+      steps++;
+    }
+    return LBIB_OK;
+  }
+
+  int step() {
     MemDev md = memdev();
     MeshDev mh = meshdev();
     const int mb = (M + 255) / 256;
@@ -881,24 +913,32 @@ struct BatchEngine2D final : lbib_sim {
   using Mem = Engine2D<St, R>;
   std::vector<Mem*> mem;
   static constexpr int NCLS = 3;  // size classes by lattice width: <= 128, <= 256, larger
-  int cls_bx[NCLS] = {64, 128, 256}, cls_seg[NCLS] = {0, 0, 0}, cls_ring[NCLS] = {3, 3, 3};
+  int cls_seg[NCLS] = {0, 0, 0};
+  // accepted and reported; a strip is one wave wide whatever they are
+  int cls_bx[NCLS] = {64, 128, 256}, cls_ring[NCLS] = {3, 3, 3};
   bool use_graph = true, dirty = true, graph_ok = false;
-  hipGraphExec_t gexec[2] = {nullptr, nullptr};
+  // one graph per buffer parity and form of the state read and written,
+  // captured when a step first needs it
+  hipGraphExec_t gexec[2][2][2] = {};
   size_t off_tab = 0, off_mems = 0, off_mpre = 0, off_cm = 0, off_bpre = 0;
-  int nmems = 0, Mtot = 0, cgrid = 1;
-  int ncm[NCLS] = {0, 0, 0}, lgrid[NCLS] = {0, 0, 0}, lseg[NCLS] = {0, 0, 0};
+  int nmems = 0, Mtot = 0, cgrid = 1, lseg[NCLS] = {0, 0, 0};
+  // lattice launches: members that do not relax, and those that do
+  static constexpr int NLIST = 2;
+  int ncm[NLIST] = {0, 0}, lgrid[NLIST][2] = {};
+  bool macro = false;  // every member can pass on Macro2 between steps
 
   ~BatchEngine2D() override {
     drop_graphs();
     for (auto m : mem) delete m;
   }
   void drop_graphs() {
-    for (auto& e : gexec)
-      if (e) {
-        (void)hipGraphExecDestroy(e);
-        e = nullptr;
-      }
-    graph_ok = false;
+    for (auto& a : gexec)
+      for (auto& b : a)
+        for (auto& e : b)
+          if (e) {
+            (void)hipGraphExecDestroy(e);
+            e = nullptr;
+          }
   }
   bool is_batch() const override { return true; }
   void mark_dirty() override { dirty = true; }
@@ -917,70 +957,46 @@ struct BatchEngine2D final : lbib_sim {
   int mem_energy(double*, long long*) override { return LBIB_ESTATE; }
 
   static int size_class(int nx) { return nx <= 128 ? 0 : (nx <= 256 ? 1 : 2); }
+  using BM = BMember<St, R>;
   static size_t table_bytes(int n, int kmax) {
-    return align_up((size_t)n * sizeof(BMember<St>)) + align_up((size_t)std::max(kmax, 1) * sizeof(int2)) +
-           align_up((size_t)(n + 1) * 4) + align_up((size_t)NCLS * n * 4) + align_up((size_t)NCLS * (n + 1) * 4);
-  }
-  template <int WPE3, int FORM>
-  const void* lb_kernel_f(int c) const {
-    const int bx = cls_bx[c];
-    if (cls_ring[c] == 4) {
-      if (bx == 128) return (const void*)&kb_lb2d<St, R, 128, 4, 2, FORM>;
-      if (bx == 192) return (const void*)&kb_lb2d<St, R, 192, 4, 2, FORM>;
-      if (bx == 256) return (const void*)&kb_lb2d<St, R, 256, 4, 2, FORM>;
-      return (const void*)&kb_lb2d<St, R, 64, 4, 2, FORM>;
-    }
-    if (bx == 128) return (const void*)&kb_lb2d<St, R, 128, 3, WPE3, FORM>;
-    if (bx == 192) return (const void*)&kb_lb2d<St, R, 192, 3, WPE3, FORM>;
-    if (bx == 256) return (const void*)&kb_lb2d<St, R, 256, 3, WPE3, FORM>;
-    return (const void*)&kb_lb2d<St, R, 64, 3, WPE3, FORM>;
-  }
-  // the divergence form's extra LDS ring leaves room for two waves per SIMD
-  const void* lb_kernel(int c) const { return force_form ? lb_kernel_f<2, 1>(c) : lb_kernel_f<3, 0>(c); }
-  int resident(const void* k, int threads) const {
-    int per_cu = 0, ncu = 0, dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, threads, 0) != hipSuccess || per_cu <= 0 ||
-        ncu <= 0)
-      return 1024;
-    return per_cu * ncu;
+    return align_up((size_t)n * sizeof(BM)) + align_up((size_t)std::max(kmax, 1) * sizeof(int2)) +
+           align_up((size_t)(n + 1) * 4) + align_up((size_t)NLIST * n * 4) +
+           align_up((size_t)NLIST * 2 * (n + 1) * 4);
   }
 
-  // device tables and launch plan; graph capture
+  // device tables and launch plan
   int prepare() {
     const int n = (int)mem.size();
     if (n == 0) return LBIB_EINVAL;
     for (auto m : mem)
       if (!m->ready || m->cur != mem[0]->cur) return LBIB_ESTATE;
-    std::vector<BMember<St>> T(n);
+    std::vector<BM> T(n);
     std::vector<int2> mems;
-    std::vector<int> mpre(n + 1, 0), cm(NCLS * n, 0), bpre(NCLS * (n + 1), 0);
-    std::vector<int> cls(n);
-    long long rows[NCLS] = {0, 0, 0};
-    for (int i = 0; i < n; i++) {
-      cls[i] = size_class(mem[i]->p.nx);
-      const int W = cls_bx[cls[i]] - 4;
-      rows[cls[i]] += (long long)((mem[i]->p.nx + W - 1) / W) * mem[i]->p.ny;
-    }
-    for (int c = 0; c < NCLS; c++) {
-      const int slots = resident(lb_kernel(c), cls_bx[c]);
-      lseg[c] = cls_seg[c] > 0 ? cls_seg[c] : (int)std::max<long long>(4, (rows[c] + slots - 1) / slots);
-      ncm[c] = 0;
-    }
+    std::vector<int> mpre(n + 1, 0), cm(NLIST * n, 0), bpre(NLIST * 2 * (n + 1), 0);
+    const int W[2] = {64 - 2 * strip_halo<St>(), 64 - 2 * strip_halo<MacroStore2<R>>()};
+    // rows per wave: with seg 0 (automatic) all members' items together are
+    // one resident round of the kernel the steps inside a call run
+    long long rows = 0;
+    for (auto m : mem) rows += (long long)((m->p.nx + W[1] - 1) / W[1]) * m->p.ny;
+    const int slots = force_form ? resident_blocks((const void*)&kb_lb2d<St, R, 1, true, true, false>, 64)
+                                 : resident_blocks((const void*)&kb_lb2d<St, R, 0, true, true, false>, 64);
+    for (int c = 0; c < NCLS; c++)
+      lseg[c] = cls_seg[c] > 0 ? cls_seg[c] : (int)std::max<long long>(MIN_SEG2, (rows + slots - 1) / slots);
     long long tiles = 0;
+    macro = true;
+    for (int l = 0; l < NLIST; l++) ncm[l] = 0;
     for (int i = 0; i < n; i++) {
       Mem* m = mem[i];
-      const int c = cls[i];
-      BMember<St>& B = T[i];
+      BM& B = T[i];
       B.P = m->P;
-      const int W = cls_bx[c] - 4;
-      B.P.seg = std::min(lseg[c], m->p.ny);
-      B.P.nstrip = (m->p.nx + W - 1) / W;
+      B.P.seg = std::min(lseg[size_class(m->p.nx)], m->p.ny);
       B.P.nseg = (m->p.ny + B.P.seg - 1) / B.P.seg;
       B.P.nxcd = 1;
+      B.P.mode = 0;
       B.a = m->store(0);
       B.b = m->store(1);
+      B.ma = m->macro(0);
+      B.mb = m->macro(1);
       B.md = m->memdev();
       B.tm = m->tilemap();
       B.ca = m->coup_args(1);
@@ -990,19 +1006,22 @@ struct BatchEngine2D final : lbib_sim {
       for (int k = 0; k < m->K; k++) mems.push_back(make_int2(i, k));
       mpre[i + 1] = mpre[i] + m->M;
       tiles += m->L.ntiles * (m->K > 0);
-      const int q = ncm[c]++;
-      cm[c * n + q] = i;
-      bpre[c * (n + 1) + q + 1] = bpre[c * (n + 1) + q] + B.P.nstrip * B.P.nseg;
+      macro = macro && m->macro_steps();
+      const int l = m->relaxes() ? 1 : 0, q = ncm[l]++;
+      cm[l * n + q] = i;
+      for (int sm = 0; sm < 2; sm++) {
+        B.nstrip[sm] = (m->p.nx + W[sm] - 1) / W[sm];
+        int* pre = bpre.data() + (l * 2 + sm) * (n + 1);
+        pre[q + 1] = pre[q] + B.nstrip[sm] * B.P.nseg;
+      }
     }
     nmems = (int)mems.size();
     Mtot = mpre[n];
     cgrid = (int)std::max<long long>(1, std::min<long long>(tiles, 4096));
-    for (int c = 0; c < NCLS; c++) {
-      const int items = bpre[c * (n + 1) + ncm[c]];
-      lgrid[c] = std::max(1, items);  // one item per workgroup
-    }
+    for (int l = 0; l < NLIST; l++)
+      for (int sm = 0; sm < 2; sm++) lgrid[l][sm] = bpre[(l * 2 + sm) * (n + 1) + ncm[l]];
     hipStream_t st = stream;
-    HIPCHK(hipMemcpyAsync(ws + off_tab, T.data(), T.size() * sizeof(BMember<St>), hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(ws + off_tab, T.data(), T.size() * sizeof(BM), hipMemcpyHostToDevice, st));
     if (!mems.empty())
       HIPCHK(hipMemcpyAsync(ws + off_mems, mems.data(), mems.size() * sizeof(int2), hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(ws + off_mpre, mpre.data(), mpre.size() * 4, hipMemcpyHostToDevice, st));
@@ -1010,90 +1029,99 @@ struct BatchEngine2D final : lbib_sim {
     HIPCHK(hipMemcpyAsync(ws + off_bpre, bpre.data(), bpre.size() * 4, hipMemcpyHostToDevice, st));
     HIPCHK(hipStreamSynchronize(st));
     drop_graphs();
-    if (use_graph) {
-      graph_ok = true;
-      for (int par = 0; par < 2 && graph_ok; par++) {
-        hipGraph_t g = nullptr;
-        if (hipStreamBeginCapture(st, hipStreamCaptureModeRelaxed) != hipSuccess) {
-          graph_ok = false;
-          break;
-        }
-        launch_all(par);
-        if (hipStreamEndCapture(st, &g) != hipSuccess || !g ||
-            hipGraphInstantiate(&gexec[par], g, nullptr, nullptr, 0) != hipSuccess)
-          graph_ok = false;
-        if (g) (void)hipGraphDestroy(g);
-      }
-      if (!graph_ok) {
-        drop_graphs();
-        (void)hipGetLastError();  // a stream that cannot be captured: launch directly
-      }
-    }
+    graph_ok = use_graph;
     dirty = false;
     return LBIB_OK;
   }
 
-  void launch_all(int parity) {
+  template <int FORM, bool SM, bool DM>
+  void launch_lb(int parity) {
     const int n = (int)mem.size();
-    BMember<St>* T = at<BMember<St>>(off_tab);
-    const int* mpre = at<int>(off_mpre);
-    hipLaunchKernelGGL(kb_begin<St>, dim3((n + 63) / 64), dim3(64), 0, stream, T, n);
-    if (nmems > 0) {
-      hipLaunchKernelGGL((kb_tiles<St, 256>), dim3(nmems), dim3(256), 0, stream, (const BMember<St>*)T,
-                         (const int2*)at<int2>(off_mems));
-      hipLaunchKernelGGL((kb_coupling2d<St, R, COUP_THREADS>), dim3(cgrid), dim3(COUP_THREADS), 0, stream,
-                         (const BMember<St>*)T, n, parity);
-      hipLaunchKernelGGL(kb_forcespread2d<St>, dim3((16 * Mtot + 255) / 256), dim3(256), 0, stream,
-                         (const BMember<St>*)T, mpre, n);
+    const BM* T = at<BM>(off_tab);
+    for (int l = 0; l < NLIST; l++) {
+      if (!ncm[l]) continue;
+      const int* cml = at<int>(off_cm) + l * n;
+      const int* bp = at<int>(off_bpre) + (l * 2 + SM) * (n + 1);
+      if (l == 0)
+        hipLaunchKernelGGL((kb_lb2d<St, R, FORM, SM, DM, false>), dim3(lgrid[l][SM]), dim3(64), 0, stream, T, cml, bp,
+                           ncm[l], parity);
+      else if constexpr (!SM && !DM)
+        hipLaunchKernelGGL((kb_lb2d<St, R, FORM, SM, DM, true>), dim3(lgrid[l][SM]), dim3(64), 0, stream, T, cml, bp,
+                           ncm[l], parity);
     }
-    for (int c = 0; c < NCLS; c++) {
-      if (!ncm[c]) continue;
-      const int* cmc = at<int>(off_cm) + c * n;
-      const int* bp = at<int>(off_bpre) + c * (n + 1);
-      const BMember<St>* Tc = T;
-#define KB_LAUNCH(BXV, NSV, WPEV)                                                                    \
-  do {                                                                                               \
-    if (force_form == 1)                                                                             \
-      hipLaunchKernelGGL((kb_lb2d<St, R, BXV, NSV, 2, 1>), dim3(lgrid[c]), dim3(BXV), 0, stream, Tc, cmc, bp, \
-                         ncm[c], parity);                                                            \
-    else                                                                                             \
-      hipLaunchKernelGGL((kb_lb2d<St, R, BXV, NSV, WPEV>), dim3(lgrid[c]), dim3(BXV), 0, stream, Tc, cmc, bp, \
-                         ncm[c], parity);                                                            \
-  } while (0)
-      if (cls_ring[c] == 4) {
-        if (cls_bx[c] == 128) KB_LAUNCH(128, 4, 2);
-        else if (cls_bx[c] == 192) KB_LAUNCH(192, 4, 2);
-        else if (cls_bx[c] == 256) KB_LAUNCH(256, 4, 2);
-        else KB_LAUNCH(64, 4, 2);
-      } else {
-        if (cls_bx[c] == 128) KB_LAUNCH(128, 3, 3);
-        else if (cls_bx[c] == 192) KB_LAUNCH(192, 3, 3);
-        else if (cls_bx[c] == 256) KB_LAUNCH(256, 3, 3);
-        else KB_LAUNCH(64, 3, 3);
-      }
-#undef KB_LAUNCH
-    }
-    if (nmems > 0)
-      hipLaunchKernelGGL((kb_interp2d<St, R>), dim3((16 * Mtot + 255) / 256), dim3(256), 0, stream,
-                         (const BMember<St>*)T, mpre, n, parity);
   }
 
-  int step() override {
-    if (dirty) {
-      int rc = prepare();
-      if (rc) return rc;
+  template <bool SM, bool DM>
+  void launch_all(int parity) {
+    const int n = (int)mem.size();
+    BM* T = at<BM>(off_tab);
+    const int* mpre = at<int>(off_mpre);
+    hipLaunchKernelGGL((kb_begin<St, R>), dim3((n + 63) / 64), dim3(64), 0, stream, T, n);
+    if (nmems > 0) {
+      hipLaunchKernelGGL((kb_tiles<St, R, 256>), dim3(nmems), dim3(256), 0, stream, (const BM*)T,
+                         (const int2*)at<int2>(off_mems));
+      hipLaunchKernelGGL((kb_coupling2d<St, R, COUP_THREADS, SM>), dim3(cgrid), dim3(COUP_THREADS), 0, stream,
+                         (const BM*)T, n, parity);
+      hipLaunchKernelGGL((kb_forcespread2d<St, R>), dim3((16 * Mtot + 255) / 256), dim3(256), 0, stream, (const BM*)T,
+                         mpre, n);
     }
+    if (force_form == 1)
+      launch_lb<1, SM, DM>(parity);
+    else
+      launch_lb<0, SM, DM>(parity);
+    if (nmems > 0)
+      hipLaunchKernelGGL((kb_interp2d<St, R, DM>), dim3((16 * Mtot + 255) / 256), dim3(256), 0, stream, (const BM*)T,
+                         mpre, n, parity);
+  }
+
+  // one step, replayed from its graph (captured at its first use; a stream
+  // that cannot be captured launches directly)
+  template <bool SM, bool DM>
+  int step() {
     const int parity = mem[0]->cur;
+    hipGraphExec_t& ge = gexec[parity][SM][DM];
+    if (graph_ok && !ge) {
+      hipGraph_t g = nullptr;
+      if (hipStreamBeginCapture(stream, hipStreamCaptureModeRelaxed) != hipSuccess) {
+        graph_ok = false;
+      } else {
+        launch_all<SM, DM>(parity);
+        if (hipStreamEndCapture(stream, &g) != hipSuccess || !g ||
+            hipGraphInstantiate(&ge, g, nullptr, nullptr, 0) != hipSuccess)
+          graph_ok = false;
+        if (g) (void)hipGraphDestroy(g);
+      }
+      if (!graph_ok) {
+        ge = nullptr;
+        drop_graphs();
+        (void)hipGetLastError();
+      }
+    }
     if (graph_ok) {
-      if (hipGraphLaunch(gexec[parity], stream) != hipSuccess) return LBIB_EHIP;
+      if (hipGraphLaunch(ge, stream) != hipSuccess) return LBIB_EHIP;
     } else {
-      launch_all(parity);
+      launch_all<SM, DM>(parity);
     }
     for (auto m : mem) {
       m->cur = 1 - m->cur;
       m->steps++;
     }
+    steps++;
     return hipGetLastError() == hipSuccess ? LBIB_OK : LBIB_EHIP;
+  }
+
+  int advance(int n) override {
+    if (n > 0 && dirty) {
+      int rc = prepare();
+      if (rc) return rc;
+    }
+    const bool mac = n > 1 && macro;
+    for (int k = 0; k < n; k++) {
+      const bool in = mac && k > 0, out = mac && k + 1 < n;
+      const int rc = in ? (out ? step<true, true>() : step<true, false>()) : (out ? step<false, true>() : step<false, false>());
+      if (rc) return rc;
+    }
+    return LBIB_OK;
   }
 };
 
@@ -1418,12 +1446,7 @@ int lbib_set_fields(lbib_sim* s, const double* rho, const double* phi, const dou
 int lbib_step(lbib_sim* s, int n) {
   if (!s || n < 0) return LBIB_EINVAL;
   if (!s->ready || s->owner) return LBIB_ESTATE;  // batch members step with their batch
-  for (int k = 0; k < n; k++) {
-    int rc = s->step();
-    if (rc) return rc;
-    s->steps++;
-  }
-  return LBIB_OK;
+  return s->advance(n);
 }
 
 long long lbib_steps_done(const lbib_sim* s) { return s ? s->steps : -1; }
@@ -1823,10 +1846,10 @@ int lbib_batch_create(int n, const lbib_params* params, void* ws, size_t ws_byte
   b->stream = (hipStream_t)stream;
   b->ready = true;
   b->off_tab = 0;
-  b->off_mems = align_up((size_t)n * sizeof(BMember<BatchEngine2D::St>));
+  b->off_mems = align_up((size_t)n * sizeof(BatchEngine2D::BM));
   b->off_mpre = b->off_mems + align_up((size_t)std::max(kmax, 1) * sizeof(int2));
   b->off_cm = b->off_mpre + align_up((size_t)(n + 1) * 4);
-  b->off_bpre = b->off_cm + align_up((size_t)BatchEngine2D::NCLS * n * 4);
+  b->off_bpre = b->off_cm + align_up((size_t)BatchEngine2D::NLIST * n * 4);
   size_t off = BatchEngine2D::table_bytes(n, kmax);
   for (int i = 0; i < n; i++) {
     Layout L = make_layout(&params[i]);

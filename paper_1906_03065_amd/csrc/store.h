@@ -23,6 +23,7 @@
 //   rest(set, node)            g_0 / h_0 (set 1, 2) as double, f_0 for set 0
 //   store<R>(set, i, node, v)  moving population (or f_0)
 //   store_rest(set, node, v)   g_0 / h_0
+//   pull<R>(set, i, flip, node)  load of population i, or (flip) of the opposite one
 #pragma once
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
@@ -52,7 +53,12 @@ struct PlainStore {
   __device__ __forceinline__ void store_rest(int set, long long node, double v) const {
     p[((long long)(set * Q)) * N + node] = (T)v;
   }
-  static constexpr bool kQuantized = false;
+  // moving population i (or, flip, its opposite), as the kernels near a membrane pull it
+  template <typename R>
+  __device__ __forceinline__ R pull(int set, int i, bool flip, long long node) const {
+    return load<R>(set, flip ? Lattice<Q>::opp[i] : i, node);
+  }
+  static constexpr bool kQuantized = false, kMacro = false, kDropsOutOfRange = false;
   template <typename R>
   __device__ __forceinline__ R quantize(R v) const { return v; }
   static constexpr long long bytes_per_node() { return 3LL * Q * (long long)sizeof(T); }
@@ -67,7 +73,8 @@ struct PlainStore {
 // Accesses go through buffer resources: the plane offset is a uniform
 // (scalar) byte offset and the node a 32-bit per-lane offset, so one address
 // register serves the three populations that travel along the same link.
-// The FP32 planes of one buffer must stay below 4 GiB (checked on the host).
+// The FP32 planes of one buffer must stay below 4 GiB (checked on the host);
+// a store to node -1 lies beyond the buffer's range and is dropped.
 template <int Q>
 struct MixStore {
   float* p;
@@ -77,10 +84,10 @@ struct MixStore {
     return set == 0 ? i : (set == 1 ? Q + i - 1 : 2 * Q - 1 + i - 1);
   }
   __device__ __forceinline__ __amdgpu_buffer_rsrc_t rp() const {
-    return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)0xffffffffu, 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)(float_planes() * N * 4), 0x00020000);
   }
   __device__ __forceinline__ __amdgpu_buffer_rsrc_t rr() const {
-    return __builtin_amdgcn_make_buffer_rsrc(r, 0, (int)0xffffffffu, 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc(r, 0, (int)(2 * N * 8), 0x00020000);
   }
   template <typename R>
   __device__ __forceinline__ R load(int set, int i, long long node) const {
@@ -112,7 +119,11 @@ struct MixStore {
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rr(), (int)(node * 8),
                                           (int)((long long)(set - 1) * N * 8), 0);
   }
-  static constexpr bool kQuantized = false;
+  template <typename R>
+  __device__ __forceinline__ R pull(int set, int i, bool flip, long long node) const {
+    return load<R>(set, flip ? Lattice<Q>::opp[i] : i, node);
+  }
+  static constexpr bool kQuantized = false, kMacro = false, kDropsOutOfRange = true;
   template <typename R>
   __device__ __forceinline__ R quantize(R v) const { return v; }
   static constexpr long long float_planes() { return 3LL * Q - 2; }
@@ -162,10 +173,14 @@ struct Split16Store {
       r12[(long long)(set - 1) * N + node] = v;
   }
   // the value a moving population reads back as after a store
-  static constexpr bool kQuantized = true;
+  static constexpr bool kQuantized = true, kMacro = false, kDropsOutOfRange = false;
   template <typename R>
   __device__ __forceinline__ R quantize(R v) const {
     return (R)(to_float(from_float((float)v * kScale)) * kInv);
+  }
+  template <typename R>
+  __device__ __forceinline__ R pull(int set, int i, bool flip, long long node) const {
+    return load<R>(set, flip ? Lattice<Q>::opp[i] : i, node);
   }
   __device__ static __forceinline__ float to_float(__half h) { return __half2float(h); }
   __device__ static __forceinline__ float to_float(__hip_bfloat16 h) { return __bfloat162float(h); }
