@@ -67,8 +67,10 @@ struct MemDev {
 struct TileMap {
   int* tflag;         // per tile: stamp of the last step it was active in
   int* tlist;         // active tiles of this step
-  int* tstate;        // [0] active-tile count, [1] stamp of this step, [2] 3D tile counter,
-                      // [4], [5] active-tile counts of a 2D simulation, by stamp parity
+  int* tstate;        // [0] active-tile count, [1] stamp of this step; 3D: [3] tiles left to
+                      // the search, [6] to the second pass, [7] entries to renew, and the
+                      // counters [2], [4], [8] their workgroups take tiles from; 2D: [4], [5]
+                      // active-tile counts of a simulation of its own, by stamp parity
   int ntx, nty, ntz, tile;
 };
 
@@ -149,13 +151,12 @@ __device__ float block_minf(float v, float* sh) {
 
 // ---------------------------------------------------------------------------
 // new step of the tile map (3D simulations and batch members; one thread):
-// [0] active-tile count, [1] stamp, [2] counter the 3D profile kernel's
-// workgroups take tiles from
+// [0] active-tile count, [1] stamp, [2] on: the counters of the 3D profile kernels
 __global__ void k_begin(int* tstate) {
   if (threadIdx.x == 0) {
     tstate[0] = 0;
     tstate[1] = tstate[1] + 1;
-    tstate[2] = 0;
+    for (int k = 2; k < 16; k++) tstate[k] = 0;
   }
 }
 

@@ -34,8 +34,14 @@ constexpr int COUP3_HASH = 512;
 // taken to lie beyond the band without a node search only COUP3_BEYOND
 // farther out, so that entries outlast some drift of the markers.
 constexpr int COUP3_CACHE = 2;
-constexpr float COUP3_PAD = 2.0f;
+constexpr float COUP3_PAD = 2.0f;    // of the search
+constexpr float COUP3_PAD1 = 0.5f;   // of one node's renewal
 constexpr float COUP3_BEYOND = 1.0f;
+// a tile renews at most this many expired entries one by one; with more, it
+// searches in full and renews every entry (some 60 us of a CU, what about a
+// hundred renewals take there)
+constexpr int COUP3_RENEW = 96;
+constexpr int C3_RING = 16;         // entries of a triangle's row in the ring table
 constexpr int C3_KEYB = 20;         // key = membrane << 20 | triangle (or a beyond code)
 constexpr int C3_IN = 0xFFFFE, C3_OUT = 0xFFFFD;
 
@@ -49,6 +55,10 @@ struct MeshDev {
   int* tedge;     // 3 per triangle: the edge opposite vertex k
   int* vtoff;     // M+1: vertex -> incident triangles (CSR)
   int* vt;
+  int* perm;      // triangles of each mesh (ids within it) in the order of the clusters
+  int* ring;      // C3_RING per triangle: the triangles that share a vertex with it, itself
+                  // among them (the count first; -1: more than fit, walk vt)
+  float4* geo;    // per step, C3_GEOT per triangle: G0 .. G5 below about the box centre
   double* fn;     // 3 per triangle: unit face normal (area vector direction)
   double* vn;     // 3 per vertex: angle-weighted normal
   int* coff;      // K+1 offsets of the 64-triangle clusters of each mesh
@@ -60,13 +70,17 @@ __device__ __forceinline__ void sub3(const double* a, const double* b, double* c
   c[1] = a[1] - b[1];
   c[2] = a[2] - b[2];
 }
+// (fused as written, with the compiler's own contraction off here and in
+// tri_d2 and node_profile3: the two profile kernels have to round alike)
 __device__ __forceinline__ double dot3d(const double* a, const double* b) {
-  return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
+#pragma clang fp contract(off)
+  return fma_(a[0], b[0], fma_(a[1], b[1], a[2] * b[2]));
 }
 __device__ __forceinline__ void cross3d(const double* a, const double* b, double* c) {
-  c[0] = a[1] * b[2] - a[2] * b[1];
-  c[1] = a[2] * b[0] - a[0] * b[2];
-  c[2] = a[0] * b[1] - a[1] * b[0];
+#pragma clang fp contract(off)
+  c[0] = fma_(a[1], b[2], -(a[2] * b[1]));
+  c[1] = fma_(a[2], b[0], -(a[0] * b[2]));
+  c[2] = fma_(a[0], b[1], -(a[1] * b[0]));
 }
 
 // ---------------------------------------------------------------------------
@@ -131,6 +145,7 @@ __global__ __launch_bounds__(NT) void k_meshvolume(MemDev md, MeshDev mh) {
 // inside the triangle, otherwise the nearest of the three edges.
 __device__ __forceinline__ double tri_d2(const double* p, const double* a, const double* b,
                                          const double* c, double* w) {
+#pragma clang fp contract(off)
   double e0[3], e1[3], ap[3], n[3];
   sub3(b, a, e0);
   sub3(c, a, e1);
@@ -163,8 +178,8 @@ __device__ __forceinline__ double tri_d2(const double* p, const double* a, const
     const double ee = dot3d(ed, ed);
     double t = ee > 0.0 ? dot3d(sp, ed) / ee : 0.0;
     t = fmin(fmax(t, 0.0), 1.0);
-    const double dx = sp[0] - t * ed[0], dy = sp[1] - t * ed[1], dz = sp[2] - t * ed[2];
-    const double d2 = dx * dx + dy * dy + dz * dz;
+    const double f[3] = {fma_(-t, ed[0], sp[0]), fma_(-t, ed[1], sp[1]), fma_(-t, ed[2], sp[2])};
+    const double d2 = dot3d(f, f);
     if (d2 < best) {
       best = d2;
       w[k] = 1.0 - t;
@@ -179,8 +194,9 @@ struct Coup3Args {
   int nx, ny, nz, wall_y, wall_z;
   double alpha, kappa_c, r_cut;
   int want_force;
-  // per node and cached membrane slot (COUP3_CACHE x N): key and bound (plus
-  // the membrane's drift when written); null disables the cache
+  // per node and cached membrane slot (COUP3_CACHE x N): key, and bound (plus
+  // the membrane's drift when written) with the node's periodic image in its
+  // last three bits; null disables the cache
   int* ckey;
   float* clb;
   long long N;
@@ -237,6 +253,32 @@ __device__ __forceinline__ TileGeo tile_geo(const double* bx, const double* ct, 
   return g;
 }
 
+// a triangle's geometry in FP32 about pc, precomputed in FP64 (G0 to G5 of the
+// search's candidates, see geo_store; put(k, G_k))
+template <class F>
+__device__ __forceinline__ void geo_write(const double* a, const double* b, const double* c, const double* pc, F put,
+                                          int3 tv) {
+  double e0[3], e1[3], e2[3], n[3], U[3], V[3];
+  sub3(b, a, e0);
+  sub3(c, a, e1);
+  sub3(e1, e0, e2);
+  cross3d(e0, e1, n);
+  const double nn = dot3d(n, n);
+  const double inn = nn > 0.0 ? 1.0 / nn : 0.0;
+  cross3d(e1, n, U);
+  cross3d(n, e0, V);
+  const double l0 = dot3d(e0, e0), l1 = dot3d(e1, e1), l2 = dot3d(e2, e2);
+  const double rn = nn > 0.0 ? 1.0 / sqrt(nn) : 0.0;
+  put(0, make_float4((float)(a[0] - pc[0]), (float)(a[1] - pc[1]), (float)(a[2] - pc[2]),
+                     l0 > 0.0 ? (float)(1.0 / l0) : 0.0f));
+  put(1, make_float4((float)e0[0], (float)e0[1], (float)e0[2], l1 > 0.0 ? (float)(1.0 / l1) : 0.0f));
+  put(2, make_float4((float)e1[0], (float)e1[1], (float)e1[2], l2 > 0.0 ? (float)(1.0 / l2) : 0.0f));
+  put(3, make_float4((float)(U[0] * inn), (float)(U[1] * inn), (float)(U[2] * inn), __int_as_float(tv.x)));
+  put(4, make_float4((float)(V[0] * inn), (float)(V[1] * inn), (float)(V[2] * inn), __int_as_float(tv.y)));
+  put(5, make_float4((float)(n[0] * rn), (float)(n[1] * rn), (float)(n[2] * rn), __int_as_float(tv.z)));
+}
+constexpr int C3_GEOT = 6;
+
 // ---------------------------------------------------------------------------
 // Closest-triangle search.  Distances are first compared in FP32 (with
 // margins far above the FP32 rounding), and every triangle whose FP32
@@ -252,6 +294,7 @@ __device__ __forceinline__ TileGeo tile_geo(const double* bx, const double* ct, 
 
 // per-step FP32 table: 4 float4 per triangle, relative to the box centre of
 // the triangle's membrane: the vertices, then (centroid, bounding radius)
+// (and, in mh.geo, the derived geometry that geo_store describes)
 __global__ void k_tritable3d(MemDev md, MeshDev mh, float4* __restrict__ tab) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= mh.T) return;
@@ -271,10 +314,12 @@ __global__ void k_tritable3d(MemDev md, MeshDev mh, float4* __restrict__ tab) {
   }
   tab[4 * t + 3] = make_float4((float)(g[0] - c[0]), (float)(g[1] - c[1]), (float)(g[2] - c[2]),
                                (float)(r * (1.0 + 1e-6) + 1e-5));
+  geo_write(v[0], v[1], v[2], c, [&](int k, float4 q) { mh.geo[C3_GEOT * (size_t)t + k] = q; }, make_int3(0, 0, 0));
 }
 
-// bounding sphere of every cluster of 64 consecutive triangles of a mesh,
-// from the triangles' spheres (one wave per cluster)
+// bounding sphere of every cluster of 64 triangles of a mesh (mh.perm: near each
+// other when the mesh was added, whatever order its triangles came in), from
+// the triangles' spheres (one wave per cluster)
 constexpr int CL3 = 64;
 __global__ void k_clusters3d(MemDev md, MeshDev mh, const float4* __restrict__ tab, float4* __restrict__ ctab,
                              int ncl) {
@@ -285,7 +330,7 @@ __global__ void k_clusters3d(MemDev md, MeshDev mh, const float4* __restrict__ t
   const int t0 = mh.toff[m] + (gk - mh.coff[m]) * CL3, t1 = min(t0 + CL3, mh.toff[m + 1]);
   const int t = t0 + lane;
   const bool live = t < t1;
-  float4 sp = live ? tab[4 * t + 3] : make_float4(0.f, 0.f, 0.f, 0.f);
+  float4 sp = live ? tab[4 * (mh.toff[m] + mh.perm[t]) + 3] : make_float4(0.f, 0.f, 0.f, 0.f);
   float sx = sp.x, sy = sp.y, sz = sp.z;
   for (int o = 32; o > 0; o >>= 1) {
     sx += __shfl_xor(sx, o, 64);
@@ -351,46 +396,30 @@ __device__ __forceinline__ float tri_d2f_vtx(float px, float py, float pz, float
 // FP64: G0 = (a, 1/|e0|^2), G1 = (e0, 1/|e1|^2), G2 = (e1, 1/|e2|^2),
 // G3 = (e1 x n)/|n|^2, G4 = (n x e0)/|n|^2, G5 = n/|n|, so that the
 // barycentric coordinates of the projection are ap.G3, ap.G4; and the
-// bounding sphere G6 = (centroid, radius)
+// bounding sphere G6 = (centroid, radius); G3 to G5 carry the triangle's vertex
+// ids in their last words
 constexpr int C3_LIST = 512;   // candidates whose geometry is staged at once
 constexpr int C3_IDS = 4096;   // candidate ids of one tile
 constexpr int C3_GEO = 7;
 constexpr int C3_TIES = 8;    // near-ties a node keeps in registers
 
-__device__ __forceinline__ void geo_store(float4 (*sg)[C3_LIST], int j, const double* a, const double* b,
-                                          const double* c, const double* pc) {
-  double e0[3], e1[3], e2[3], n[3], U[3], V[3], g[3];
-  sub3(b, a, e0);
-  sub3(c, a, e1);
-  sub3(e1, e0, e2);
-  cross3d(e0, e1, n);
-  const double nn = dot3d(n, n);
-  const double inn = nn > 0.0 ? 1.0 / nn : 0.0;
-  cross3d(e1, n, U);
-  cross3d(n, e0, V);
-  const double l0 = dot3d(e0, e0), l1 = dot3d(e1, e1), l2 = dot3d(e2, e2);
-  const double rn = nn > 0.0 ? 1.0 / sqrt(nn) : 0.0;
+__device__ __forceinline__ void geo_store(float4 (*sg)[C3_LIST], int j, const int* tv, const double* a,
+                                          const double* b, const double* c, const double* pc) {
+  geo_write(a, b, c, pc, [&](int k, float4 q) { sg[k][j] = q; }, make_int3(tv[0], tv[1], tv[2]));
+  double g[3], r = 0.0;
   for (int q = 0; q < 3; q++) g[q] = (a[q] + b[q] + c[q]) / 3.0;
-  double r = 0.0;
   const double* P[3] = {a, b, c};
   for (int k = 0; k < 3; k++) {
     double d[3];
     sub3(P[k], g, d);
     r = fmax(r, sqrt(dot3d(d, d)));
   }
-  sg[0][j] = make_float4((float)(a[0] - pc[0]), (float)(a[1] - pc[1]), (float)(a[2] - pc[2]),
-                         l0 > 0.0 ? (float)(1.0 / l0) : 0.0f);
-  sg[1][j] = make_float4((float)e0[0], (float)e0[1], (float)e0[2], l1 > 0.0 ? (float)(1.0 / l1) : 0.0f);
-  sg[2][j] = make_float4((float)e1[0], (float)e1[1], (float)e1[2], l2 > 0.0 ? (float)(1.0 / l2) : 0.0f);
-  sg[3][j] = make_float4((float)(U[0] * inn), (float)(U[1] * inn), (float)(U[2] * inn), 0.0f);
-  sg[4][j] = make_float4((float)(V[0] * inn), (float)(V[1] * inn), (float)(V[2] * inn), 0.0f);
-  sg[5][j] = make_float4((float)(n[0] * rn), (float)(n[1] * rn), (float)(n[2] * rn), 0.0f);
   sg[6][j] = make_float4((float)(g[0] - pc[0]), (float)(g[1] - pc[1]), (float)(g[2] - pc[2]),
                          (float)(r * (1.0 + 1e-6) + 1e-5));
 }
 
-__device__ __forceinline__ float geo_d2f(const float4 (*sg)[C3_LIST], int j, float px, float py, float pz) {
-  const float4 g0 = sg[0][j], g1 = sg[1][j], g2 = sg[2][j], g3 = sg[3][j], g4 = sg[4][j], g5 = sg[5][j];
+__device__ __forceinline__ float geo_d2(float4 g0, float4 g1, float4 g2, float4 g3, float4 g4, float4 g5, float px,
+                                        float py, float pz) {
   const float apx = px - g0.x, apy = py - g0.y, apz = pz - g0.z;
   const float u = dot3f(apx, apy, apz, g3.x, g3.y, g3.z), v = dot3f(apx, apy, apz, g4.x, g4.y, g4.z);
   const float h = dot3f(apx, apy, apz, g5.x, g5.y, g5.z);
@@ -398,6 +427,22 @@ __device__ __forceinline__ float geo_d2f(const float4 (*sg)[C3_LIST], int j, flo
   d = fminf(d, seg_d2f(apx, apy, apz, g2.x, g2.y, g2.z, g1.w));
   d = fminf(d, seg_d2f(apx - g1.x, apy - g1.y, apz - g1.z, g2.x - g1.x, g2.y - g1.y, g2.z - g1.z, g2.w));
   return (u > 0.0f && v > 0.0f && u + v < 1.0f) ? h * h : d;
+}
+__device__ __forceinline__ float geo_d2f(const float4 (*sg)[C3_LIST], int j, float px, float py, float pz) {
+  return geo_d2(sg[0][j], sg[1][j], sg[2][j], sg[3][j], sg[4][j], sg[5][j], px, py, pz);
+}
+__device__ __forceinline__ float geo_d2g(const float4* g, float px, float py, float pz) {
+  return geo_d2(g[0], g[1], g[2], g[3], g[4], g[5], px, py, pz);
+}
+
+__device__ __forceinline__ bool geo_shares(const float4 (*sg)[C3_LIST], int j, int v0, int v1, int v2) {
+  bool adj = false;
+#pragma unroll
+  for (int k = 3; k < 6; k++) {
+    const int u = __float_as_int(sg[k][j].w);
+    adj |= u == v0 || u == v1 || u == v2;
+  }
+  return adj;
 }
 
 // side of point P (true: inside) at its closest triangle tg with weights w:
@@ -465,15 +510,281 @@ __device__ void block_argmin(double& d, int& i, double* sd, int* si) {
 }
 
 
-// one 8^3 tile at a time per workgroup of 512 threads; resident workgroups
-// take the active tiles from a counter (tiles differ in cost by 20x, so a
-// fixed assignment leaves CUs idle at the end); wave w holds the 4^3
-// sub-tile (w & 1, (w >> 1) & 1, w >> 2)
+// FP32 distances of geo_d2g at p (about the box centre) are within this of exact
+__device__ __forceinline__ float geo_margin(float b, float px, float py, float pz) {
+  return 1e-3f + 1e-5f * b + 2e-6f * (fabsf(px) + fabsf(py) + fabsf(pz)) * (1.0f + b);
+}
+
+// The closest triangle to P over the whole mesh by one wave (FP64, lowest index
+// on ties) and a lower bound on the distance of every triangle that shares no
+// vertex with it, at most COUP3_PAD1 above its own distance.  near: a squared
+// distance known to be reached (3e38: none).  One FP32 scan of the clusters that
+// come within reach, two at a time, one triangle per lane; each lane keeps its
+// three nearest, among which the near-ties are compared in FP64 and the bound is
+// found (a lane whose three all share a vertex with the closest triangle bounds
+// its others by the third).
+__device__ __forceinline__ void wave_closest3(const MemDev& md, const MeshDev& mh, const float4* __restrict__ cls,
+                                              int ncl, int t0m, int nt, const double* bx, const double* P, float near,
+                                              double& d2, int& t, double& lb) {
+  const int lane = threadIdx.x & 63;
+  const float mg = 0.02f;
+  const float px = (float)(P[0] - 0.5 * (bx[0] + bx[3])), py = (float)(P[1] - 0.5 * (bx[1] + bx[4])),
+              pz = (float)(P[2] - 0.5 * (bx[2] + bx[5]));
+  float ul = sqrtf(near);
+  for (int k = lane; k < ncl; k += 64) ul = fminf(ul, sph_dist(px, py, pz, cls[k]) + cls[k].w);
+  const float reach = wave_minf(ul) + mg + COUP3_PAD1;
+  float k0 = 3.0e38f, k1 = 3.0e38f, k2 = 3.0e38f;  // this lane's nearest, ascending
+  int q0 = -1, q1 = -1, q2 = -1;
+  auto add = [&](float d, int q) {
+    if (d < k2) {
+      k2 = d;
+      q2 = q;
+    }
+    if (k2 < k1) {
+      const float f = k1;
+      const int i = q1;
+      k1 = k2;
+      q1 = q2;
+      k2 = f;
+      q2 = i;
+    }
+    if (k1 < k0) {
+      const float f = k0;
+      const int i = q0;
+      k0 = k1;
+      q0 = q1;
+      k1 = f;
+      q1 = i;
+    }
+  };
+  const float4* geo = mh.geo + C3_GEOT * (size_t)t0m;
+  const int* perm = mh.perm + t0m;
+  auto scan = [&](auto visit) {
+    for (int c0 = 0; c0 < ncl; c0 += 64) {
+      float lo = 3.0e38f;
+      if (c0 + lane < ncl) {
+        const float4 cs = cls[c0 + lane];
+        lo = sph_dist(px, py, pz, cs) - cs.w;
+      }
+      unsigned long long todo = __ballot(lo <= reach);
+      while (todo) {
+        const int ka = __ffsll((long long)todo) - 1;
+        todo &= todo - 1ull;
+        const int kb = todo ? __ffsll((long long)todo) - 1 : ka;  // an odd one out is taken twice
+        todo &= todo - 1ull;
+        const int pa = (c0 + ka) * CL3 + lane, pb = (c0 + kb) * CL3 + lane;
+        const int qa = perm[min(pa, nt - 1)], qb = perm[min(pb, nt - 1)];
+        const float da = geo_d2g(geo + C3_GEOT * (size_t)qa, px, py, pz);
+        const float db = geo_d2g(geo + C3_GEOT * (size_t)qb, px, py, pz);
+        if (pa < nt) visit(da, qa);
+        if (kb != ka && pb < nt) visit(db, qb);
+      }
+    }
+  };
+  scan(add);
+  const float bf = wave_minf(k0), tol = bf + geo_margin(bf, px, py, pz);
+  d2 = 1e300;
+  t = -1;
+  auto exact = [&](int q) {
+    double w[3];
+    argmin_merge(d2, t, tri_d2_id(md, mh, t0m + q, P, w), q);
+  };
+  if (k0 <= tol) exact(q0);  // the least of all among them
+  if (k1 <= tol) exact(q1);
+  if (__ballot(k2 <= tol))  // more near-ties than a lane keeps: every one again
+    scan([&](float d, int q) {
+      if (d <= tol) exact(q);
+    });
+  wave_argmin(d2, t);
+  const int* tv = mh.tri + 3 * (t0m + t);
+  const int v0 = tv[0], v1 = tv[1], v2 = tv[2];
+  auto shares = [&](int q) {
+    const int* uv = mh.tri + 3 * (t0m + q);
+    bool adj = false;
+#pragma unroll
+    for (int a = 0; a < 3; a++) adj |= uv[a] == v0 || uv[a] == v1 || uv[a] == v2;
+    return adj;
+  };
+  const float lim = fminf(reach, (float)sqrt(d2) + COUP3_PAD1);
+  float o2 = lim * lim;
+  if (q0 >= 0 && k0 < o2) {
+    if (!shares(q0))
+      o2 = k0;
+    else if (q1 >= 0 && k1 < o2)
+      o2 = shares(q1) ? fminf(o2, k2) : k1;  // (k2 whether it shares or not: a lower bound)
+  }
+  o2 = wave_minf(o2);
+  lb = sqrt(fmax((double)(o2 - geo_margin(o2, px, py, pz)), 0.0));
+}
+
+// what a node keeps of its closest triangle tb (squared distance d2b, bound lb
+// on the others): the triangle, or well beyond the band its side and distance
+__device__ __forceinline__ void entry3(const MemDev& md, const MeshDev& mh, int m, int t0m, int tb, double d2b,
+                                       double lb, const double* P, double o, double r_cut, int& key, double& bound) {
+  key = (m << C3_KEYB) | tb;
+  bound = lb;
+  const double d = sqrt(d2b);
+  if (d > r_cut + COUP3_BEYOND) {
+    double w[3];
+    tri_d2_id(md, mh, t0m + tb, P, w);
+    key = (m << C3_KEYB) | (mesh_side(md, mh, t0m + tb, w, P, o) ? C3_IN : C3_OUT);
+    bound = d;
+  }
+}
+
+// Which periodic image of the node lies nearest the membrane's box centre (its
+// parity per axis).  A node's distances jump when its image changes, so an entry
+// holds for one image; the grown box is narrower than the period, so of two
+// neighbouring images only one is ever inside it.
+__device__ __forceinline__ int image3(const double* pp, const int* xi, const int* dims) {
+  int im = 0;
+#pragma unroll
+  for (int a = 0; a < 3; a++) im |= ((int)((pp[a] - xi[a]) / dims[a]) & 1) << a;
+  return im;
+}
+// the stored form of a bound: with the drift so far added and rounded down, so
+// the bound at a later step is the stored value less the drift then
+__device__ __forceinline__ float bound3(double lb, double drift, int image) {
+  const float v = __double2float_rd(fmax(lb - 1e-3 - 1e-5 * fabs(lb) + drift, 0.0));
+  return __int_as_float((__float_as_int(v) & ~7) | image);
+}
+
+// a band node's closest triangle, the closest point's weights on its first two
+// vertices, and the direction in which the coupling energy pushes them,
+// -sign(d) nhat sech^2(d / 2 alpha) (eq. DiscreteCF without the factor
+// kappa_c / (4 alpha) (psi - I) and the weights)
+struct Band3 {
+  int tri = -1;
+  double w0 = 0.0, w1 = 0.0, g[3] = {0.0, 0.0, 0.0};
+};
+
+// The node's share of the profile from its closest triangle tg (weights w,
+// squared distance d2), and its band data.
+__device__ __forceinline__ double node_profile3(const MemDev& md, const MeshDev& mh, int tg, const double* w,
+                                                const double* P, double d2, double o, double alpha, double r_cut,
+                                                Band3& b) {
+#pragma clang fp contract(off)
+  const bool in = mesh_side(md, mh, tg, w, P, o);
+  const double d = sqrt(d2);
+  if (d > r_cut) return in ? 1.0 : 0.0;
+  double s2;
+  const double I = profile_sech2((in ? d : -d) / (2.0 * alpha), s2);
+  if (d > 0.0) {
+    const int* tv = mh.tri + 3 * tg;
+    b.tri = tg;
+    b.w0 = w[0];
+    b.w1 = w[1];
+    const double f = (in ? -s2 : s2) / d;
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+      const double q = fma_(w[0], md.X[3 * tv[0] + a], fma_(w[1], md.X[3 * tv[1] + a], w[2] * md.X[3 * tv[2] + a]));
+      b.g[a] = f * (P[a] - q);
+    }
+  }
+  return I;
+}
+
+// hash table of the markers a tile's band nodes push: marker ids (-1 free) and
+// fixed-point force sums
+struct ForceTable3 {
+  int v[COUP3_HASH];
+  long long f[COUP3_HASH][3];
+};
+
+// the coupling forces of one tile's band nodes on their markers (eq.
+// DiscreteCF); every thread of the workgroup calls it
+template <class St, typename R, int NT>
+__device__ __forceinline__ void tile_forces3(const MemDev& md, const MeshDev& mh, const Coup3Args& ca, const St& cur,
+                                             ForceTable3& T, const Band3 (&bd)[COUP3_KEEP], const int* xi, bool valid,
+                                             long long node, double Itot) {
+  const int lt = (int)threadIdx.x;
+  bool anyband = false;
+#pragma unroll
+  for (int k = 0; k < COUP3_KEEP; k++) anyband |= bd[k].tri >= 0;
+  // psi only in waves that hold band nodes
+  double psi = 0.0;
+  if (valid && __ballot(anyband) != 0ull) {
+    using L = Lattice<19>;
+    psi = cur.rest(2, node);
+    // neighbour planes, rows and columns of the node, wrapped once
+    const long long pl = (long long)ca.ny * ca.nx;
+    const long long zlo = (xi[2] == 0 ? ca.nz - 1 : xi[2] - 1) * pl, zc = xi[2] * pl;
+    const long long zhi = (xi[2] == ca.nz - 1 ? 0 : xi[2] + 1) * pl;
+    const long long ylo = (long long)(xi[1] == 0 ? ca.ny - 1 : xi[1] - 1) * ca.nx;
+    const long long yhi = (long long)(xi[1] == ca.ny - 1 ? 0 : xi[1] + 1) * ca.nx;
+    const long long yc = (long long)xi[1] * ca.nx;
+    const int xlo = xi[0] == 0 ? ca.nx - 1 : xi[0] - 1, xhi = xi[0] == ca.nx - 1 ? 0 : xi[0] + 1;
+    const bool wylo = ca.wall_y && xi[1] == 0, wyhi = ca.wall_y && xi[1] == ca.ny - 1;
+    const bool wzlo = ca.wall_z && xi[2] == 0, wzhi = ca.wall_z && xi[2] == ca.nz - 1;
+#pragma unroll
+    for (int i = 1; i < 19; i++) {
+      const int ex = L::cx[i], ey = L::cy[i], ez = L::cz[i];
+      const bool back = (ey > 0 ? wylo : (ey < 0 ? wyhi : false)) || (ez > 0 ? wzlo : (ez < 0 ? wzhi : false));
+      const long long sn = (ez > 0 ? zlo : (ez < 0 ? zhi : zc)) + (ey > 0 ? ylo : (ey < 0 ? yhi : yc)) +
+                           (ex > 0 ? xlo : (ex < 0 ? xhi : xi[0]));
+      psi += (double)cur.template pull<R>(2, i, back, back ? node : sn);
+    }
+  }
+  for (int i = lt; i < COUP3_HASH; i += NT) {
+    T.v[i] = -1;
+    T.f[i][0] = T.f[i][1] = T.f[i][2] = 0;
+  }
+  __syncthreads();
+  const double wgt = ca.kappa_c / (4.0 * ca.alpha) * (psi - Itot);
+#pragma unroll
+  for (int c = 0; c < COUP3_KEEP; c++) {
+    const Band3& b = bd[c];
+    if (b.tri < 0) continue;
+    const double ww[3] = {b.w0, b.w1, 1.0 - b.w0 - b.w1};
+    const int* tv = mh.tri + 3 * b.tri;
+    for (int k = 0; k < 3; k++) {
+      const int v = tv[k];
+      long long fx[3];
+#pragma unroll
+      for (int a = 0; a < 3; a++) fx[a] = to_fix(b.g[a] * wgt * ww[k]);
+      // slot of marker v: linear probing from its hash
+      int h = (int)(((unsigned)v * 2654435761u) >> 23) & (COUP3_HASH - 1);
+      int found = -1;
+      for (int probe = 0; probe < COUP3_HASH; probe++) {
+        const int prev = atomicCAS(&T.v[h], -1, v);
+        if (prev == -1 || prev == v) {
+          found = h;
+          break;
+        }
+        h = (h + 1) & (COUP3_HASH - 1);
+      }
+      if (found >= 0) {
+        for (int a = 0; a < 3; a++) atomicAdd((unsigned long long*)&T.f[found][a], (unsigned long long)fx[a]);
+      } else {
+        long long* A = md.Facc + 3 * v;
+        for (int a = 0; a < 3; a++) atomicAdd((unsigned long long*)&A[a], (unsigned long long)fx[a]);
+      }
+    }
+  }
+  __syncthreads();
+  // one global atomic per marker and component (integer sums: the same
+  // totals in any order)
+  for (int i = lt; i < COUP3_HASH; i += NT) {
+    const int v = T.v[i];
+    if (v >= 0) {
+      long long* A = md.Facc + 3 * v;
+      for (int a = 0; a < 3; a++)
+        if (T.f[i][a] != 0) atomicAdd((unsigned long long*)&A[a], (unsigned long long)T.f[i][a]);
+    }
+  }
+}
+
+// The full search: one 8^3 tile at a time per workgroup of 512 threads, of the
+// tiles that k_coupling3d_kept left over (with the cache off, of all active
+// tiles).  Resident workgroups take them from a counter (tiles differ in cost
+// by 20x, so a fixed assignment leaves CUs idle at the end); wave w holds the
+// 4^3 sub-tile (w & 1, (w >> 1) & 1, w >> 2).
 template <class St, typename R, int NT>
 __global__ __launch_bounds__(NT) void k_coupling3d(MemDev md, MeshDev mh, TileMap tm, Coup3Args ca,
                                                    const float4* __restrict__ ttab,
                                                    const float4* __restrict__ ctab,
-                                                   double* __restrict__ Ifield, St cur) {
+                                                   double* __restrict__ Ifield, St cur,
+                                                   const int* __restrict__ list, const int* __restrict__ nlist) {
   static_assert(NT == 512, "one thread per node of an 8^3 tile");
   __shared__ float4 s_g[C3_GEO][C3_LIST];
   __shared__ int s_id[C3_IDS];
@@ -482,12 +793,9 @@ __global__ __launch_bounds__(NT) void k_coupling3d(MemDev md, MeshDev mh, TileMa
   __shared__ double s_red[NT / 64];
   __shared__ int s_redi[NT / 64];
   __shared__ float s_redf[NT / 64];
-  __shared__ int b_tri[COUP3_KEEP][NT];
-  __shared__ double b_sd[COUP3_KEEP][NT];
-  __shared__ int s_hv[COUP3_HASH];                 // marker id of each hash slot, -1 free
-  __shared__ long long s_ha[COUP3_HASH][3];        // its fixed-point force sums
+  __shared__ ForceTable3 s_f;
   __shared__ int s_li;
-  const int ntl = tm.tstate[0];
+  const int ntl = *nlist;
   const double reach = ca.r_cut + 1.0;
   const double hd = 0.5 * TILE3 * 1.7320508075688772;  // tile half-diagonal (box tests)
   // largest distance of a node from the centre of its tile / sub-tile
@@ -508,31 +816,16 @@ __global__ __launch_bounds__(NT) void k_coupling3d(MemDev md, MeshDev mh, TileMa
     __syncthreads();
     const int li = s_li;
     if (li >= ntl) break;  // uniform over the workgroup
-    const int t = tm.tlist[li];
+    const int t = list[li];
     const int tx = t % tm.ntx, ty = (t / tm.ntx) % tm.nty, tz = t / (tm.ntx * tm.nty);
     const int t0[3] = {tx * TILE3, ty * TILE3, tz * TILE3};
     const int xi[3] = {t0[0] + off[0], t0[1] + off[1], t0[2] + off[2]};
     const bool valid = xi[0] < ca.nx && xi[1] < ca.ny && xi[2] < ca.nz;
     const long long nodeid = valid ? ((long long)xi[2] * ca.ny + xi[1]) * ca.nx + xi[0] : 0;
-    // the node's cache entries of both slots, loaded before the membrane loop
-    // so that their latency overlaps the tile geometry (read only for a valid
-    // node inside a grown box, and only with the cache on)
-    int kpre[COUP3_CACHE];
-    float lpre[COUP3_CACHE];
-    {
-      const bool on = ca.ckey != nullptr;
-      const int* kp = on ? ca.ckey : md.status;
-      const float* lp = on ? ca.clb : (const float*)md.status;
-#pragma unroll
-      for (int c = 0; c < COUP3_CACHE; c++) {
-        const long long e = on ? (long long)c * ca.N + nodeid : 0;
-        kpre[c] = kp[e];
-        lpre[c] = lp[e];
-      }
-    }
     const double ct[3] = {t0[0] + 0.5 * (TILE3 - 1), t0[1] + 0.5 * (TILE3 - 1), t0[2] + 0.5 * (TILE3 - 1)};
     double Itot = 0.0;
     int kept = 0;
+    Band3 bd[COUP3_KEEP];
     for (int m = 0; m < md.K; m++) {
       const TileGeo g = tile_geo(md.mbox + 8 * m, ct, xi, t0, dims, per, hd, reach, valid);
       if (g.miss) continue;  // uniform over the block
@@ -542,68 +835,30 @@ __global__ __launch_bounds__(NT) void k_coupling3d(MemDev md, MeshDev mh, TileMa
       double d2b = 1e300;
       int tb = -1;
       bool decided = false;  // I of this node already added (no band data)
-      // cache: a node's entry holds while the nearest triangle of the one-ring
-      // of its kept triangle (FP64, lowest index on ties) is nearer than the
-      // bound less the drift since, or, beyond the band, while the bound less
-      // the drift exceeds r_cut.  A tile skips the search when every node holds.
-      const bool cslot = ca.ckey != nullptr && slot < COUP3_CACHE && !g.split && m < 2048;  // uniform
+      const bool cslot = ca.ckey != nullptr && slot < COUP3_CACHE && m < 2048;  // uniform
       const long long cix = (long long)slot * ca.N + nodeid;
       const double drift = md.mbox[8 * m + 7];
-      bool cached = false;
-      if (cslot) {
-        bool ok = true;
-        int side = -1;
-        if (valid && g.inbox) {
-          int key = kpre[0];
-          float klb = lpre[0];
-#pragma unroll
-          for (int c = 1; c < COUP3_CACHE; c++)
-            if (slot == c) {
-              key = kpre[c];
-              klb = lpre[c];
-            }
-          ok = key >= 0 && (key >> C3_KEYB) == m;
-          if (ok) {
-            const double thr = (double)klb - drift;
-            const int q = key & ((1 << C3_KEYB) - 1);
-            if (q >= C3_OUT) {
-              ok = thr > ca.r_cut;
-              side = q == C3_IN ? 1 : 0;
-            } else {
-              const int* tv = mh.tri + 3 * (t0m + q);
-              for (int k = 0; k < 3; k++) {
-                const int v = tv[k];
-                for (int e = mh.vtoff[v]; e < mh.vtoff[v + 1]; e++) {
-                  const int tq = mh.vt[e];
-                  double w[3];
-                  argmin_merge(d2b, tb, tri_d2_id(md, mh, tq, g.pp, w), tq - t0m);
-                }
-              }
-              ok = sqrt(d2b) < thr;
-            }
-          }
-        }
-        cached = __syncthreads_and(ok) != 0;
-        if (!cached) {
-          d2b = 1e300;
-          tb = -1;
-        } else if (side >= 0) {
-          Itot += side ? 1.0 : 0.0;
-          decided = true;
-        }
-      }
       // entry written after a search (-1: none)
       int keyw = -1;
       double lbw = 0.0;
-      if (cached) {
-        // nothing to search
-      } else if (g.split) {
-        // nodes of different images: each searches the whole mesh in FP64
-        if (g.inbox)
-          for (int q = 0; q < nt; q++) {
-            double w[3];
-            argmin_merge(d2b, tb, tri_d2_id(md, mh, t0m + q, g.pp, w), q);
+      if (g.split) {
+        // nodes of different images: the sub-tile's bounds do not hold for
+        // them, and each is searched for by its wave
+        unsigned long long todo = __ballot(g.inbox);
+        while (todo) {
+          const int ln = __ffsll((long long)todo) - 1;
+          todo &= todo - 1ull;
+          const double P[3] = {__shfl(g.pp[0], ln, 64), __shfl(g.pp[1], ln, 64), __shfl(g.pp[2], ln, 64)};
+          double rd2, rlb;
+          int rt;
+          wave_closest3(md, mh, ctab + mh.coff[m], mh.coff[m + 1] - mh.coff[m], t0m, nt,
+                        md.mbox + 8 * m, P, 3.0e38f, rd2, rt, rlb);
+          if (lane == ln) {
+            d2b = rd2;
+            tb = rt;
+            entry3(md, mh, m, t0m, tb, d2b, rlb, g.pp, o, ca.r_cut, keyw, lbw);
           }
+        }
       } else {
         const double* bx = md.mbox + 8 * m;
         const float pcr[3] = {(float)(g.pc[0] - 0.5 * (bx[0] + bx[3])), (float)(g.pc[1] - 0.5 * (bx[1] + bx[4])),
@@ -611,6 +866,11 @@ __global__ __launch_bounds__(NT) void k_coupling3d(MemDev md, MeshDev mh, TileMa
         const float4* tab = ttab + 4 * (size_t)t0m;
         const float4* cls = ctab + mh.coff[m];
         const int ncl = mh.coff[m + 1] - mh.coff[m];
+        const int* perm = mh.perm + t0m;
+        auto member = [&](int k) {  // this lane's triangle of cluster k, or nt
+          const int p = k * CL3 + lane;
+          return p < nt ? perm[p] : nt;
+        };
         // distance of the tile centre to the mesh: the least cluster upper
         // bound, then exact distances in the clusters that reach below it
         // (one wave per cluster, one lane per triangle)
@@ -621,7 +881,7 @@ __global__ __launch_bounds__(NT) void k_coupling3d(MemDev md, MeshDev mh, TileMa
         for (int k = wv; k < ncl; k += NT / 64) {
           const float4 cs = cls[k];
           if (sph_dist(pcr[0], pcr[1], pcr[2], cs) - cs.w > U) continue;
-          const int q = k * CL3 + lane;
+          const int q = member(k);
           if (q < nt) dl = fminf(dl, tri_d2f_vtx(pcr[0], pcr[1], pcr[2], tab[4 * q], tab[4 * q + 1], tab[4 * q + 2]));
         }
         const float dminf = sqrtf(block_minf<NT>(dl, s_redf));
@@ -635,7 +895,7 @@ __global__ __launch_bounds__(NT) void k_coupling3d(MemDev md, MeshDev mh, TileMa
           for (int k = wv; k < ncl; k += NT / 64) {
             const float4 cs = cls[k];
             if (sph_dist(pcr[0], pcr[1], pcr[2], cs) - cs.w > tlr) continue;
-            const int q = k * CL3 + lane;
+            const int q = member(k);
             if (q < nt &&
                 tri_d2f_vtx(pcr[0], pcr[1], pcr[2], tab[4 * q], tab[4 * q + 1], tab[4 * q + 2]) <= tl) {
               double w[3];
@@ -665,7 +925,7 @@ __global__ __launch_bounds__(NT) void k_coupling3d(MemDev md, MeshDev mh, TileMa
           for (int k = wv; k < ncl; k += NT / 64) {
             const float4 cs = cls[k];
             if (sph_dist(pcr[0], pcr[1], pcr[2], cs) - cs.w > cull) continue;
-            const int q = k * CL3 + lane;
+            const int q = member(k);
             bool in = false;
             if (q < nt) {
               const float4 sp = tab[4 * q + 3];
@@ -708,7 +968,7 @@ __global__ __launch_bounds__(NT) void k_coupling3d(MemDev md, MeshDev mh, TileMa
               const int c0 = c * C3_LIST, n0 = min(C3_LIST, nc - c0);
               for (int j = lt; j < n0; j += NT) {
                 const int* tv = mh.tri + 3 * (t0m + s_id[c0 + j]);
-                geo_store(s_g, j, md.X + 3 * tv[0], md.X + 3 * tv[1], md.X + 3 * tv[2], g.pc);
+                geo_store(s_g, j, tv, md.X + 3 * tv[0], md.X + 3 * tv[1], md.X + 3 * tv[2], g.pc);
               }
             };
             // 1. sub-tile centre distance over all candidates (the least
@@ -901,15 +1161,11 @@ __global__ __launch_bounds__(NT) void k_coupling3d(MemDev md, MeshDev mh, TileMa
                 stage(c);
                 __syncthreads();
                 if (!wfar) {
-                  const int c0 = c * C3_LIST, cn = wave_list(c);
+                  const int cn = wave_list(c);
                   if (v0 >= 0)
                     for (int k = 0; k < cn; k++) {
                       const int j = s_wl[wv][k];
-                      const int* uv = mh.tri + 3 * (t0m + s_id[c0 + j]);
-                      bool adj = false;
-#pragma unroll
-                      for (int a = 0; a < 3; a++) adj |= uv[a] == v0 || uv[a] == v1 || uv[a] == v2;
-                      if (!adj) o2m = fminf(o2m, geo_d2f(s_g, j, pn[0], pn[1], pn[2]));
+                      if (!geo_shares(s_g, j, v0, v1, v2)) o2m = fminf(o2m, geo_d2f(s_g, j, pn[0], pn[1], pn[2]));
                     }
                 }
               }
@@ -933,11 +1189,7 @@ __global__ __launch_bounds__(NT) void k_coupling3d(MemDev md, MeshDev mh, TileMa
                   const int v0 = tv[0], v1 = tv[1], v2 = tv[2];
                   for (int k = 0; k < cnt; k++) {
                     const int j = s_wl[wv][k];
-                    const int* uv = mh.tri + 3 * (t0m + s_id[j]);
-                    bool adj = false;
-#pragma unroll
-                    for (int a = 0; a < 3; a++) adj |= uv[a] == v0 || uv[a] == v1 || uv[a] == v2;
-                    if (!adj) o2 = fminf(o2, geo_d2f(s_g, j, pn[0], pn[1], pn[2]));
+                    if (!geo_shares(s_g, j, v0, v1, v2)) o2 = fminf(o2, geo_d2f(s_g, j, pn[0], pn[1], pn[2]));
                   }
                 }
                 const double lout = fmin((double)cwr - rn4 - 0.01, (double)cull - rn8 - 0.02);
@@ -948,122 +1200,264 @@ __global__ __launch_bounds__(NT) void k_coupling3d(MemDev md, MeshDev mh, TileMa
           }
         }
       }
-      if (cslot && !cached && valid) {
+      if (cslot && valid) {
         // FP32 distances are within 1e-5 relative of exact here: a margin of
-        // 1e-3 plus 1e-5 of the bound; stored with the drift so far added and
-        // rounded down, so the bound at a later step is the stored value less
-        // the drift then
+        // 1e-3 plus 1e-5 of the bound
         ca.ckey[cix] = keyw;
-        ca.clb[cix] = keyw >= 0 ? __double2float_rd(lbw - 1e-3 - 1e-5 * fabs(lbw) + drift) : 0.0f;
+        ca.clb[cix] = keyw >= 0 ? bound3(lbw, drift, image3(g.pp, xi, dims)) : 0.0f;
       }
-      double sd = 0.0;
-      bool band = false;
+      Band3 here;
       if (!decided && g.inbox && tb >= 0) {
         double w[3];
         tri_d2_id(md, mh, t0m + tb, g.pp, w);
-        const bool in = mesh_side(md, mh, t0m + tb, w, g.pp, o);
-        const double d = sqrt(d2b);
-        sd = in ? d : -d;
-        band = d <= ca.r_cut;
-        Itot += band ? 0.5 * (1.0 + tanh(sd / (2.0 * ca.alpha))) : (in ? 1.0 : 0.0);
+        Itot += node_profile3(md, mh, t0m + tb, w, g.pp, d2b, o, ca.alpha, ca.r_cut, here);
       }
-      if (slot < COUP3_KEEP) {
-        b_tri[slot][lt] = band ? t0m + tb : -1;
-        b_sd[slot][lt] = sd;
-      }
+#pragma unroll
+      for (int c = 0; c < COUP3_KEEP; c++)
+        if (c == slot) bd[c] = here;
       __syncthreads();  // candidate lists are rebuilt for the next membrane
     }
-    const long long node = valid ? ((long long)xi[2] * ca.ny + xi[1]) * ca.nx + xi[0] : 0;
-    if (valid) Ifield[node] = Itot;
+    if (valid) Ifield[nodeid] = Itot;
     if (ca.want_force) {
       if (kept > COUP3_KEEP && lt == 0) md.status[1] = 1;
-      bool anyband = false;
-      for (int k = 0; k < min(kept, COUP3_KEEP); k++) anyband |= b_tri[k][lt] >= 0;
-      // psi and the force pass only in waves that hold band nodes
-      double psi = 0.0;
-      const bool wband = __ballot(anyband) != 0ull;
-      if (valid && wband) {
-        using L = Lattice<19>;
-        psi = cur.rest(2, node);
-        // neighbour planes, rows and columns of the node, wrapped once
-        const long long pl = (long long)ca.ny * ca.nx;
-        const long long zlo = (xi[2] == 0 ? ca.nz - 1 : xi[2] - 1) * pl, zc = xi[2] * pl;
-        const long long zhi = (xi[2] == ca.nz - 1 ? 0 : xi[2] + 1) * pl;
-        const long long ylo = (long long)(xi[1] == 0 ? ca.ny - 1 : xi[1] - 1) * ca.nx;
-        const long long yhi = (long long)(xi[1] == ca.ny - 1 ? 0 : xi[1] + 1) * ca.nx;
-        const long long yc = (long long)xi[1] * ca.nx;
-        const int xlo = xi[0] == 0 ? ca.nx - 1 : xi[0] - 1, xhi = xi[0] == ca.nx - 1 ? 0 : xi[0] + 1;
-        const bool wylo = ca.wall_y && xi[1] == 0, wyhi = ca.wall_y && xi[1] == ca.ny - 1;
-        const bool wzlo = ca.wall_z && xi[2] == 0, wzhi = ca.wall_z && xi[2] == ca.nz - 1;
-        for (int i = 1; i < 19; i++) {
-          const int ex = L::cx[i], ey = L::cy[i], ez = L::cz[i];
-          const bool back = (ey > 0 ? wylo : (ey < 0 ? wyhi : false)) || (ez > 0 ? wzlo : (ez < 0 ? wzhi : false));
-          const long long sn = (ez > 0 ? zlo : (ez < 0 ? zhi : zc)) + (ey > 0 ? ylo : (ey < 0 ? yhi : yc)) +
-                               (ex > 0 ? xlo : (ex < 0 ? xhi : xi[0]));
-          psi += (double)cur.template load<R>(2, back ? L::opp[i] : i, back ? node : sn);
-        }
-      }
-      // an empty hash table (the previous tile flushed it before its last barrier)
-      for (int i = lt; i < COUP3_HASH; i += NT) {
-        s_hv[i] = -1;
-        s_ha[i][0] = s_ha[i][1] = s_ha[i][2] = 0;
-      }
-      __syncthreads();
-      int slot = 0;
-      for (int m = 0; wband && m < md.K && slot < COUP3_KEEP; m++) {
-        const TileGeo g = tile_geo(md.mbox + 8 * m, ct, xi, t0, dims, per, hd, reach, valid);
-        if (g.miss) continue;
-        const int my = slot++;
-        const int tg = b_tri[my][lt];
-        if (tg < 0) continue;
-        const double sd = b_sd[my][lt];
-        const double d = fabs(sd);
-        if (d == 0.0) continue;
-        double w[3];
-        tri_d2_id(md, mh, tg, g.pp, w);
-        const int* tv = mh.tri + 3 * tg;
-        double Qp[3] = {0, 0, 0};
-        for (int k = 0; k < 3; k++)
-          for (int a = 0; a < 3; a++) Qp[a] += w[k] * md.X[3 * tv[k] + a];
-        const double sg = sd > 0.0 ? 1.0 : -1.0;
-        const double ch = cosh(sd / (2.0 * ca.alpha));
-        const double wgt = ca.kappa_c / (4.0 * ca.alpha) * (psi - Itot) / (ch * ch);
-        for (int k = 0; k < 3; k++) {
-          const int v = tv[k];
-          long long fx[3];
-          for (int a = 0; a < 3; a++) fx[a] = to_fix(-sg * (g.pp[a] - Qp[a]) / d * wgt * w[k]);
-          // slot of marker v: linear probing from its hash
-          int h = (int)(((unsigned)v * 2654435761u) >> 23) & (COUP3_HASH - 1);
-          int found = -1;
-          for (int probe = 0; probe < COUP3_HASH; probe++) {
-            const int prev = atomicCAS(&s_hv[h], -1, v);
-            if (prev == -1 || prev == v) {
-              found = h;
-              break;
-            }
-            h = (h + 1) & (COUP3_HASH - 1);
-          }
-          if (found >= 0) {
-            for (int a = 0; a < 3; a++) atomicAdd((unsigned long long*)&s_ha[found][a], (unsigned long long)fx[a]);
-          } else {
-            long long* A = md.Facc + 3 * v;
-            for (int a = 0; a < 3; a++) atomicAdd((unsigned long long*)&A[a], (unsigned long long)fx[a]);
-          }
-        }
-      }
-      __syncthreads();
-      // one global atomic per marker and component (integer sums: the same
-      // totals in any order)
-      for (int i = lt; i < COUP3_HASH; i += NT) {
-        const int v = s_hv[i];
-        if (v >= 0) {
-          long long* A = md.Facc + 3 * v;
-          for (int a = 0; a < 3; a++)
-            if (s_ha[i][a] != 0) atomicAdd((unsigned long long*)&A[a], (unsigned long long)s_ha[i][a]);
-        }
-      }
+      tile_forces3<St, R, NT>(md, mh, ca, cur, s_f, bd, xi, valid, nodeid, Itot);
     }
     __syncthreads();
+  }
+}
+
+// an expired entry: its node, membrane and slot, and a squared distance known to
+// be reached (3e38: none)
+struct Renew3 {
+  int node, mem, slot;
+  float near;
+};
+
+// The tiles whose nodes all hold their entries: the profile and coupling forces
+// without a search.  A node's entry holds while the nearest triangle of the
+// one-ring of its kept triangle (FP32 screening, then FP64 for the near-ties,
+// lowest index on ties) is nearer than the bound less the drift since, or,
+// beyond the band, while the bound less the drift exceeds r_cut.
+//
+// The first pass (PASS 0) takes the active tiles.  A tile with a few expired
+// entries queues them for k_renew3d and itself for the second pass; a tile with
+// a node that has none, or with more expired ones, is left to the search.  In
+// the second pass every entry that had expired has been renewed in this step, so
+// the entries' triangles are the closest and no bound is asked (a node as near
+// to some other part of the mesh has none to show).
+//
+// What bounds it: chains of dependent loads (entry, ring, triangle, vertices)
+// and FP64 arithmetic, so it is kept apart from the search and from the
+// renewals: a renewal is a chain of 10 to 40 us for one wave, and in here every
+// wave of its tile would wait for it (1.33 ms for this kernel then, at the first
+// size below).  Per step, with k_renew3d between the passes and the search after
+// them, against a search of every tile in each step:
+//   256^3, two 5120-triangle capsules, some 7200 tiles: 0.73 + 0.29 + 0.48 +
+//     0.02 ms, before 1.86
+//   64^3, the same meshes: 131 + 47 + 134 + 8 us, before 2.47 ms
+template <class St, typename R, int NT, int PASS>
+__global__ __launch_bounds__(NT, 2) void k_coupling3d_kept(MemDev md, MeshDev mh, TileMap tm, Coup3Args ca,
+                                                           double* __restrict__ Ifield, St cur,
+                                                           int* __restrict__ left, int* __restrict__ again,
+                                                           Renew3* __restrict__ queue) {
+  static_assert(NT == 512, "one thread per node of an 8^3 tile");
+  __shared__ ForceTable3 s_f;
+  __shared__ int s_li;
+  const int ntl = tm.tstate[PASS == 0 ? 0 : 6];
+  const int* list = PASS == 0 ? tm.tlist : again;
+  const double reach = ca.r_cut + 1.0;
+  const double hd = 0.5 * TILE3 * 1.7320508075688772;
+  const int per[3] = {1, !ca.wall_y, !ca.wall_z};
+  const int dims[3] = {ca.nx, ca.ny, ca.nz};
+  const int lt = (int)threadIdx.x, lane = lt & 63, wv = lt >> 6;
+  const int off[3] = {(wv & 1) * 4 + (lane & 3), ((wv >> 1) & 1) * 4 + ((lane >> 2) & 3), (wv >> 2) * 4 + (lane >> 4)};
+  for (;;) {
+    // the previous tile ended with a barrier, so s_li is free to rewrite
+    if (lt == 0) s_li = atomicAdd(&tm.tstate[PASS == 0 ? 4 : 8], 1);
+    __syncthreads();
+    const int li = s_li;
+    if (li >= ntl) break;  // uniform over the workgroup
+    const int t = list[li];
+    const int tx = t % tm.ntx, ty = (t / tm.ntx) % tm.nty, tz = t / (tm.ntx * tm.nty);
+    const int t0[3] = {tx * TILE3, ty * TILE3, tz * TILE3};
+    const int xi[3] = {t0[0] + off[0], t0[1] + off[1], t0[2] + off[2]};
+    const bool valid = xi[0] < ca.nx && xi[1] < ca.ny && xi[2] < ca.nz;
+    const long long nodeid = valid ? ((long long)xi[2] * ca.ny + xi[1]) * ca.nx + xi[0] : 0;
+    // the node's entries of both slots, loaded before the membrane loop so that
+    // their latency overlaps the tile geometry
+    int kpre[COUP3_CACHE];
+    float lpre[COUP3_CACHE];
+#pragma unroll
+    for (int c = 0; c < COUP3_CACHE; c++) {
+      kpre[c] = ca.ckey[(long long)c * ca.N + nodeid];
+      lpre[c] = ca.clb[(long long)c * ca.N + nodeid];
+    }
+    const double ct[3] = {t0[0] + 0.5 * (TILE3 - 1), t0[1] + 0.5 * (TILE3 - 1), t0[2] + 0.5 * (TILE3 - 1)};
+    double Itot = 0.0;
+    int kept = 0;
+    bool search = false;
+    int expired = 0;
+    bool late[COUP3_CACHE] = {};  // this node's entry of the slot has expired
+    int lmem[COUP3_CACHE] = {};
+    float lnear[COUP3_CACHE] = {};
+    Band3 bd[COUP3_KEEP];
+    for (int m = 0; m < md.K; m++) {
+      const TileGeo g = tile_geo(md.mbox + 8 * m, ct, xi, t0, dims, per, hd, reach, valid);
+      if (g.miss) continue;  // uniform over the block
+      const int slot = kept++;
+      if (slot >= COUP3_CACHE || m >= 2048) {
+        search = true;
+        break;
+      }
+      const int t0m = mh.toff[m];
+      const double* bx = md.mbox + 8 * m;
+      const double o = bx[6], drift = bx[7];
+      const int key = slot == 0 ? kpre[0] : kpre[1];
+      const float klb = slot == 0 ? lpre[0] : lpre[1];
+      const bool in = valid && g.inbox;
+      const bool has = in && key >= 0 && (key >> C3_KEYB) == m;  // an entry of this membrane
+      const int image = in ? image3(g.pp, xi, dims) : 0;
+      double d2b = 1e300, w[3] = {0.0, 0.0, 0.0};
+      int tb = -1, side = -1;
+      bool ok = !in;
+      if (has) {
+        const int lw = __float_as_int(klb);
+        const double thr = (lw & 7) == image ? (double)__int_as_float(lw & ~7) - drift : -1.0;
+        const int q = key & ((1 << C3_KEYB) - 1);
+        if (q >= C3_OUT) {
+          ok = thr > ca.r_cut;
+          side = q == C3_IN ? 1 : 0;
+        } else {
+          auto exact = [&](int tq) {
+            double wq[3];
+            const double d2 = tri_d2_id(md, mh, tq, g.pp, wq);
+            if (d2 < d2b || (d2 == d2b && tq < tb)) {
+              d2b = d2;
+              tb = tq;
+              w[0] = wq[0];
+              w[1] = wq[1];
+              w[2] = wq[2];
+            }
+          };
+          const int* ring = mh.ring + C3_RING * (size_t)(t0m + q);
+          const int nr = ring[0];
+          int near[2] = {-1, -1}, n = 0;  // the nearest two in FP32, and how many to compare
+          bool all = nr <= 0;
+          if (nr > 0) {
+            const float px = (float)(g.pp[0] - 0.5 * (bx[0] + bx[3])), py = (float)(g.pp[1] - 0.5 * (bx[1] + bx[4])),
+                        pz = (float)(g.pp[2] - 0.5 * (bx[2] + bx[5]));
+            float f0 = 3.0e38f, f1 = 3.0e38f, f2 = 3.0e38f;
+#pragma unroll 3
+            for (int k = 0; k < C3_RING - 1; k++) {
+              const int id = ring[1 + k];  // past the count: the first one again
+              float d = geo_d2g(mh.geo + C3_GEOT * (size_t)id, px, py, pz);
+              if (k >= nr) d = 3.0e38f;
+              f2 = fminf(f2, fmaxf(d, f1));
+              if (d < f1) {
+                f1 = d;
+                near[1] = id;
+              }
+              if (f1 < f0) {
+                const float f = f0;
+                const int i = near[0];
+                f0 = f1;
+                near[0] = near[1];
+                f1 = f;
+                near[1] = i;
+              }
+            }
+            const float tol = f0 + geo_margin(f0, px, py, pz);
+            n = f1 <= tol ? 2 : 1;
+            all = f2 <= tol;
+          }
+          if (!all) {
+#pragma unroll 1
+            for (int k = 0; k < n; k++) exact(k ? near[1] : near[0]);
+          } else {
+            const int* tv = mh.tri + 3 * (t0m + q);
+#pragma unroll 1
+            for (int k = 0; k < 3; k++)
+#pragma unroll 1
+              for (int e = mh.vtoff[tv[k]]; e < mh.vtoff[tv[k] + 1]; e++) exact(mh.vt[e]);
+          }
+          ok = sqrt(d2b) < thr;
+        }
+      }
+      if (__syncthreads_or(in && !has)) {
+        search = true;
+        break;
+      }
+      const int late_now = PASS == 0 ? __syncthreads_count(!ok) : 0;
+      if (late_now) {
+        expired += late_now;
+#pragma unroll
+        for (int c = 0; c < COUP3_CACHE; c++)
+          if (c == slot) {
+            late[c] = !ok;
+            lmem[c] = m;
+            lnear[c] = d2b < 1e30 ? (float)d2b * 1.0001f + 0.01f : 3.0e38f;
+          }
+        continue;
+      }
+      if (expired) continue;
+      Band3 here;
+      if (in) Itot += side >= 0 ? (double)side : node_profile3(md, mh, tb, w, g.pp, d2b, o, ca.alpha, ca.r_cut, here);
+#pragma unroll
+      for (int c = 0; c < COUP3_KEEP; c++)
+        if (c == slot) bd[c] = here;
+    }
+    if (search || expired > COUP3_RENEW) {  // uniform over the workgroup
+      if (lt == 0) left[atomicAdd(&tm.tstate[3], 1)] = t;
+      __syncthreads();
+      continue;
+    }
+    if (expired) {
+      if (lt == 0) again[atomicAdd(&tm.tstate[6], 1)] = t;
+#pragma unroll
+      for (int c = 0; c < COUP3_CACHE; c++) {
+        const unsigned long long mk = __ballot(late[c]);
+        if (!mk) continue;
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&tm.tstate[7], __popcll(mk));
+        base = __shfl(base, 0, 64);
+        if (late[c])
+          queue[base + __popcll(mk & ((1ull << lane) - 1ull))] = Renew3{(int)nodeid, lmem[c], c, lnear[c]};
+      }
+      __syncthreads();
+      continue;
+    }
+    if (valid) Ifield[nodeid] = Itot;
+    if (ca.want_force) tile_forces3<St, R, NT>(md, mh, ca, cur, s_f, bd, xi, valid, nodeid, Itot);
+    __syncthreads();
+  }
+}
+
+// renews the queued entries, one wave each
+__global__ __launch_bounds__(256) void k_renew3d(MemDev md, MeshDev mh, const int* __restrict__ tstate, Coup3Args ca,
+                                                 const float4* __restrict__ ctab, const Renew3* __restrict__ queue) {
+  const int n = tstate[7];
+  const int waves = (int)(gridDim.x * blockDim.x) >> 6;
+  const int per[3] = {1, !ca.wall_y, !ca.wall_z};
+  const int dims[3] = {ca.nx, ca.ny, ca.nz};
+  for (int i = (int)(blockIdx.x * blockDim.x + threadIdx.x) >> 6; i < n; i += waves) {
+    const Renew3 r = queue[i];
+    const int xi[3] = {r.node % ca.nx, (r.node / ca.nx) % ca.ny, r.node / (ca.nx * ca.ny)};
+    const double* bx = md.mbox + 8 * r.mem;
+    double P[3];
+    for (int a = 0; a < 3; a++) P[a] = near_img((double)xi[a], 0.5 * (bx[a] + bx[3 + a]), dims[a], per[a]);
+    const int t0m = mh.toff[r.mem];
+    double d2, lb;
+    int t;
+    wave_closest3(md, mh, ctab + mh.coff[r.mem], mh.coff[r.mem + 1] - mh.coff[r.mem], t0m,
+                  mh.toff[r.mem + 1] - t0m, bx, P, r.near, d2, t, lb);
+    if ((threadIdx.x & 63) == 0) {
+      int key;
+      double bound;
+      entry3(md, mh, r.mem, t0m, t, d2, lb, P, bx[6], ca.r_cut, key, bound);
+      const long long c = (long long)r.slot * ca.N + r.node;
+      ca.ckey[c] = key;
+      ca.clb[c] = bound3(bound, bx[7], image3(P, xi, dims));
+    }
   }
 }
 

@@ -63,7 +63,7 @@ struct Layout {
   // 2D coupling cache: per node and cached membrane slot, key and bound
   size_t ckey, clb;
   // 3D: moment field and triangle meshes
-  size_t mom, tri, toff, edge, erest, eoff, emem, tadj, tedge, vtoff, vt, fn, vn, ttab, ctab, coff;
+  size_t mom, tri, toff, edge, erest, eoff, emem, tadj, tedge, ring, perm, geo, left, again, queue, vtoff, vt, fn, vn, ttab, ctab, coff;
   int maxCl;
   int maxT, maxE;
   size_t total;
@@ -155,6 +155,12 @@ Layout make_layout(const lbib_params* p) {
   L.emem = c.take((size_t)L.maxE * 4);
   L.tadj = c.take((size_t)L.maxT * 3 * 4);
   L.tedge = c.take((size_t)L.maxT * 3 * 4);
+  L.ring = c.take((size_t)L.maxT * C3_RING * 4);
+  L.perm = c.take((size_t)L.maxT * 4);
+  L.geo = c.take((size_t)L.maxT * C3_GEOT * 16);
+  L.left = c.take(d3 ? (size_t)L.ntiles * 4 : 0);
+  L.again = c.take(d3 ? (size_t)L.ntiles * 4 : 0);
+  L.queue = c.take(d3 ? (size_t)L.ntiles * COUP3_RENEW * sizeof(Renew3) : 0);
   L.vtoff = c.take(d3 ? (size_t)(M + 1) * 4 : 0);
   L.vt = c.take((size_t)L.maxT * 3 * 4);
   L.fn = c.take((size_t)L.maxT * 3 * 8);
@@ -296,6 +302,9 @@ struct lbib_sim {
     h.tadj = at<int>(L.tadj);
     h.vtoff = at<int>(L.vtoff);
     h.vt = at<int>(L.vt);
+    h.ring = at<int>(L.ring);
+    h.geo = at<float4>(L.geo);
+    h.perm = at<int>(L.perm);
     h.fn = at<double>(L.fn);
     h.vn = at<double>(L.vn);
     h.coff = at<int>(L.coff);
@@ -750,28 +759,38 @@ struct Engine3D final : lbib_sim {
     const int ncl = coff.back();
     hipLaunchKernelGGL(k_clusters3d, dim3((ncl * 64 + 255) / 256), dim3(256), 0, stream, md, mh,
                        (const float4*)at<float4>(L.ttab), at<float4>(L.ctab), ncl);
-    // resident workgroups only: they take the active tiles from a counter
-    const int grid = (int)std::min<long long>(std::max<long long>(L.ntiles, 1), coup3_slots());
-    hipLaunchKernelGGL((k_coupling3d<St, R, COUP3_THREADS>), dim3(grid), dim3(COUP3_THREADS), 0, stream,
-                       md, mh, tm, coup_args(want_force), (const float4*)at<float4>(L.ttab),
-                       (const float4*)at<float4>(L.ctab), at<double>(L.Ifield), store(cur));
+    // resident workgroups only: they take the tiles from a counter
+    const long long tiles = std::max<long long>(L.ntiles, 1);
+    const Coup3Args ca = coup_args(want_force);
+    const int* list = tm.tlist;
+    const int* nlist = tm.tstate;
+    if (ca.ckey) {
+      // the tiles whose nodes hold their entries, some after a few renewals;
+      // the others are left to the search
+      if (!kept_slots) {
+        kept_slots = resident_blocks((const void*)&k_coupling3d_kept<St, R, COUP3_THREADS, 0>, COUP3_THREADS);
+        renew_slots = resident_blocks((const void*)&k_renew3d, 256);
+      }
+      const dim3 kg((unsigned)std::min<long long>(tiles, kept_slots)), kb(COUP3_THREADS);
+      Renew3* queue = at<Renew3>(L.queue);
+      hipLaunchKernelGGL((k_coupling3d_kept<St, R, COUP3_THREADS, 0>), kg, kb, 0, stream, md, mh, tm, ca,
+                         at<double>(L.Ifield), store(cur), at<int>(L.left), at<int>(L.again), queue);
+      hipLaunchKernelGGL(k_renew3d, dim3((unsigned)std::min<long long>(tiles * COUP3_RENEW / 4, renew_slots)), dim3(256),
+                         0, stream, md, mh, (const int*)tm.tstate, ca, (const float4*)at<float4>(L.ctab),
+                         (const Renew3*)queue);
+      hipLaunchKernelGGL((k_coupling3d_kept<St, R, COUP3_THREADS, 1>), kg, kb, 0, stream, md, mh, tm, ca,
+                         at<double>(L.Ifield), store(cur), at<int>(L.left), at<int>(L.again), queue);
+      list = at<int>(L.left);
+      nlist = tm.tstate + 3;
+    }
+    if (!search_slots) search_slots = resident_blocks((const void*)&k_coupling3d<St, R, COUP3_THREADS>, COUP3_THREADS);
+    hipLaunchKernelGGL((k_coupling3d<St, R, COUP3_THREADS>), dim3((unsigned)std::min<long long>(tiles, search_slots)),
+                       dim3(COUP3_THREADS), 0, stream, md, mh, tm, ca, (const float4*)at<float4>(L.ttab),
+                       (const float4*)at<float4>(L.ctab), at<double>(L.Ifield), store(cur), list, nlist);
     return hipGetLastError() == hipSuccess ? LBIB_OK : LBIB_EHIP;
   }
-
-  // workgroups of the profile kernel resident at once (queried once)
-  int c3slots = 0;
-  int coup3_slots() {
-    if (c3slots > 0) return c3slots;
-    int per_cu = 0, ncu = 0, dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)&k_coupling3d<St, R, COUP3_THREADS>,
-                                                     COUP3_THREADS, 0) != hipSuccess ||
-        per_cu <= 0 || ncu <= 0)
-      return 1024;
-    c3slots = per_cu * ncu;
-    return c3slots;
-  }
+  // workgroups of the profile kernels resident at once (queried once)
+  int kept_slots = 0, renew_slots = 0, search_slots = 0;
 
   // planes per workgroup: with seg = 0, one resident round of workgroups
   int pick_seg() const {
@@ -1158,6 +1177,7 @@ struct MeshTopo {
   std::vector<int> tadj;   // 3 per triangle
   std::vector<int> vtoff;  // n + 1
   std::vector<int> vt;
+  std::vector<int> ring;   // C3_RING per triangle: count, then the triangles that share a vertex with it
 };
 
 int mesh_topology(int n, int nt, const int* tri, MeshTopo& mt) {
@@ -1198,7 +1218,50 @@ int mesh_topology(int n, int nt, const int* tri, MeshTopo& mt) {
   std::vector<int> fill(mt.vtoff.begin(), mt.vtoff.end() - 1);
   for (int t = 0; t < nt; t++)
     for (int k = 0; k < 3; k++) mt.vt[fill[tri[3 * t + k]]++] = t;
+  mt.ring.assign((size_t)C3_RING * nt, -1);
+  for (int t = 0; t < nt; t++) {
+    std::vector<int> near;
+    for (int k = 0; k < 3; k++) {
+      const int v = tri[3 * t + k];
+      near.insert(near.end(), mt.vt.begin() + mt.vtoff[v], mt.vt.begin() + mt.vtoff[v + 1]);
+    }
+    std::sort(near.begin(), near.end());
+    near.erase(std::unique(near.begin(), near.end()), near.end());
+    if (near.size() >= (size_t)C3_RING) continue;
+    int* r = mt.ring.data() + (size_t)C3_RING * t;
+    r[0] = (int)near.size();
+    for (int k = 1; k < C3_RING; k++) r[k] = near[k <= r[0] ? k - 1 : 0];
+  }
   return LBIB_OK;
+}
+
+// the triangles of a mesh in an order that keeps neighbours together: by the
+// Morton code of their centroids in the mesh's bounding box
+std::vector<int> mesh_order(int n, const double* X, int nt, const int* tri) {
+  double lo[3], hi[3];
+  for (int a = 0; a < 3; a++) {
+    lo[a] = hi[a] = X[a];
+    for (int v = 1; v < n; v++) {
+      lo[a] = std::min(lo[a], X[3 * (size_t)v + a]);
+      hi[a] = std::max(hi[a], X[3 * (size_t)v + a]);
+    }
+  }
+  std::vector<std::pair<unsigned, int>> key(nt);
+  for (int t = 0; t < nt; t++) {
+    unsigned code = 0;
+    for (int a = 0; a < 3; a++) {
+      double c = 0.0;
+      for (int k = 0; k < 3; k++) c += X[3 * (size_t)tri[3 * t + k] + a] / 3.0;
+      const double w = hi[a] - lo[a];
+      const unsigned q = w > 0.0 ? (unsigned)std::min(1023.0, std::max(0.0, 1024.0 * (c - lo[a]) / w)) : 0u;
+      for (int b = 0; b < 10; b++) code |= (q >> b & 1u) << (3 * b + a);
+    }
+    key[t] = {code, t};
+  }
+  std::sort(key.begin(), key.end());
+  std::vector<int> out(nt);
+  for (int t = 0; t < nt; t++) out[t] = key[t].second;
+  return out;
 }
 
 }  // namespace
@@ -1302,7 +1365,7 @@ int lbib_add_membrane(lbib_sim* s, int n, const double* X, int n_elems, const in
   const int off = s->M;
   hipStream_t st = s->stream;
   MeshTopo mt;
-  std::vector<int> tri_g, edge_g, tadj_g, tedge_g, vtoff_g, vt_g, emem;
+  std::vector<int> tri_g, edge_g, tadj_g, tedge_g, ring_g, perm, vtoff_g, vt_g, emem;
   std::vector<double> erest;
   if (s->D == 3) {
     int rc = mesh_topology(n, n_elems, conn, mt);
@@ -1314,6 +1377,10 @@ int lbib_add_membrane(lbib_sim* s, int n, const double* X, int n_elems, const in
     for (int q = 0; q < 3 * n_elems; q++) tri_g[q] = conn[q] + off;
     tadj_g.resize(mt.tadj.size());
     for (size_t q = 0; q < mt.tadj.size(); q++) tadj_g[q] = mt.tadj[q] + s->ntri;
+    perm = mesh_order(n, X3.data(), n_elems, conn);
+    ring_g = mt.ring;
+    for (size_t q = 0; q < ring_g.size(); q++)
+      if (q % C3_RING != 0 && ring_g[q] >= 0) ring_g[q] += s->ntri;
     edge_g.resize(mt.edge.size());
     erest.resize(ne);
     for (int e = 0; e < ne; e++) {
@@ -1363,6 +1430,8 @@ int lbib_add_membrane(lbib_sim* s, int n, const double* X, int n_elems, const in
     char* w = s->ws;
     HIPCHK(hipMemcpyAsync(w + s->L.tri + (size_t)s->ntri * 12, tri_g.data(), tri_g.size() * 4, hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(w + s->L.tadj + (size_t)s->ntri * 12, tadj_g.data(), tadj_g.size() * 4, hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(w + s->L.perm + (size_t)s->ntri * 4, perm.data(), perm.size() * 4, hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(w + s->L.ring + (size_t)s->ntri * C3_RING * 4, ring_g.data(), ring_g.size() * 4, hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(w + s->L.tedge + (size_t)s->ntri * 12, tedge_g.data(), tedge_g.size() * 4, hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(w + s->L.edge + (size_t)s->nedge * 16, edge_g.data(), edge_g.size() * 4, hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(w + s->L.erest + (size_t)s->nedge * 8, erest.data(), erest.size() * 8, hipMemcpyHostToDevice, st));
