@@ -68,8 +68,8 @@ struct TileMap {
   int* tflag;         // per tile: stamp of the last step it was active in
   int* tlist;         // active tiles of this step
   int* tstate;        // [0] active-tile count, [1] stamp of this step; 3D: [3] tiles left to
-                      // the search, [6] to the second pass, [7] entries to renew, and the
-                      // counters [2], [4], [8] their workgroups take tiles from; 2D: [4], [5]
+                      // the search, [7] nodes to renew, and the counters [2], [4] their
+                      // workgroups take tiles from; 2D: [4], [5]
                       // active-tile counts of a simulation of its own, by stamp parity
   int ntx, nty, ntz, tile;
 };

@@ -41,6 +41,7 @@ constexpr float COUP3_BEYOND = 1.0f;
 // searches in full and renews every entry (some 60 us of a CU, what about a
 // hundred renewals take there)
 constexpr int COUP3_RENEW = 96;
+static_assert(COUP3_KEEP == COUP3_CACHE, "a node with entries keeps its band data");
 constexpr int C3_RING = 16;         // entries of a triangle's row in the ring table
 constexpr int C3_KEYB = 20;         // key = membrane << 20 | triangle (or a beyond code)
 constexpr int C3_IN = 0xFFFFE, C3_OUT = 0xFFFFD;
@@ -691,6 +692,32 @@ struct ForceTable3 {
   long long f[COUP3_HASH][3];
 };
 
+// psi at a node, from the populations that stream to it
+template <class St, typename R>
+__device__ __forceinline__ double node_psi3(const Coup3Args& ca, const St& cur, const int* xi, long long node) {
+  using L = Lattice<19>;
+  double psi = cur.rest(2, node);
+  // wrapped once
+  const long long pl = (long long)ca.ny * ca.nx;
+  const long long zlo = (xi[2] == 0 ? ca.nz - 1 : xi[2] - 1) * pl, zc = xi[2] * pl;
+  const long long zhi = (xi[2] == ca.nz - 1 ? 0 : xi[2] + 1) * pl;
+  const long long ylo = (long long)(xi[1] == 0 ? ca.ny - 1 : xi[1] - 1) * ca.nx;
+  const long long yhi = (long long)(xi[1] == ca.ny - 1 ? 0 : xi[1] + 1) * ca.nx;
+  const long long yc = (long long)xi[1] * ca.nx;
+  const int xlo = xi[0] == 0 ? ca.nx - 1 : xi[0] - 1, xhi = xi[0] == ca.nx - 1 ? 0 : xi[0] + 1;
+  const bool wylo = ca.wall_y && xi[1] == 0, wyhi = ca.wall_y && xi[1] == ca.ny - 1;
+  const bool wzlo = ca.wall_z && xi[2] == 0, wzhi = ca.wall_z && xi[2] == ca.nz - 1;
+#pragma unroll
+  for (int i = 1; i < 19; i++) {
+    const int ex = L::cx[i], ey = L::cy[i], ez = L::cz[i];
+    const bool back = (ey > 0 ? wylo : (ey < 0 ? wyhi : false)) || (ez > 0 ? wzlo : (ez < 0 ? wzhi : false));
+    const long long sn = (ez > 0 ? zlo : (ez < 0 ? zhi : zc)) + (ey > 0 ? ylo : (ey < 0 ? yhi : yc)) +
+                         (ex > 0 ? xlo : (ex < 0 ? xhi : xi[0]));
+    psi += (double)cur.template pull<R>(2, i, back, back ? node : sn);
+  }
+  return psi;
+}
+
 // the coupling forces of one tile's band nodes on their markers (eq.
 // DiscreteCF); every thread of the workgroup calls it
 template <class St, typename R, int NT>
@@ -703,28 +730,7 @@ __device__ __forceinline__ void tile_forces3(const MemDev& md, const MeshDev& mh
   for (int k = 0; k < COUP3_KEEP; k++) anyband |= bd[k].tri >= 0;
   // psi only in waves that hold band nodes
   double psi = 0.0;
-  if (valid && __ballot(anyband) != 0ull) {
-    using L = Lattice<19>;
-    psi = cur.rest(2, node);
-    // neighbour planes, rows and columns of the node, wrapped once
-    const long long pl = (long long)ca.ny * ca.nx;
-    const long long zlo = (xi[2] == 0 ? ca.nz - 1 : xi[2] - 1) * pl, zc = xi[2] * pl;
-    const long long zhi = (xi[2] == ca.nz - 1 ? 0 : xi[2] + 1) * pl;
-    const long long ylo = (long long)(xi[1] == 0 ? ca.ny - 1 : xi[1] - 1) * ca.nx;
-    const long long yhi = (long long)(xi[1] == ca.ny - 1 ? 0 : xi[1] + 1) * ca.nx;
-    const long long yc = (long long)xi[1] * ca.nx;
-    const int xlo = xi[0] == 0 ? ca.nx - 1 : xi[0] - 1, xhi = xi[0] == ca.nx - 1 ? 0 : xi[0] + 1;
-    const bool wylo = ca.wall_y && xi[1] == 0, wyhi = ca.wall_y && xi[1] == ca.ny - 1;
-    const bool wzlo = ca.wall_z && xi[2] == 0, wzhi = ca.wall_z && xi[2] == ca.nz - 1;
-#pragma unroll
-    for (int i = 1; i < 19; i++) {
-      const int ex = L::cx[i], ey = L::cy[i], ez = L::cz[i];
-      const bool back = (ey > 0 ? wylo : (ey < 0 ? wyhi : false)) || (ez > 0 ? wzlo : (ez < 0 ? wzhi : false));
-      const long long sn = (ez > 0 ? zlo : (ez < 0 ? zhi : zc)) + (ey > 0 ? ylo : (ey < 0 ? yhi : yc)) +
-                           (ex > 0 ? xlo : (ex < 0 ? xhi : xi[0]));
-      psi += (double)cur.template pull<R>(2, i, back, back ? node : sn);
-    }
-  }
+  if (valid && __ballot(anyband) != 0ull) psi = node_psi3<St, R>(ca, cur, xi, node);
   for (int i = lt; i < COUP3_HASH; i += NT) {
     T.v[i] = -1;
     T.f[i][0] = T.f[i][1] = T.f[i][2] = 0;
@@ -1226,58 +1232,50 @@ __global__ __launch_bounds__(NT) void k_coupling3d(MemDev md, MeshDev mh, TileMa
   }
 }
 
-// an expired entry: its node, membrane and slot, and a squared distance known to
-// be reached (3e38: none)
+// a node with an expired entry: the membrane of each slot (-1: none within reach)
+// and a squared distance known to be reached (3e38: none)
 struct Renew3 {
-  int node, mem, slot;
-  float near;
+  int node, mem[COUP3_CACHE];
+  float near[COUP3_CACHE];
 };
 
-// The tiles whose nodes all hold their entries: the profile and coupling forces
-// without a search.  A node's entry holds while the nearest triangle of the
-// one-ring of its kept triangle (FP32 screening, then FP64 for the near-ties,
-// lowest index on ties) is nearer than the bound less the drift since, or,
-// beyond the band, while the bound less the drift exceeds r_cut.
-//
-// The first pass (PASS 0) takes the active tiles.  A tile with a few expired
-// entries queues them for k_renew3d and itself for the second pass; a tile with
-// a node that has none, or with more expired ones, is left to the search.  In
-// the second pass every entry that had expired has been renewed in this step, so
-// the entries' triangles are the closest and no bound is asked (a node as near
-// to some other part of the mesh has none to show).
+// The active tiles whose nodes all hold entries: the profile and coupling forces
+// without a search.  An entry is good while the nearest triangle of the one-ring
+// of its kept triangle (FP32 screening, then FP64 for the near-ties, lowest index
+// on ties) is nearer than the bound less the drift since, or, beyond the band,
+// while the bound less the drift exceeds r_cut.  A node with an expired entry is
+// queued for k_renew3d, which does the node's whole work; a tile with a node
+// that has no entry, or with too many to renew, is left to the search.
 //
 // What bounds it: chains of dependent loads (entry, ring, triangle, vertices)
-// and FP64 arithmetic, so it is kept apart from the search and from the
-// renewals: a renewal is a chain of 10 to 40 us for one wave, and in here every
-// wave of its tile would wait for it (1.33 ms for this kernel then, at the first
-// size below).  Per step, with k_renew3d between the passes and the search after
-// them, against a search of every tile in each step:
-//   256^3, two 5120-triangle capsules, some 7200 tiles: 0.73 + 0.29 + 0.48 +
-//     0.02 ms, before 1.86
-//   64^3, the same meshes: 131 + 47 + 134 + 8 us, before 2.47 ms
-template <class St, typename R, int NT, int PASS>
+// and FP64 arithmetic at two waves per SIMD, so it is kept apart from the search
+// and from the renewals: a renewal is a chain of 10 to 40 us for one wave, and in
+// here every wave of its tile would wait for it (1.33 ms for this kernel then, at
+// the first size below; a second pass over the tiles with renewed entries instead
+// of the node's whole work in k_renew3d took 0.48 ms there).  Per step, this
+// kernel, k_renew3d and the search, against a search of every tile:
+//   256^3, two 5120-triangle capsules, some 7200 tiles: 0.77 + 0.35 + 0.02 ms,
+//     before 1.86
+//   64^3, the same meshes: 166 + 106 + 8 us, before 2.47 ms
+template <class St, typename R, int NT>
 __global__ __launch_bounds__(NT, 2) void k_coupling3d_kept(MemDev md, MeshDev mh, TileMap tm, Coup3Args ca,
                                                            double* __restrict__ Ifield, St cur,
-                                                           int* __restrict__ left, int* __restrict__ again,
-                                                           Renew3* __restrict__ queue) {
+                                                           int* __restrict__ left, Renew3* __restrict__ queue) {
   static_assert(NT == 512, "one thread per node of an 8^3 tile");
   __shared__ ForceTable3 s_f;
-  __shared__ int s_li;
-  const int ntl = tm.tstate[PASS == 0 ? 0 : 6];
-  const int* list = PASS == 0 ? tm.tlist : again;
+  __shared__ int s_li, s_w[NT / 64];
+  const int ntl = tm.tstate[0];
   const double reach = ca.r_cut + 1.0;
   const double hd = 0.5 * TILE3 * 1.7320508075688772;
   const int per[3] = {1, !ca.wall_y, !ca.wall_z};
   const int dims[3] = {ca.nx, ca.ny, ca.nz};
   const int lt = (int)threadIdx.x, lane = lt & 63, wv = lt >> 6;
   const int off[3] = {(wv & 1) * 4 + (lane & 3), ((wv >> 1) & 1) * 4 + ((lane >> 2) & 3), (wv >> 2) * 4 + (lane >> 4)};
-  for (;;) {
-    // the previous tile ended with a barrier, so s_li is free to rewrite
-    if (lt == 0) s_li = atomicAdd(&tm.tstate[PASS == 0 ? 4 : 8], 1);
-    __syncthreads();
-    const int li = s_li;
-    if (li >= ntl) break;  // uniform over the workgroup
-    const int t = list[li];
+  int li = (int)blockIdx.x;
+  while (li < ntl) {  // uniform over the workgroup
+    // the tile after this one
+    if (lt == 0) s_li = (int)gridDim.x + atomicAdd(&tm.tstate[4], 1);
+    const int t = tm.tlist[li];
     const int tx = t % tm.ntx, ty = (t / tm.ntx) % tm.nty, tz = t / (tm.ntx * tm.nty);
     const int t0[3] = {tx * TILE3, ty * TILE3, tz * TILE3};
     const int xi[3] = {t0[0] + off[0], t0[1] + off[1], t0[2] + off[2]};
@@ -1295,11 +1293,10 @@ __global__ __launch_bounds__(NT, 2) void k_coupling3d_kept(MemDev md, MeshDev mh
     const double ct[3] = {t0[0] + 0.5 * (TILE3 - 1), t0[1] + 0.5 * (TILE3 - 1), t0[2] + 0.5 * (TILE3 - 1)};
     double Itot = 0.0;
     int kept = 0;
-    bool search = false;
-    int expired = 0;
-    bool late[COUP3_CACHE] = {};  // this node's entry of the slot has expired
-    int lmem[COUP3_CACHE] = {};
-    float lnear[COUP3_CACHE] = {};
+    bool search = false, late = false;  // no entry; an expired one
+    Renew3 rn;
+#pragma unroll
+    for (int c = 0; c < COUP3_CACHE; c++) rn.mem[c] = -1;
     Band3 bd[COUP3_KEEP];
     for (int m = 0; m < md.K; m++) {
       const TileGeo g = tile_geo(md.mbox + 8 * m, ct, xi, t0, dims, per, hd, reach, valid);
@@ -1383,80 +1380,108 @@ __global__ __launch_bounds__(NT, 2) void k_coupling3d_kept(MemDev md, MeshDev mh
           ok = sqrt(d2b) < thr;
         }
       }
-      if (__syncthreads_or(in && !has)) {
-        search = true;
-        break;
-      }
-      const int late_now = PASS == 0 ? __syncthreads_count(!ok) : 0;
-      if (late_now) {
-        expired += late_now;
+      search |= in && !has;
+      late |= !ok;
+      if (in) {
 #pragma unroll
         for (int c = 0; c < COUP3_CACHE; c++)
           if (c == slot) {
-            late[c] = !ok;
-            lmem[c] = m;
-            lnear[c] = d2b < 1e30 ? (float)d2b * 1.0001f + 0.01f : 3.0e38f;
+            rn.mem[c] = m;
+            rn.near[c] = d2b < 1e30 ? (float)d2b * 1.0001f + 0.01f : 3.0e38f;
           }
-        continue;
       }
-      if (expired) continue;
+      if (!in || late) continue;
       Band3 here;
-      if (in) Itot += side >= 0 ? (double)side : node_profile3(md, mh, tb, w, g.pp, d2b, o, ca.alpha, ca.r_cut, here);
+      Itot += side >= 0 ? (double)side : node_profile3(md, mh, tb, w, g.pp, d2b, o, ca.alpha, ca.r_cut, here);
 #pragma unroll
       for (int c = 0; c < COUP3_KEEP; c++)
         if (c == slot) bd[c] = here;
     }
-    if (search || expired > COUP3_RENEW) {  // uniform over the workgroup
-      if (lt == 0) left[atomicAdd(&tm.tstate[3], 1)] = t;
-      __syncthreads();
-      continue;
-    }
-    if (expired) {
-      if (lt == 0) again[atomicAdd(&tm.tstate[6], 1)] = t;
+    bool band = false;
 #pragma unroll
-      for (int c = 0; c < COUP3_CACHE; c++) {
-        const unsigned long long mk = __ballot(late[c]);
-        if (!mk) continue;
-        int base = 0;
-        if (lane == 0) base = atomicAdd(&tm.tstate[7], __popcll(mk));
-        base = __shfl(base, 0, 64);
-        if (late[c])
-          queue[base + __popcll(mk & ((1ull << lane) - 1ull))] = Renew3{(int)nodeid, lmem[c], c, lnear[c]};
-      }
-      __syncthreads();
-      continue;
+    for (int c = 0; c < COUP3_KEEP; c++) {
+      if (late) bd[c].tri = -1;
+      band |= bd[c].tri >= 0;
     }
-    if (valid) Ifield[nodeid] = Itot;
-    if (ca.want_force) tile_forces3<St, R, NT>(md, mh, ca, cur, s_f, bd, xi, valid, nodeid, Itot);
+    const unsigned long long lm = __ballot(late);
+    if (lane == 0) s_w[wv] = __popcll(lm);
+    if (__ballot(search) && lane == 0) s_w[wv] = COUP3_RENEW + 1;
+    if (__ballot(band) && lane == 0) s_w[wv] |= 1 << 16;
+    __syncthreads();
+    int sum = 0, any = 0;
+#pragma unroll
+    for (int k = 0; k < NT / 64; k++) {
+      sum += s_w[k] & 0xffff;
+      any |= s_w[k] >> 16;
+    }
+    li = s_li;
+    if (sum > COUP3_RENEW) {  // uniform over the workgroup
+      if (lt == 0) left[atomicAdd(&tm.tstate[3], 1)] = t;
+    } else {
+      if (lm) {
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&tm.tstate[7], __popcll(lm));
+        base = __shfl(base, 0, 64);
+        if (late) {
+          rn.node = (int)nodeid;
+          queue[base + __popcll(lm & ((1ull << lane) - 1ull))] = rn;
+        }
+      }
+      if (valid && !late) Ifield[nodeid] = Itot;
+      if (ca.want_force && any) tile_forces3<St, R, NT>(md, mh, ca, cur, s_f, bd, xi, valid, nodeid, Itot);
+    }
     __syncthreads();
   }
 }
 
-// renews the queued entries, one wave each
+// The nodes k_coupling3d_kept queued, one wave each: the closest triangles by a
+// search, their entries, the profile and the coupling force.
+template <class St, typename R>
 __global__ __launch_bounds__(256) void k_renew3d(MemDev md, MeshDev mh, const int* __restrict__ tstate, Coup3Args ca,
-                                                 const float4* __restrict__ ctab, const Renew3* __restrict__ queue) {
+                                                 const float4* __restrict__ ctab, const Renew3* __restrict__ queue,
+                                                 double* __restrict__ Ifield, St cur) {
   const int n = tstate[7];
-  const int waves = (int)(gridDim.x * blockDim.x) >> 6;
+  const int waves = (int)(gridDim.x * blockDim.x) >> 6, lane = (int)threadIdx.x & 63;
   const int per[3] = {1, !ca.wall_y, !ca.wall_z};
   const int dims[3] = {ca.nx, ca.ny, ca.nz};
   for (int i = (int)(blockIdx.x * blockDim.x + threadIdx.x) >> 6; i < n; i += waves) {
     const Renew3 r = queue[i];
     const int xi[3] = {r.node % ca.nx, (r.node / ca.nx) % ca.ny, r.node / (ca.nx * ca.ny)};
-    const double* bx = md.mbox + 8 * r.mem;
-    double P[3];
-    for (int a = 0; a < 3; a++) P[a] = near_img((double)xi[a], 0.5 * (bx[a] + bx[3 + a]), dims[a], per[a]);
-    const int t0m = mh.toff[r.mem];
-    double d2, lb;
-    int t;
-    wave_closest3(md, mh, ctab + mh.coff[r.mem], mh.coff[r.mem + 1] - mh.coff[r.mem], t0m,
-                  mh.toff[r.mem + 1] - t0m, bx, P, r.near, d2, t, lb);
-    if ((threadIdx.x & 63) == 0) {
-      int key;
-      double bound;
-      entry3(md, mh, r.mem, t0m, t, d2, lb, P, bx[6], ca.r_cut, key, bound);
-      const long long c = (long long)r.slot * ca.N + r.node;
-      ca.ckey[c] = key;
-      ca.clb[c] = bound3(bound, bx[7], image3(P, xi, dims));
+    const double psi = ca.want_force ? node_psi3<St, R>(ca, cur, xi, r.node) : 0.0;
+    Band3 bd[COUP3_CACHE];
+    double Itot = 0.0;
+#pragma unroll
+    for (int c = 0; c < COUP3_CACHE; c++) {
+      const int m = r.mem[c];
+      if (m < 0) continue;  // uniform over the wave
+      const double* bx = md.mbox + 8 * m;
+      double P[3];
+      for (int a = 0; a < 3; a++) P[a] = near_img((double)xi[a], 0.5 * (bx[a] + bx[3 + a]), dims[a], per[a]);
+      const int t0m = mh.toff[m];
+      double d2, lb, w[3];
+      int t;
+      wave_closest3(md, mh, ctab + mh.coff[m], mh.coff[m + 1] - mh.coff[m], t0m, mh.toff[m + 1] - t0m, bx, P, r.near[c],
+                    d2, t, lb);
+      d2 = tri_d2_id(md, mh, t0m + t, P, w);
+      Itot += node_profile3(md, mh, t0m + t, w, P, d2, bx[6], ca.alpha, ca.r_cut, bd[c]);
+      if (lane == 0) {
+        int key;
+        double bound;
+        entry3(md, mh, m, t0m, t, d2, lb, P, bx[6], ca.r_cut, key, bound);
+        const long long e = (long long)c * ca.N + r.node;
+        ca.ckey[e] = key;
+        ca.clb[e] = bound3(bound, bx[7], image3(P, xi, dims));
+      }
+    }
+    if (lane == 0) Ifield[r.node] = Itot;
+    if (!ca.want_force || lane >= 3) continue;
+    const double wgt = ca.kappa_c / (4.0 * ca.alpha) * (psi - Itot);
+    for (int c = 0; c < COUP3_KEEP; c++) {
+      if (bd[c].tri < 0) continue;
+      const double ww = lane == 0 ? bd[c].w0 : (lane == 1 ? bd[c].w1 : 1.0 - bd[c].w0 - bd[c].w1);
+      long long* A = md.Facc + 3 * mh.tri[3 * bd[c].tri + lane];
+      for (int a = 0; a < 3; a++)
+        atomicAdd((unsigned long long*)&A[a], (unsigned long long)to_fix(bd[c].g[a] * wgt * ww));
     }
   }
 }

@@ -63,7 +63,7 @@ struct Layout {
   // 2D coupling cache: per node and cached membrane slot, key and bound
   size_t ckey, clb;
   // 3D: moment field and triangle meshes
-  size_t mom, tri, toff, edge, erest, eoff, emem, tadj, tedge, ring, perm, geo, left, again, queue, vtoff, vt, fn, vn, ttab, ctab, coff;
+  size_t mom, tri, toff, edge, erest, eoff, emem, tadj, tedge, ring, perm, geo, left, queue, vtoff, vt, fn, vn, ttab, ctab, coff;
   int maxCl;
   int maxT, maxE;
   size_t total;
@@ -159,7 +159,6 @@ Layout make_layout(const lbib_params* p) {
   L.perm = c.take((size_t)L.maxT * 4);
   L.geo = c.take((size_t)L.maxT * C3_GEOT * 16);
   L.left = c.take(d3 ? (size_t)L.ntiles * 4 : 0);
-  L.again = c.take(d3 ? (size_t)L.ntiles * 4 : 0);
   L.queue = c.take(d3 ? (size_t)L.ntiles * COUP3_RENEW * sizeof(Renew3) : 0);
   L.vtoff = c.take(d3 ? (size_t)(M + 1) * 4 : 0);
   L.vt = c.take((size_t)L.maxT * 3 * 4);
@@ -768,18 +767,16 @@ struct Engine3D final : lbib_sim {
       // the tiles whose nodes hold their entries, some after a few renewals;
       // the others are left to the search
       if (!kept_slots) {
-        kept_slots = resident_blocks((const void*)&k_coupling3d_kept<St, R, COUP3_THREADS, 0>, COUP3_THREADS);
-        renew_slots = resident_blocks((const void*)&k_renew3d, 256);
+        kept_slots = resident_blocks((const void*)&k_coupling3d_kept<St, R, COUP3_THREADS>, COUP3_THREADS);
+        renew_slots = resident_blocks((const void*)&k_renew3d<St, R>, 256);
       }
-      const dim3 kg((unsigned)std::min<long long>(tiles, kept_slots)), kb(COUP3_THREADS);
       Renew3* queue = at<Renew3>(L.queue);
-      hipLaunchKernelGGL((k_coupling3d_kept<St, R, COUP3_THREADS, 0>), kg, kb, 0, stream, md, mh, tm, ca,
-                         at<double>(L.Ifield), store(cur), at<int>(L.left), at<int>(L.again), queue);
-      hipLaunchKernelGGL(k_renew3d, dim3((unsigned)std::min<long long>(tiles * COUP3_RENEW / 4, renew_slots)), dim3(256),
-                         0, stream, md, mh, (const int*)tm.tstate, ca, (const float4*)at<float4>(L.ctab),
-                         (const Renew3*)queue);
-      hipLaunchKernelGGL((k_coupling3d_kept<St, R, COUP3_THREADS, 1>), kg, kb, 0, stream, md, mh, tm, ca,
-                         at<double>(L.Ifield), store(cur), at<int>(L.left), at<int>(L.again), queue);
+      hipLaunchKernelGGL((k_coupling3d_kept<St, R, COUP3_THREADS>), dim3((unsigned)std::min<long long>(tiles, kept_slots)),
+                         dim3(COUP3_THREADS), 0, stream, md, mh, tm, ca, at<double>(L.Ifield), store(cur),
+                         at<int>(L.left), queue);
+      hipLaunchKernelGGL((k_renew3d<St, R>), dim3((unsigned)std::min<long long>(tiles * COUP3_RENEW / 4, renew_slots)),
+                         dim3(256), 0, stream, md, mh, (const int*)tm.tstate, ca, (const float4*)at<float4>(L.ctab),
+                         (const Renew3*)queue, at<double>(L.Ifield), store(cur));
       list = at<int>(L.left);
       nlist = tm.tstate + 3;
     }
