@@ -1731,12 +1731,13 @@ __global__ void k_interp3d(MemDev md, St cur, LBParams P, const double* __restri
       const bool wylo = P.wall_y && yw == 0, wyhi = P.wall_y && yw == P.ny - 1;
       const bool wzlo = P.wall_z && zw == 0, wzhi = P.wall_z && zw == P.nz - 1;
       double d = 0, j[3] = {0, 0, 0};
+#pragma unroll
       for (int i = 0; i < 19; i++) {
         const int ex = L::cx[i], ey = L::cy[i], ez = L::cz[i];
         const bool back = (ey > 0 ? wylo : (ey < 0 ? wyhi : false)) || (ez > 0 ? wzlo : (ez < 0 ? wzhi : false));
         const long long sn = (ez > 0 ? zlo : (ez < 0 ? zhi : zc)) + (ey > 0 ? ylo : (ey < 0 ? yhi : yc)) +
                              (ex > 0 ? xlo : (ex < 0 ? xhi : xw));
-        const double v = (double)cur.template load<R>(0, back ? L::opp[i] : i, back ? node : sn);
+        const double v = (double)cur.template pull<R>(0, i, back, back ? node : sn);
         d += v;
         j[0] += L::cx[i] * v;
         j[1] += L::cy[i] * v;

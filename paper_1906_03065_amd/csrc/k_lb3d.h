@@ -1,8 +1,9 @@
-// k_lb3d.h -- the lattice-Boltzmann step (Sec. 3.1) on D3Q19.
+// k_lb3d.h -- the lattice-Boltzmann step (Sec. 3.1) on D3Q19, for any
+// relaxation times and storage.
 //
 // Two kernels per step:
 //   k_mom3d   pull-streams every node and writes its moments drho, phi and
-//             psi (FP64) to a moment field (24 B per node);
+//             psi (the last two FP64) to a moment field;
 //   k_lb3d    a workgroup of 256 threads owns a TX x TY column of nodes
 //             (TX TY = 256; 16 x 16, 32 x 8 or 64 x 4) and marches along z.
 //             Per plane it stages the moments of the (TX+4) x (TY+4) region
@@ -24,8 +25,10 @@ namespace lb {
 
 constexpr int T3 = 32;  // default tile extent in x (y: 256 / T3)
 
+template <typename R>
 struct Moments3 {
-  double* d;     // drho = rho - 1
+  R* d;  // drho = rho - rho0
+  R *jx, *jy, *jz;
   double* phi;
   double* psi;
 };
@@ -58,10 +61,9 @@ __device__ __forceinline__ void pull19(const St& src, const LBParams& P, int x, 
     const long long yo = L::cy[i] > 0 ? ylo : (L::cy[i] < 0 ? yhi : yc);
     const int xo = L::cx[i] > 0 ? xlo : (L::cx[i] < 0 ? xhi : x);
     const long long node = back ? here : zo + yo + xo;
-    const int dir = back ? L::opp[i] : i;
-    pf[i] = src.template load<R>(0, dir, node);
-    pg[i] = src.template load<R>(1, dir, node);
-    ph[i] = src.template load<R>(2, dir, node);
+    pf[i] = src.template pull<R>(0, i, back, node);
+    pg[i] = src.template pull<R>(1, i, back, node);
+    ph[i] = src.template pull<R>(2, i, back, node);
   }
 }
 
@@ -91,7 +93,7 @@ __device__ __forceinline__ void moments19(const R* pf, const R* pg, const R* ph,
 }
 
 template <class St, typename R>
-__global__ __launch_bounds__(256) void k_mom3d(St src, LBParams P, Moments3 M) {
+__global__ __launch_bounds__(256) void k_mom3d(St src, LBParams P, Moments3<R> M) {
   const long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (n >= P.N) return;
   const int x = (int)(n % P.nx), y = (int)((n / P.nx) % P.ny), z = (int)(n / ((long long)P.nx * P.ny));
@@ -99,7 +101,7 @@ __global__ __launch_bounds__(256) void k_mom3d(St src, LBParams P, Moments3 M) {
   double g0, h0, d, jx, jy, jz, phi, psi;
   pull19(src, P, x, y, z, pf, pg, ph, g0, h0);
   moments19(pf, pg, ph, g0, h0, d, jx, jy, jz, phi, psi);
-  M.d[n] = d;
+  M.d[n] = (R)d;  // a sum in R
   M.phi[n] = phi;
   M.psi[n] = psi;
 }
@@ -166,7 +168,7 @@ __device__ __forceinline__ int tile3(const LBParams& P, int x, int y, int z) {
 
 // TX: tile extent in x (wider tiles read whole cache lines of each x row)
 template <class St, typename R, int TX = T3>
-__global__ __launch_bounds__(256, 2) void k_lb3d(St src, St dst, LBParams P, Moments3 M,
+__global__ __launch_bounds__(256, 2) void k_lb3d(St src, St dst, LBParams P, Moments3<R> M,
                                                  const int* __restrict__ tflag,
                                                  const int* __restrict__ tstate,
                                                  const double* __restrict__ Ifield,
@@ -257,7 +259,7 @@ __global__ __launch_bounds__(256, 2) void k_lb3d(St src, St dst, LBParams P, Mom
       const int xx = wrap(x0 - 2 + hx, P.nx);
       const int yy = halo_row(y0t - 2 + hy, P.ny, P.wall_y);
       const long long nd = ((long long)zr * P.ny + yy) * P.nx + xx;
-      mv[r][0] = M.d[nd];
+      mv[r][0] = (double)M.d[nd];
       mv[r][1] = M.phi[nd];
       mv[r][2] = M.psi[nd];
     }

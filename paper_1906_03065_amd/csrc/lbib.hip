@@ -26,6 +26,7 @@
 #include "k_ibm.h"
 #include "k_ibm3d.h"
 #include "k_lb.h"
+#include "k_eq3d.h"
 #include "k_lb3d.h"
 #include "k_misc.h"
 #include "store.h"
@@ -146,7 +147,7 @@ Layout make_layout(const lbib_params* p) {
   L.ckey = c.take((size_t)(D == 2 ? COUP_CACHE : COUP3_CACHE) * N * 4);
   L.clb = c.take((size_t)(D == 2 ? COUP_CACHE : COUP3_CACHE) * N * 4);
   const bool d3 = D == 3;
-  L.mom = c.take(d3 ? (size_t)N * 3 * 8 : 0);
+  L.mom = c.take(d3 ? (size_t)N * (2 * 8 + 4 * (p->storage == LBIB_FP64 ? 8 : 4)) : 0);
   L.tri = c.take((size_t)L.maxT * 3 * 4);
   L.toff = c.take(d3 ? (size_t)(K + 1) * 4 : 0);
   L.edge = c.take((size_t)L.maxE * 4 * 4);
@@ -439,6 +440,7 @@ int resident_blocks(const void* k, int threads) {
   return per_cu * ncu;
 }
 
+constexpr long long EQ3_WIDE = 1500000;  // nodes from which the D3Q19 tile is the wide one
 constexpr int MIN_SEG2 = 4;  // fewest rows of a D2Q9 segment chosen automatically
 
 template <class St, typename R>
@@ -716,12 +718,35 @@ struct Engine3D final : lbib_sim {
 
   void setup() override { fill_params(P, p, L, N, seg, fext, mw); }
 
-  Moments3 mom3() const {
-    Moments3 m;
-    m.d = at<double>(L.mom);
-    m.phi = m.d + N;
-    m.psi = m.d + 2 * N;
+  Moments3<R> mom3() const {
+    Moments3<R> m;
+    m.phi = at<double>(L.mom);
+    m.psi = m.phi + N;
+    m.d = reinterpret_cast<R*>(m.psi + N);
+    m.jx = m.d + N;
+    m.jy = m.jx + N;
+    m.jz = m.jy + N;
     return m;
+  }
+
+  // with tau = 1 throughout a collision leaves equilibria, and the steps inside
+  // a call can pass on Macro3 instead of populations (the 16-bit formats keep
+  // what a collision leaves of the populations' rounding) ...
+  bool relaxes() const {
+    return St::kQuantized || p.tau != 1.0 || p.tau_phi != 1.0 || p.tau_psi != 1.0;
+  }
+  // ... where its planes can be addressed (below 4 GiB per type)
+  using Mac = MacroStore3<R>;
+  bool macro_steps() const {
+    const long long rb = Mac::kR * N * (long long)sizeof(R);
+    return !relaxes() && rb < 0xfffffff0LL && 16 * N < 0xfffffff0LL &&
+           align_up((size_t)rb) + (size_t)(16 * N) <= L.pop_bytes;
+  }
+  Mac macro(int which) const {
+    char* base = ws + L.pops[which];
+    return Mac{reinterpret_cast<R*>(base),
+               reinterpret_cast<double*>(base + align_up((size_t)(Mac::kR * N) * sizeof(R))), (unsigned)N, P.rho0,
+               P.psh[0], P.psh[1]};
   }
 
   Coup3Args coup_args(int want_force) const {
@@ -743,7 +768,9 @@ struct Engine3D final : lbib_sim {
 
   // mesh geometry at X(t): boxes and the active-tile map, face normals,
   // orientation, vertex normals; then the profile and coupling forces
-  int coupling(int want_force) override {
+  int coupling(int want_force) override { return coupling_from(store(cur), want_force); }
+  template <class Src>
+  int coupling_from(Src src, int want_force) {
     if (K == 0) return LBIB_OK;
     MemDev md = memdev();
     MeshDev mh = meshdev();
@@ -761,33 +788,35 @@ struct Engine3D final : lbib_sim {
     // resident workgroups only: they take the tiles from a counter
     const long long tiles = std::max<long long>(L.ntiles, 1);
     const Coup3Args ca = coup_args(want_force);
+    int &kept_slots = slots3[Src::kMacro][0], &renew_slots = slots3[Src::kMacro][1], &search_slots = slots3[Src::kMacro][2];
     const int* list = tm.tlist;
     const int* nlist = tm.tstate;
     if (ca.ckey) {
       // the tiles whose nodes hold their entries, some after a few renewals;
       // the others are left to the search
       if (!kept_slots) {
-        kept_slots = resident_blocks((const void*)&k_coupling3d_kept<St, R, COUP3_THREADS>, COUP3_THREADS);
-        renew_slots = resident_blocks((const void*)&k_renew3d<St, R>, 256);
+        kept_slots = resident_blocks((const void*)&k_coupling3d_kept<Src, R, COUP3_THREADS>, COUP3_THREADS);
+        renew_slots = resident_blocks((const void*)&k_renew3d<Src, R>, 256);
       }
       Renew3* queue = at<Renew3>(L.queue);
-      hipLaunchKernelGGL((k_coupling3d_kept<St, R, COUP3_THREADS>), dim3((unsigned)std::min<long long>(tiles, kept_slots)),
-                         dim3(COUP3_THREADS), 0, stream, md, mh, tm, ca, at<double>(L.Ifield), store(cur),
+      hipLaunchKernelGGL((k_coupling3d_kept<Src, R, COUP3_THREADS>), dim3((unsigned)std::min<long long>(tiles, kept_slots)),
+                         dim3(COUP3_THREADS), 0, stream, md, mh, tm, ca, at<double>(L.Ifield), src,
                          at<int>(L.left), queue);
-      hipLaunchKernelGGL((k_renew3d<St, R>), dim3((unsigned)std::min<long long>(tiles * COUP3_RENEW / 4, renew_slots)),
+      hipLaunchKernelGGL((k_renew3d<Src, R>), dim3((unsigned)std::min<long long>(tiles * COUP3_RENEW / 4, renew_slots)),
                          dim3(256), 0, stream, md, mh, (const int*)tm.tstate, ca, (const float4*)at<float4>(L.ctab),
-                         (const Renew3*)queue, at<double>(L.Ifield), store(cur));
+                         (const Renew3*)queue, at<double>(L.Ifield), src);
       list = at<int>(L.left);
       nlist = tm.tstate + 3;
     }
-    if (!search_slots) search_slots = resident_blocks((const void*)&k_coupling3d<St, R, COUP3_THREADS>, COUP3_THREADS);
-    hipLaunchKernelGGL((k_coupling3d<St, R, COUP3_THREADS>), dim3((unsigned)std::min<long long>(tiles, search_slots)),
+    if (!search_slots) search_slots = resident_blocks((const void*)&k_coupling3d<Src, R, COUP3_THREADS>, COUP3_THREADS);
+    hipLaunchKernelGGL((k_coupling3d<Src, R, COUP3_THREADS>), dim3((unsigned)std::min<long long>(tiles, search_slots)),
                        dim3(COUP3_THREADS), 0, stream, md, mh, tm, ca, (const float4*)at<float4>(L.ttab),
-                       (const float4*)at<float4>(L.ctab), at<double>(L.Ifield), store(cur), list, nlist);
+                       (const float4*)at<float4>(L.ctab), at<double>(L.Ifield), src, list, nlist);
     return hipGetLastError() == hipSuccess ? LBIB_OK : LBIB_EHIP;
   }
-  // workgroups of the profile kernels resident at once (queried once)
-  int kept_slots = 0, renew_slots = 0, search_slots = 0;
+  // workgroups of the profile kernels resident at once (queried once per form
+  // of the state they read)
+  int slots3[2][3] = {};
 
   // planes per workgroup: with seg = 0, one resident round of workgroups
   int pick_seg() const {
@@ -804,11 +833,11 @@ struct Engine3D final : lbib_sim {
     return (int)std::max<long long>(std::min<long long>(4, p.nz), std::min<long long>(p.nz, planes));
   }
 
-  void launch_lb(St src, St dst) {
+  void launch_relax(St src, St dst) {
     P.seg = pick_seg();
     P.nseg = (p.nz + P.seg - 1) / P.seg;
     P.nxcd = nxcd > 0 ? nxcd : 8;
-    Moments3 m3 = mom3();
+    const Moments3<R> m3 = mom3();
     const int nb = (int)((N + 255) / 256);
     hipLaunchKernelGGL((k_mom3d<St, R>), dim3(nb), dim3(256), 0, stream, src, P, m3);
     dim3 grid(ntilex() * ntiley(), P.nseg);
@@ -826,23 +855,103 @@ struct Engine3D final : lbib_sim {
 #undef LB3_LAUNCH
   }
 
+  // rows per wave of k_mom3d_eq: some four rounds of waves, whose tails even out
+  int pick_rows(int nstrip) {
+    if (!mom_slots) mom_slots = resident_blocks((const void*)&k_mom3d_eq<R>, 64);
+    const long long rows = ((long long)p.ny * p.nz * nstrip + 4LL * mom_slots - 1) / (4LL * mom_slots);
+    return (int)std::min<long long>(p.ny, std::max<long long>(rows, 8));
+  }
+  int mom_slots = 0;
+
+  template <int TX, int TY, class Dst>
+  void launch_eq(Dst dst, const Moments3<R>& m3) {
+    constexpr int NT = (TX * (TY + 2) + 2 * (TY + 2) + 63) / 64 * 64;
+    const int ntx = (p.nx + TX - 1) / TX, nty = (p.ny + TY - 1) / TY;
+    int& slots = eq_slots[Dst::kMacro][TX == 64];
+    if (!slots) slots = resident_blocks((const void*)&k_lb3d_eq<Dst, R, TX, TY>, NT);
+    // planes per workgroup: the fewest plane iterations (5 of each workgroup's
+    // are its halo) over the rounds of resident workgroups
+    int best = p.nz;
+    if (seg > 0) {
+      best = std::min(seg, p.nz);
+    } else {
+      long long cost = LLONG_MAX;
+      for (int n = 1; n <= p.nz; n++) {
+        const int s = (p.nz + n - 1) / n;
+        const long long rounds = ((long long)ntx * nty * ((p.nz + s - 1) / s) + slots - 1) / slots;
+        if (rounds * (s + 5) < cost) {
+          cost = rounds * (s + 5);
+          best = s;
+        }
+      }
+    }
+    P.seg = best;
+    P.nseg = (p.nz + best - 1) / best;
+    hipLaunchKernelGGL((k_lb3d_eq<Dst, R, TX, TY>), dim3(ntx * nty, P.nseg), dim3(NT), 0, stream, dst, P, m3,
+                       (const int*)at<int>(L.tflag), (const int*)at<int>(L.tstate),
+                       (const double*)at<double>(L.Ifield), at<long long>(L.fib), at<double>(L.force), ntx);
+  }
+  int eq_slots[2][2] = {};
+
+  template <class Src, class Dst>
+  void launch_lb(Src src, Dst dst) {
+    if constexpr (St::kQuantized) {
+      launch_relax(src, dst);
+    } else {
+      if constexpr (!Src::kMacro && !Dst::kMacro)
+        if (relaxes()) {
+          launch_relax(src, dst);
+          return;
+        }
+      P.nxcd = nxcd > 0 ? nxcd : 8;
+      const Moments3<R> m3 = mom3();
+      if constexpr (Src::kMacro) {
+        const int nstrip = (p.nx + 61) / 62, width = (p.nx + nstrip - 1) / nstrip;
+        const int rows = pick_rows(nstrip), nseg = (p.ny + rows - 1) / rows;
+        hipLaunchKernelGGL((k_mom3d_eq<R>), dim3((unsigned)(p.nz * nstrip * nseg)), dim3(64), 0, stream, src, P, m3, width,
+                           nstrip, rows, nseg);
+        const long long zb = p.wall_z ? std::min(p.nz, 2) : 0, yb = p.wall_y ? std::min(p.ny, 2) : 0;
+        const long long nb = (zb * p.ny + (p.nz - zb) * yb) * p.nx;
+        if (nb > 0)
+          hipLaunchKernelGGL((k_mom3d_pull<Src, R, true>), dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, stream, src,
+                             P, m3, nb);
+      } else {
+        hipLaunchKernelGGL((k_mom3d_pull<Src, R, false>), dim3((unsigned)((N + 255) / 256)), dim3(256), 0, stream, src, P,
+                           m3, N);
+      }
+      if (N >= EQ3_WIDE)
+        launch_eq<64, 8>(dst, m3);
+      else
+        launch_eq<32, 4>(dst, m3);
+    }
+  }
+
+  // the first step of a call reads populations, the last one writes them;
+  // those between pass on Macro3 where they can (the population buffers hold it)
   int advance(int n) override {
     for (int k = 0; k < n; k++) {
-      const int rc = step();
+      int rc;
+      if constexpr (St::kQuantized) {
+        rc = step(store(cur), store(1 - cur));
+      } else {
+        const bool mac = n > 1 && macro_steps(), in = mac && k > 0, out = mac && k + 1 < n;
+        rc = in ? (out ? step(macro(cur), macro(1 - cur)) : step(macro(cur), store(1 - cur)))
+                : (out ? step(store(cur), macro(1 - cur)) : step(store(cur), store(1 - cur)));
+      }
       if (rc) return rc;
-      steps++;
     }
     return LBIB_OK;
   }
 
-  int step() {
+  template <class Src, class Dst>
+  int step(Src src, Dst dst) {
     MemDev md = memdev();
     MeshDev mh = meshdev();
     const int mb = (M + 255) / 256;
     const int mb64 = (int)((64LL * M + 255) / 256);  // one wave per marker
     if (K > 0) {
       hipEvent_t t0 = tbeg(1);
-      int rc = coupling(1);
+      int rc = coupling_from(src, 1);
       if (rc) return rc;
       tend(1, t0);
       t0 = tbeg(2);
@@ -856,15 +965,16 @@ struct Engine3D final : lbib_sim {
       tend(2, t0);
     }
     hipEvent_t t1 = tbeg(0);
-    launch_lb(store(cur), store(1 - cur));
+    launch_lb(src, dst);
     tend(0, t1);
     if (K > 0) {
       hipEvent_t t2 = tbeg(3);
-      hipLaunchKernelGGL((k_interp3d<St, R>), dim3(mb64), dim3(256), 0, stream, md, store(1 - cur), P,
+      hipLaunchKernelGGL((k_interp3d<Dst, R>), dim3(mb64), dim3(256), 0, stream, md, dst, P,
                          (const double*)at<double>(L.force));
       tend(3, t2);
     }
     cur = 1 - cur;
+    steps++;
     if (timing) {
       timed_steps++;
       if (ev_used > 4096) {
