@@ -263,7 +263,7 @@ __global__ __launch_bounds__(256) void k_mom3d_pull(Src src, LBParams P, Moments
 // neighbour planes come out of L2 (waves of consecutive planes run side by side
 // on one XCD).  No LDS, no barriers; the next row is fetched while one is summed.
 template <typename R>
-__global__ __launch_bounds__(64, sizeof(R) == 4 ? 4 : 2) void k_mom3d_eq(MacroStore3<R> src, LBParams P, Moments3<R> M, int width, int nstrip,
+__global__ __launch_bounds__(64, sizeof(R) == 4 ? 3 : 2) void k_mom3d_eq(MacroStore3<R> src, LBParams P, Moments3<R> M, int width, int nstrip,
                                                  int seg, int nseg) {
 #pragma clang fp contract(off)
   using L = Lattice<19>;
