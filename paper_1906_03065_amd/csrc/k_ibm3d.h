@@ -59,7 +59,7 @@ struct MeshDev {
   int* perm;      // triangles of each mesh (ids within it) in the order of the clusters
   int* ring;      // C3_RING per triangle: the triangles that share a vertex with it, itself
                   // among them (the count first; -1: more than fit, walk vt)
-  float4* geo;    // per step, C3_GEOT per triangle: G0 .. G5 below about the box centre
+  float4* geo;    // per step, C3_GEOT per triangle: G0 .. G2 below about the box centre
   double* fn;     // 3 per triangle: unit face normal (area vector direction)
   double* vn;     // 3 per vertex: angle-weighted normal
   int* coff;      // K+1 offsets of the 64-triangle clusters of each mesh
@@ -278,7 +278,13 @@ __device__ __forceinline__ void geo_write(const double* a, const double* b, cons
   put(4, make_float4((float)(V[0] * inn), (float)(V[1] * inn), (float)(V[2] * inn), __int_as_float(tv.y)));
   put(5, make_float4((float)(n[0] * rn), (float)(n[1] * rn), (float)(n[2] * rn), __int_as_float(tv.z)));
 }
-constexpr int C3_GEOT = 6;
+// What the kernels that gather single triangles read of one (mh.geo, one 64 B
+// line of float4): G0 to G2; they form the normal themselves, as their bound is
+// the addresses that the cache takes in per load, one or more per lane (six
+// float4 per triangle instead of three: MEASUREDGEO).  A triangle whose height
+// is below a twentieth of its longest edge has no good FP32 normal from its
+// edges: its G0.w is negative, and its distance is formed in FP64.
+constexpr int C3_GEOT = 4;
 
 // ---------------------------------------------------------------------------
 // Closest-triangle search.  Distances are first compared in FP32 (with
@@ -295,7 +301,7 @@ constexpr int C3_GEOT = 6;
 
 // per-step FP32 table: 4 float4 per triangle, relative to the box centre of
 // the triangle's membrane: the vertices, then (centroid, bounding radius)
-// (and, in mh.geo, the derived geometry that geo_store describes)
+// (and mh.geo)
 __global__ void k_tritable3d(MemDev md, MeshDev mh, float4* __restrict__ tab) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= mh.T) return;
@@ -315,7 +321,17 @@ __global__ void k_tritable3d(MemDev md, MeshDev mh, float4* __restrict__ tab) {
   }
   tab[4 * t + 3] = make_float4((float)(g[0] - c[0]), (float)(g[1] - c[1]), (float)(g[2] - c[2]),
                                (float)(r * (1.0 + 1e-6) + 1e-5));
-  geo_write(v[0], v[1], v[2], c, [&](int k, float4 q) { mh.geo[C3_GEOT * (size_t)t + k] = q; }, make_int3(0, 0, 0));
+  double e0[3], e1[3], e2[3], n[3];
+  sub3(v[1], v[0], e0);
+  sub3(v[2], v[0], e1);
+  sub3(e1, e0, e2);
+  cross3d(e0, e1, n);
+  const double l0 = dot3d(e0, e0), l1 = dot3d(e1, e1), l2 = dot3d(e2, e2), lm = fmax(l0, fmax(l1, l2));
+  const bool thin = !(dot3d(n, n) >= 2.5e-3 * lm * lm && l0 > 0.0 && l1 > 0.0 && l2 > 0.0);
+  float4* gq = mh.geo + C3_GEOT * (size_t)t;
+  gq[0] = make_float4((float)(v[0][0] - c[0]), (float)(v[0][1] - c[1]), (float)(v[0][2] - c[2]), thin ? -1.0f : (float)(1.0 / l0));
+  gq[1] = make_float4((float)e0[0], (float)e0[1], (float)e0[2], thin ? 0.0f : (float)(1.0 / l1));
+  gq[2] = make_float4((float)e1[0], (float)e1[1], (float)e1[2], thin ? 0.0f : (float)(1.0 / l2));
 }
 
 // bounding sphere of every cluster of 64 triangles of a mesh (mh.perm: near each
@@ -432,8 +448,18 @@ __device__ __forceinline__ float geo_d2(float4 g0, float4 g1, float4 g2, float4 
 __device__ __forceinline__ float geo_d2f(const float4 (*sg)[C3_LIST], int j, float px, float py, float pz) {
   return geo_d2(sg[0][j], sg[1][j], sg[2][j], sg[3][j], sg[4][j], sg[5][j], px, py, pz);
 }
-__device__ __forceinline__ float geo_d2g(const float4* g, float px, float py, float pz) {
-  return geo_d2(g[0], g[1], g[2], g[3], g[4], g[5], px, py, pz);
+// squared distance from G0 to G2 of a triangle that is not thin (G0.w > 0)
+__device__ __forceinline__ float geo_d2g(float4 g0, float4 g1, float4 g2, float px, float py, float pz) {
+  const float ax = px - g0.x, ay = py - g0.y, az = pz - g0.z;
+  const float nx = g1.y * g2.z - g1.z * g2.y, ny = g1.z * g2.x - g1.x * g2.z, nz = g1.x * g2.y - g1.y * g2.x;
+  const float nn = dot3f(nx, ny, nz, nx, ny, nz), h = dot3f(ax, ay, az, nx, ny, nz);
+  // q = n x (p - a): q.e1 and -q.e0 are |n|^2 times the barycentric coordinates
+  const float qx = ny * az - nz * ay, qy = nz * ax - nx * az, qz = nx * ay - ny * ax;
+  const float u = dot3f(qx, qy, qz, g2.x, g2.y, g2.z), v = -dot3f(qx, qy, qz, g1.x, g1.y, g1.z);
+  float d = seg_d2f(ax, ay, az, g1.x, g1.y, g1.z, g0.w);
+  d = fminf(d, seg_d2f(ax, ay, az, g2.x, g2.y, g2.z, g1.w));
+  d = fminf(d, seg_d2f(ax - g1.x, ay - g1.y, az - g1.z, g2.x - g1.x, g2.y - g1.y, g2.z - g1.z, g2.w));
+  return (u > 0.0f && v > 0.0f && u + v < nn) ? h * h * __builtin_amdgcn_rcpf(nn) : d;
 }
 
 __device__ __forceinline__ bool geo_shares(const float4 (*sg)[C3_LIST], int j, int v0, int v1, int v2) {
@@ -575,8 +601,13 @@ __device__ __forceinline__ void wave_closest3(const MemDev& md, const MeshDev& m
         todo &= todo - 1ull;
         const int pa = (c0 + ka) * CL3 + lane, pb = (c0 + kb) * CL3 + lane;
         const int qa = perm[min(pa, nt - 1)], qb = perm[min(pb, nt - 1)];
-        const float da = geo_d2g(geo + C3_GEOT * (size_t)qa, px, py, pz);
-        const float db = geo_d2g(geo + C3_GEOT * (size_t)qb, px, py, pz);
+        const float4* ga = geo + C3_GEOT * (size_t)qa;
+        const float4* gb = geo + C3_GEOT * (size_t)qb;
+        const float4 a0 = ga[0], a1 = ga[1], a2 = ga[2], b0 = gb[0], b1 = gb[1], b2 = gb[2];
+        float da = geo_d2g(a0, a1, a2, px, py, pz), db = geo_d2g(b0, b1, b2, px, py, pz);
+        double wt[3];
+        if (a0.w < 0.0f) da = (float)tri_d2_id(md, mh, t0m + qa, P, wt);
+        if (b0.w < 0.0f) db = (float)tri_d2_id(md, mh, t0m + qb, P, wt);
         if (pa < nt) visit(da, qa);
         if (kb != ka && pb < nt) visit(db, qb);
       }
@@ -1336,19 +1367,27 @@ __global__ __launch_bounds__(NT, 2) void k_coupling3d_kept(MemDev md, MeshDev mh
               w[2] = wq[2];
             }
           };
-          const int* ring = mh.ring + C3_RING * (size_t)(t0m + q);
-          const int nr = ring[0];
+          int4 row[C3_RING / 4];
+          const int4* ring = (const int4*)(mh.ring + C3_RING * (size_t)(t0m + q));
+#pragma unroll
+          for (int k = 0; k < C3_RING / 4; k++) row[k] = ring[k];
+          const int nr = row[0].x;
           int near[2] = {-1, -1}, n = 0;  // the nearest two in FP32, and how many to compare
           bool all = nr <= 0;
           if (nr > 0) {
             const float px = (float)(g.pp[0] - 0.5 * (bx[0] + bx[3])), py = (float)(g.pp[1] - 0.5 * (bx[1] + bx[4])),
                         pz = (float)(g.pp[2] - 0.5 * (bx[2] + bx[5]));
             float f0 = 3.0e38f, f1 = 3.0e38f, f2 = 3.0e38f;
-#pragma unroll 3
-            for (int k = 0; k < C3_RING - 1; k++) {
-              const int id = ring[1 + k];  // past the count: the first one again
-              float d = geo_d2g(mh.geo + C3_GEOT * (size_t)id, px, py, pz);
-              if (k >= nr) d = 3.0e38f;
+            bool thin = false;
+#pragma unroll
+            for (int k = 1; k < C3_RING; k++) {
+              // past the count: the first one again
+              const int id = (k & 3) == 0 ? row[k / 4].x : ((k & 3) == 1 ? row[k / 4].y : ((k & 3) == 2 ? row[k / 4].z : row[k / 4].w));
+              const float4* gq = mh.geo + C3_GEOT * (size_t)id;
+              const float4 g0 = gq[0], g1 = gq[1], g2 = gq[2];
+              thin |= g0.w < 0.0f;
+              float d = geo_d2g(g0, g1, g2, px, py, pz);
+              if (k > nr) d = 3.0e38f;
               f2 = fminf(f2, fmaxf(d, f1));
               if (d < f1) {
                 f1 = d;
@@ -1362,10 +1401,11 @@ __global__ __launch_bounds__(NT, 2) void k_coupling3d_kept(MemDev md, MeshDev mh
                 f1 = f;
                 near[1] = i;
               }
+              if (k % 5 == 0) __builtin_amdgcn_sched_barrier(0);  // five triangles in flight
             }
             const float tol = f0 + geo_margin(f0, px, py, pz);
             n = f1 <= tol ? 2 : 1;
-            all = f2 <= tol;
+            all = f2 <= tol || thin;
           }
           if (!all) {
 #pragma unroll 1
