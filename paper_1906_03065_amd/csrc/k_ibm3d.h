@@ -774,28 +774,39 @@ __device__ __forceinline__ void tile_forces3(const MemDev& md, const MeshDev& mh
     if (b.tri < 0) continue;
     const double ww[3] = {b.w0, b.w1, 1.0 - b.w0 - b.w1};
     const int* tv = mh.tri + 3 * b.tri;
+    int at[3];
+#pragma unroll
     for (int k = 0; k < 3; k++) {
       const int v = tv[k];
-      long long fx[3];
-#pragma unroll
-      for (int a = 0; a < 3; a++) fx[a] = to_fix(b.g[a] * wgt * ww[k]);
-      // slot of marker v: linear probing from its hash
+      // slot of marker v: linear probing from its hash (a plain read first:
+      // neighbouring nodes push the same markers, and equal addresses of an
+      // atomic are served one by one)
       int h = (int)(((unsigned)v * 2654435761u) >> 23) & (COUP3_HASH - 1);
-      int found = -1;
+      at[k] = -1;
       for (int probe = 0; probe < COUP3_HASH; probe++) {
-        const int prev = atomicCAS(&T.v[h], -1, v);
+        int prev = *(volatile int*)&T.v[h];
+        if (prev == -1) prev = atomicCAS(&T.v[h], -1, v);
         if (prev == -1 || prev == v) {
-          found = h;
+          at[k] = h;
           break;
         }
         h = (h + 1) & (COUP3_HASH - 1);
       }
-      if (found >= 0) {
-        for (int a = 0; a < 3; a++) atomicAdd((unsigned long long*)&T.f[found][a], (unsigned long long)fx[a]);
-      } else {
-        long long* A = md.Facc + 3 * v;
-        for (int a = 0; a < 3; a++) atomicAdd((unsigned long long*)&A[a], (unsigned long long)fx[a]);
-      }
+    }
+    // the nine sums in an order that starts elsewhere in each lane, for the
+    // same reason
+    int j = lt % 9;
+#pragma unroll 1
+    for (int n = 0; n < 9; n++) {
+      const int k = j / 3, a = j - 3 * k;
+      const double w = k == 0 ? ww[0] : (k == 1 ? ww[1] : ww[2]), ga = a == 0 ? b.g[0] : (a == 1 ? b.g[1] : b.g[2]);
+      const long long fx = to_fix(ga * wgt * w);
+      const int h = k == 0 ? at[0] : (k == 1 ? at[1] : at[2]);
+      if (h >= 0)
+        atomicAdd((unsigned long long*)&T.f[h][a], (unsigned long long)fx);
+      else
+        atomicAdd((unsigned long long*)&md.Facc[3 * tv[k] + a], (unsigned long long)fx);
+      j = j == 8 ? 0 : j + 1;
     }
   }
   __syncthreads();
@@ -1372,12 +1383,11 @@ __global__ __launch_bounds__(NT, 2) void k_coupling3d_kept(MemDev md, MeshDev mh
 #pragma unroll
           for (int k = 0; k < C3_RING / 4; k++) row[k] = ring[k];
           const int nr = row[0].x;
-          int near[2] = {-1, -1}, n = 0;  // the nearest two in FP32, and how many to compare
           bool all = nr <= 0;
           if (nr > 0) {
             const float px = (float)(g.pp[0] - 0.5 * (bx[0] + bx[3])), py = (float)(g.pp[1] - 0.5 * (bx[1] + bx[4])),
                         pz = (float)(g.pp[2] - 0.5 * (bx[2] + bx[5]));
-            float f0 = 3.0e38f, f1 = 3.0e38f, f2 = 3.0e38f;
+            float f[C3_RING], fm = 3.0e38f;
             bool thin = false;
 #pragma unroll
             for (int k = 1; k < C3_RING; k++) {
@@ -1386,31 +1396,25 @@ __global__ __launch_bounds__(NT, 2) void k_coupling3d_kept(MemDev md, MeshDev mh
               const float4* gq = mh.geo + C3_GEOT * (size_t)id;
               const float4 g0 = gq[0], g1 = gq[1], g2 = gq[2];
               thin |= g0.w < 0.0f;
-              float d = geo_d2g(g0, g1, g2, px, py, pz);
-              if (k > nr) d = 3.0e38f;
-              f2 = fminf(f2, fmaxf(d, f1));
-              if (d < f1) {
-                f1 = d;
-                near[1] = id;
-              }
-              if (f1 < f0) {
-                const float f = f0;
-                const int i = near[0];
-                f0 = f1;
-                near[0] = near[1];
-                f1 = f;
-                near[1] = i;
-              }
+              f[k] = k > nr ? 3.0e38f : geo_d2g(g0, g1, g2, px, py, pz);
+              fm = fminf(fm, f[k]);
               if (k % 5 == 0) __builtin_amdgcn_sched_barrier(0);  // five triangles in flight
             }
-            const float tol = f0 + geo_margin(f0, px, py, pz);
-            n = f1 <= tol ? 2 : 1;
-            all = f2 <= tol || thin;
-          }
-          if (!all) {
+            // those within the margin of the least (at a vertex, all around it)
+            const float tol = fm + geo_margin(fm, px, py, pz);
+            unsigned ties = 0;
+#pragma unroll
+            for (int k = 1; k < C3_RING; k++) ties |= (f[k] <= tol ? 1u : 0u) << k;
+            all = thin;
+            if (thin) ties = 0;
 #pragma unroll 1
-            for (int k = 0; k < n; k++) exact(k ? near[1] : near[0]);
-          } else {
+            while (ties) {
+              const int k = __ffs((int)ties) - 1;
+              ties &= ties - 1u;
+              exact(((const int*)ring)[k]);
+            }
+          }
+          if (all) {
             const int* tv = mh.tri + 3 * (t0m + q);
 #pragma unroll 1
             for (int k = 0; k < 3; k++)
