@@ -519,9 +519,24 @@ __device__ __forceinline__ void coupling2d_tile(const MemDev& md, const TileMap&
         lpre[c] = lp[e];
       }
     }
-    R hmov[8];
-    const double hrest = cur.rest(2, cnode);
-    {
+    // (from Macro2 a wave takes in the 10 x 10 nodes its populations come from
+    // once, 8 loads per lane; pulled one by one they were 40, and half of the
+    // kernel: MEASUREDPSI)
+    R hmov[8], mh[2][3];
+    double hrest = 0.0, mpsi[2];
+    if constexpr (St::kMacro) {
+#pragma unroll
+      for (int r = 0; r < 2; r++) {
+        const int q = min(lane + 64 * r, 99);
+        const int hx = wrap(x - (lane & 7) - 1 + q % 10, ca.nx), hy = y - (lane >> 3) - 1 + q / 10;
+        const unsigned hn = (unsigned)((ca.wall_y ? min(max(hy, 0), ca.ny - 1) : wrap(hy, ca.ny)) * ca.nx + hx);
+        mh[r][0] = cur.get(6, hn);
+        mh[r][1] = cur.get(3, hn);
+        mh[r][2] = cur.get(4, hn);
+        mpsi[r] = cur.getd(1, hn);
+      }
+    } else {
+      hrest = cur.rest(2, cnode);
       using L = Lattice<9>;
       // neighbour rows and columns of (xc, yc), wrapped once
       const long long rlo = (long long)(yc == 0 ? ca.ny - 1 : yc - 1) * ca.nx;
@@ -706,39 +721,41 @@ __device__ __forceinline__ void coupling2d_tile(const MemDev& md, const TileMap&
               ok = thr > ca.r_cut;
               side = sk == 0xFFFE ? 1 : 0;
             } else {
-              // the kept segment and COUP_WIN on each side (lowest index on
-              // equal distances, whatever the order), walked along the ring;
-              // each vertex is loaded two segments before it is needed, so
-              // the loads of three vertices are in flight at once
-              constexpr int NW = 2 * COUP_WIN + 2;  // vertices of the window
-              auto nxt = [&](int v) { return (v + 1 == n) ? 0 : v + 1; };
-              int q = (sk - COUP_WIN) % n;
-              if (q < 0) q += n;
-              int q1 = nxt(q), q2 = nxt(q1);
-              double ax = X[3 * q], ay = X[3 * q + 1];
-              double b1x = X[3 * q1], b1y = X[3 * q1 + 1];
-              double b2x = X[3 * q2], b2y = X[3 * q2 + 1];
+              // the kept segment and COUP_WIN on each side: screened in FP32
+              // (with the margin of the renewals below), the near-ties, one or
+              // two as a rule, compared in FP64 (lowest index on equal
+              // distances).  All 17 in FP64, a division each, were most of
+              // this kernel's arithmetic: MEASUREDWIN
+              constexpr int NW = 2 * COUP_WIN + 1;  // segments of the window
+              const float4* stab = md.stab + b;
+              const float* sinv = md.sinv + b;
+              const float fcx = (float)(px - cx), fcy = (float)(py - cy);
+              int q0 = (sk - COUP_WIN) % n;
+              if (q0 < 0) q0 += n;
+              float f[NW], bf = 3.0e38f;
+              int q = q0;
 #pragma unroll
-              for (int k = 0; k + 1 < NW; k++) {
-                // vertex k + 3 (the last ones load their predecessor again)
-                const int q3 = k + 3 < NW ? nxt(q2) : q2;
-                const double b3x = X[3 * q3], b3y = X[3 * q3 + 1];
+              for (int k = 0; k < NW; k++) {
+                f[k] = seg_d2f(fcx, fcy, stab[q], sinv[q]);
+                bf = fminf(bf, f[k]);
+                q = (q + 1 == n) ? 0 : q + 1;
+              }
+              const float tol = bf + (2e-3f + 2e-5f * bf);
+              unsigned ties = 0;
+#pragma unroll
+              for (int k = 0; k < NW; k++) ties |= (f[k] > tol ? 0u : 1u) << k;
+#pragma unroll 1
+              while (ties) {
+                q = (q0 + __ffs((int)ties) - 1) % n;
+                ties &= ties - 1u;
+                const int q1 = (q + 1 == n) ? 0 : q + 1;
                 double tt;
-                const double d2 = seg_d2(px, py, ax, ay, b1x, b1y, tt);
+                const double d2 = seg_d2(px, py, X[3 * q], X[3 * q + 1], X[3 * q1], X[3 * q1 + 1], tt);
                 if (d2 < d2b || (d2 == d2b && q < sb)) {
                   d2b = d2;
                   sb = q;
                   tb = tt;
                 }
-                q = q1;
-                q1 = q2;
-                q2 = q3;
-                ax = b1x;
-                ay = b1y;
-                b1x = b2x;
-                b1y = b2y;
-                b2x = b3x;
-                b2y = b3y;
               }
               ok = sqrt(d2b) < thr;
             }
@@ -1066,7 +1083,44 @@ __device__ __forceinline__ void coupling2d_tile(const MemDev& md, const TileMap&
       for (int slot = 0; slot < nk; slot++) anyband |= b_seg[slot][threadIdx.x] >= 0;
       // psi only where a node of the wave is in a band
       double psi = 0.0;
-      if (valid && __ballot(anyband)) {
+      if (__ballot(anyband)) {
+        if constexpr (St::kMacro) {
+          // the end points of the candidates are read no more: a wave's share
+          // of their LDS takes its nodes' psi and, half at a time (each with
+          // its opposites), their moving populations h_i
+          using L = Lattice<9>;
+          constexpr int SHARE = sizeof(s_end) / (NT / 64);
+          static_assert(100 * 8 + 400 * sizeof(R) <= SHARE, "a wave's share");
+          double* sp = reinterpret_cast<double*>(reinterpret_cast<char*>(s_end) + wv * SHARE);
+          R* sh = reinterpret_cast<R*>(sp + 100);
+          R mv[2][9], ph[9];
+#pragma unroll
+          for (int r = 0; r < 2; r++) {
+            eq9_g((R)mpsi[r], mh[r][0], mh[r][1], mh[r][2], mv[r]);
+            if (lane + 64 * r < 100) sp[lane + 64 * r] = mpsi[r];
+          }
+          const int q = ((lane >> 3) + 1) * 10 + (lane & 7) + 1;
+          const bool wlo = ca.wall_y && yc == 0, whi = ca.wall_y && yc == ca.ny - 1;
+#pragma unroll
+          for (int half = 1; half < 9; half += 4) {
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int r = 0; r < 2; r++)
+              if (lane + 64 * r < 100)
+#pragma unroll
+                for (int i = half; i < half + 4; i++) sh[(i - half) * 100 + lane + 64 * r] = mv[r][i];
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int i = half; i < half + 4; i++) {
+              ph[i] = sh[(i - half) * 100 + q];
+              const bool back = L::cy[i] > 0 ? wlo : (L::cy[i] < 0 ? whi : false);
+              hmov[i - 1] = sh[back ? (L::opp[i] - half) * 100 + q : (i - half) * 100 + q - 10 * L::cy[i] - L::cx[i]];
+            }
+          }
+          hrest = eq9_rest(sp[q], ph);
+        }
         psi = hrest;
 #pragma unroll
         for (int i = 0; i < 8; i++) psi += (double)hmov[i];
