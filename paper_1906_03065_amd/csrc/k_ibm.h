@@ -90,6 +90,25 @@ __device__ double block_sum(double v, double* sh) {
   return t;
 }
 
+// block_sum of eight values at once, thread k of the first eight storing the
+// k-th to out (each in the order of block_sum); sh: 8 NT / 64 values
+template <int NT>
+__device__ void block_sum8(double (&v)[8], double* sh, double* out) {
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int k = 0; k < 8; k++) v[k] += __shfl_down(v[k], o, 64);
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  if (lane == 0)
+#pragma unroll
+    for (int k = 0; k < 8; k++) sh[8 * wv + k] = v[k];
+  __syncthreads();
+  if (threadIdx.x < 8) {
+    double t = 0;
+    for (int i = 0; i < NT / 64; i++) t += sh[8 * i + threadIdx.x];
+    out[threadIdx.x] = t;
+  }
+}
+
 template <int NT>
 __device__ double block_min(double v, double* sh) {
   for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_down(v, o, 64));

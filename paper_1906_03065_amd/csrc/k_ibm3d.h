@@ -1903,7 +1903,7 @@ __global__ __launch_bounds__(NT) void k_energy_nodes3d(LBParams P, const double*
                                                        const double* __restrict__ Ifield,
                                                        double* __restrict__ part) {
   using L = Lattice<19>;
-  __shared__ double sh[NT / 64];
+  __shared__ double sh[8 * (NT / 64)];
   const long long n = (long long)blockIdx.x * NT + threadIdx.x;
   double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   if (n < P.N) {
@@ -1938,10 +1938,7 @@ __global__ __launch_bounds__(NT) void k_energy_nodes3d(LBParams P, const double*
       v[7] = rho * log(rho) / 3.0;
     }
   }
-  for (int k = 0; k < 8; k++) {
-    const double s = block_sum<NT>(v[k], sh);
-    if (threadIdx.x == 0) part[(long long)blockIdx.x * 8 + k] = s;
-  }
+  block_sum8<NT>(v, sh, part + (long long)blockIdx.x * 8);
 }
 
 }  // namespace lb

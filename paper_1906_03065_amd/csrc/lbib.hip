@@ -141,7 +141,7 @@ Layout make_layout(const lbib_params* p) {
   L.law = c.take((size_t)K * 4);
   L.mbox = c.take((size_t)K * 8 * 8);
   L.status = c.take(64);
-  L.memE = c.take(64);
+  L.memE = c.take(128);
   L.stab = c.take(D == 2 ? (size_t)M * 16 : 0);
   L.sinv = c.take(D == 2 ? (size_t)M * 4 : 0);
   L.ckey = c.take((size_t)(D == 2 ? COUP_CACHE : COUP3_CACHE) * N * 4);
@@ -1787,9 +1787,28 @@ int lbib_energy(lbib_sim* s, lbib_energies* out) {
   rc = s->energy_nodes(part, &nblk);
   if (rc) return rc;
   double* sums = s->at<double>(s->L.memE);
-  hipLaunchKernelGGL(k_sum_rows<256>, dim3(1), dim3(256), 0, s->stream, (const double*)part, nblk, 8, sums);
-  double host[8];
-  HIPCHK(hipMemcpyAsync(host, sums, 64, hipMemcpyDeviceToHost, s->stream));
+  // rows of w values to w sums; many rows in two levels, the first one's
+  // sums in the moment readout's place (read no more)
+  auto sum_rows = [&](const double* in, long long rows, int w, double* out) {
+    constexpr long long CHUNK = 4096;
+    const long long g = (rows + CHUNK - 1) / CHUNK;
+    if (g > 1) {
+      hipLaunchKernelGGL(k_sum_rows<1024>, dim3((unsigned)g), dim3(1024), 0, s->stream, in, rows, w, CHUNK, stage);
+      in = stage;
+      rows = g;
+    }
+    hipLaunchKernelGGL(k_sum_rows<1024>, dim3(1), dim3(1024), 0, s->stream, in, rows, w, rows, out);
+  };
+  sum_rows(part, nblk, 8, sums);
+  if (s->K > 0) {
+    double* me = part + ((s->N + 255) / 256 + 1) * 8;
+    long long rows = 0;
+    rc = s->mem_energy(me, &rows);
+    if (rc) return rc;
+    sum_rows(me, rows, 2, sums + 8);
+  }
+  double host[10] = {};
+  HIPCHK(hipMemcpyAsync(host, sums, s->K > 0 ? 80 : 64, hipMemcpyDeviceToHost, s->stream));
   HIPCHK(hipStreamSynchronize(s->stream));
   for (int k = 0; k < 3; k++) out->mass[k] = host[k];
   out->F_bulk = host[3];
@@ -1797,20 +1816,8 @@ int lbib_energy(lbib_sim* s, lbib_energies* out) {
   out->E_c = host[5];
   out->E_kin = host[6];
   out->p_ideal = host[7];
-  out->E_s = out->E_b = 0.0;
-  if (s->K > 0) {
-    double* me = part + ((s->N + 255) / 256 + 1) * 8;
-    long long rows = 0;
-    rc = s->mem_energy(me, &rows);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_sum_rows<256>, dim3(1), dim3(256), 0, s->stream, (const double*)me, rows, 2,
-                       sums);
-    double h2[2];
-    HIPCHK(hipMemcpyAsync(h2, sums, 16, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipStreamSynchronize(s->stream));
-    out->E_s = h2[0];
-    out->E_b = h2[1];
-  }
+  out->E_s = host[8];
+  out->E_b = host[9];
   return LBIB_OK;
 }
 
