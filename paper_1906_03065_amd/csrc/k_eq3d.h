@@ -14,7 +14,8 @@
 // bits alone.
 //
 // 256^3 with two capsules, per step: 2245 + 843 us with populations between all
-// steps; MEASURED3D
+// steps; now 620 (k_mom3d_eq) + 599 (k_lb3d_eq), in a call's first step 870 + 599,
+// in its last 620 + 1316.  64^3: 63 + 12 before, 21 + 25 now.
 #pragma once
 #include "common.h"
 #include "k_lb.h"
@@ -258,21 +259,31 @@ __global__ __launch_bounds__(256) void k_mom3d_pull(Src src, LBParams P, Moments
 // below and above send, moves them one lane in x, and adds them to the three
 // rows that receive them.
 //
-// What bounds it: VALU issue (some 500 operations per node, each population
-// formed once) against 84 B per node from and to memory; the rows of the
-// neighbour planes come out of L2 (waves of consecutive planes run side by side
-// on one XCD).  No LDS, no barriers; the next row is fetched while one is summed.
+// What bounds it: VALU issue (some 480 operations per node, each population
+// formed once; half of the issue slots at 256^3, with five strips of 52 in 64
+// lanes) and memory (84 B per node if every plane were read once).  The next row
+// is fetched while one is summed.  The rows of the neighbour planes come out of a
+// cache as long as the waves of neighbouring planes keep to the same row: a
+// workgroup is four waves of consecutive planes with a barrier per row.  At 256^3
+// one wave per workgroup reads 2.8 GB and takes 656 us, four 1.9 GB and 620 us,
+// six 1.7 GB and 842 us (they wait for each other, and 12 waves fit a CU).
+// Registers: 144, three waves per SIMD; held to 128 for four, 12 of them spill
+// and it takes 1152 us.
+constexpr int MOM3_WAVES = 4;
 template <typename R>
-__global__ __launch_bounds__(64, sizeof(R) == 4 ? 3 : 2) void k_mom3d_eq(MacroStore3<R> src, LBParams P, Moments3<R> M, int width, int nstrip,
-                                                 int seg, int nseg) {
+__global__ __launch_bounds__(64 * MOM3_WAVES, sizeof(R) == 4 ? 3 : 2) void k_mom3d_eq(
+    MacroStore3<R> src, LBParams P, Moments3<R> M, int width, int nstrip, int seg, int nseg) {
 #pragma clang fp contract(off)
   using L = Lattice<19>;
-  const int l = dealt_index((int)blockIdx.x, P.nz * nstrip * nseg, P.nxcd);
-  const int z = l % P.nz, strip = (l / P.nz) % nstrip, sg = l / (P.nz * nstrip);
-  if (P.wall_z && (z == 0 || z == P.nz - 1)) return;
+  const int nzg = (P.nz + MOM3_WAVES - 1) / MOM3_WAVES;
+  const int l = dealt_index((int)blockIdx.x, nzg * nstrip * nseg, P.nxcd);
+  const int zw = (l % nzg) * MOM3_WAVES + (int)(threadIdx.x >> 6), strip = (l / nzg) % nstrip, sg = l / (nzg * nstrip);
+  // (a wave past the last plane, or at a wall, goes along with its workgroup)
+  const int z = min(zw, P.nz - 1);
+  const bool out = zw < P.nz && !(P.wall_z && (z == 0 || z == P.nz - 1));
   const int j = threadIdx.x & 63, xc = strip * width - 1 + j;
   const int x = wrap(xc, P.nx);
-  const bool mine = j >= 1 && j <= width && xc < P.nx;
+  const bool mine = out && j >= 1 && j <= width && xc < P.nx;
   const int y0 = sg * seg, y1 = min(y0 + seg, P.ny);
   const int zs[3] = {z == 0 ? P.nz - 1 : z - 1, z, z == P.nz - 1 ? 0 : z + 1};
   const R rho0 = (R)src.rho0;
@@ -294,6 +305,9 @@ __global__ __launch_bounds__(64, sizeof(R) == 4 ? 3 : 2) void k_mom3d_eq(MacroSt
 #pragma unroll
     for (int a = 0; a < 3; a++) s[a] = nxt[a];
     fetch(min(r + 1, y1));
+    // waves of neighbouring planes keep to the same row, so that what they
+    // share comes out of the cache
+    __builtin_amdgcn_s_barrier();
     // one set after the other, each moved in x and summed before the next
     Share19<R> o, up, dn;
     double g0, h0;
@@ -370,7 +384,10 @@ __global__ __launch_bounds__(64, sizeof(R) == 4 ? 3 : 2) void k_mom3d_eq(MacroSt
 // and stencil instead of 18).  The potentials of plane k - 2, the sums of plane k
 // and the collision of plane k - 3 share an iteration and one barrier.
 //
-// What bounds it: MEASURED3D
+// What bounds it: memory (1.0 GB read, 1.0 GB written at 256^3, 416 us at the rate
+// of a copy) and the barrier, with one workgroup per CU at the wide tile (11 waves
+// at 168 registers): 599 us, to populations 1316 us (0.9 + 4.2 GB).  The narrow
+// tile gives a small lattice's CUs a workgroup each: see EQ3_WIDE.
 template <class Dst, typename R, int TX, int TY>
 __global__ __launch_bounds__((TX * (TY + 2) + 2 * (TY + 2) + 63) / 64 * 64) void k_lb3d_eq(
     Dst dst, LBParams P, Moments3<R> M, const int* __restrict__ tflag, const int* __restrict__ tstate,
@@ -410,12 +427,11 @@ __global__ __launch_bounds__((TX * (TY + 2) + 2 * (TY + 2) + 63) / 64 * 64) void
   const long long plane = (long long)P.ny * P.nx;
 
   // in flight: the staged moments of the next plane, the profile field of the
-  // next potentials, the moments and spread force of the next collision
+  // next potentials, the moments of the next collision
   R nd[NH];
   double nphi[NH], npsi[NH];
   double Inx = 0.0, cphi = 0.0;
   R cd = 0, cjx = 0, cjy = 0, cjz = 0;
-  long long fb[3] = {0, 0, 0};
   int fl0 = 0, fl1 = 0;  // tile flags of this node in the last plane and the one before
   bool cact = false;
   // sums of the last planes: concentrations c and their in-plane differences
@@ -467,7 +483,6 @@ __global__ __launch_bounds__((TX * (TY + 2) + 2 * (TY + 2) + 63) / 64 * 64) void
     }
     const R d = cd, jx = cjx, jy = cjy, jz = cjz;
     const double phi = cphi, psi = psi3;
-    const long long fx = fb[0], fy = fb[1], fz = fb[2];
     const bool act = cact;
     __syncthreads();
     __builtin_amdgcn_sched_barrier(0);
@@ -479,8 +494,6 @@ __global__ __launch_bounds__((TX * (TY + 2) + 2 * (TY + 2) + 63) / 64 * 64) void
       const int cz = min(max(zbase + dir * (k - 2), 0), P.nz - 1);
       const long long cn = cz * plane;
       cact = own && k >= 4 && k < K && fl1 == stamp;
-      if (cact)
-        for (int a = 0; a < 3; a++) fb[a] = (fib + 3 * cn)[3 * here + a];
       const int zf = halo_row(zbase + dir * k, P.nz, P.wall_z);
       fl1 = fl0;
       fl0 = tflag[tile3(P, xw, yw, zf)];
@@ -545,12 +558,16 @@ __global__ __launch_bounds__((TX * (TY + 2) + 2 * (TY + 2) + 63) / 64 * 64) void
 #pragma unroll
       for (int a = 0; a < 3; a++) F[a] = fma_(-1.0 / 12.0, F[a], P.fext[a]);
       if (act) {
+        // (the spread force is loaded here, not ahead: only few planes have one,
+        // and six registers more spill)
+        long long* fp = fib + 3 * (cz * plane) + 3 * here;
+        const long long fx = fp[0], fy = fp[1], fz = fp[2];
         F[0] += from_fix(fx);
         F[1] += from_fix(fy);
         F[2] += from_fix(fz);
 #pragma unroll
         for (int a = 0; a < 3; a++) {
-          (fib + 3 * (cz * plane))[3 * here + a] = 0;
+          fp[a] = 0;
           (force + 3 * (cz * plane))[3 * here + a] = F[a];
         }
       }
@@ -568,6 +585,7 @@ __global__ __launch_bounds__((TX * (TY + 2) + 2 * (TY + 2) + 63) / 64 * 64) void
       o.hm = (R)(3.0 * P.gpsi * s_u[b ^ 1][2][uq]);
       o.phi = phi;
       o.psi = psi;
+      __builtin_amdgcn_sched_barrier(0);
       if constexpr (Dst::kMacro) {
         dst.set_node(own ? (unsigned)node : 0xffffffffu, o);  // past the buffer: dropped
       } else if (own) {
@@ -580,10 +598,12 @@ __global__ __launch_bounds__((TX * (TY + 2) + 2 * (TY + 2) + 63) / 64 * 64) void
           eq_pair_f(R(Lattice<19>::w(i)), rr, drs, q, along19(i, o.w[0], o.w[1], o.w[2]), f[i], f[i + 1]);
           dst.template store<R>(0, i, node, f[i]);
           dst.template store<R>(0, i + 1, node, f[i + 1]);
+          __builtin_amdgcn_sched_barrier(0);
         }
         double g0;
 #pragma unroll
         for (int set = 1; set < 3; set++) {
+          __builtin_amdgcn_sched_barrier(0);
           eq19_gall(set == 1 ? o.phi : o.psi, set == 1 ? o.gm : o.hm, o.v, f, g0);
           dst.store_rest(set, node, g0);
 #pragma unroll

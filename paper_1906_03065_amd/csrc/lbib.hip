@@ -857,7 +857,7 @@ struct Engine3D final : lbib_sim {
 
   // rows per wave of k_mom3d_eq: some four rounds of waves, whose tails even out
   int pick_rows(int nstrip) {
-    if (!mom_slots) mom_slots = resident_blocks((const void*)&k_mom3d_eq<R>, 64);
+    if (!mom_slots) mom_slots = MOM3_WAVES * resident_blocks((const void*)&k_mom3d_eq<R>, 64 * MOM3_WAVES);
     const long long rows = ((long long)p.ny * p.nz * nstrip + 4LL * mom_slots - 1) / (4LL * mom_slots);
     return (int)std::min<long long>(p.ny, std::max<long long>(rows, 8));
   }
@@ -908,8 +908,9 @@ struct Engine3D final : lbib_sim {
       if constexpr (Src::kMacro) {
         const int nstrip = (p.nx + 61) / 62, width = (p.nx + nstrip - 1) / nstrip;
         const int rows = pick_rows(nstrip), nseg = (p.ny + rows - 1) / rows;
-        hipLaunchKernelGGL((k_mom3d_eq<R>), dim3((unsigned)(p.nz * nstrip * nseg)), dim3(64), 0, stream, src, P, m3, width,
-                           nstrip, rows, nseg);
+        const int nzg = (p.nz + MOM3_WAVES - 1) / MOM3_WAVES;
+        hipLaunchKernelGGL((k_mom3d_eq<R>), dim3((unsigned)(nzg * nstrip * nseg)), dim3(64 * MOM3_WAVES), 0, stream, src, P,
+                           m3, width, nstrip, rows, nseg);
         const long long zb = p.wall_z ? std::min(p.nz, 2) : 0, yb = p.wall_y ? std::min(p.ny, 2) : 0;
         const long long nb = (zb * p.ny + (p.nz - zb) * yb) * p.nx;
         if (nb > 0)
