@@ -540,7 +540,7 @@ __device__ __forceinline__ void coupling2d_tile(const MemDev& md, const TileMap&
     }
     // (from Macro2 a wave takes in the 10 x 10 nodes its populations come from
     // once, 8 loads per lane; pulled one by one they were 40, and half of the
-    // kernel: MEASUREDPSI)
+    // kernel: 54 us against 33 at 2048 x 2048 with two capsules)
     R hmov[8], mh[2][3];
     double hrest = 0.0, mpsi[2];
     if constexpr (St::kMacro) {
@@ -740,41 +740,39 @@ __device__ __forceinline__ void coupling2d_tile(const MemDev& md, const TileMap&
               ok = thr > ca.r_cut;
               side = sk == 0xFFFE ? 1 : 0;
             } else {
-              // the kept segment and COUP_WIN on each side: screened in FP32
-              // (with the margin of the renewals below), the near-ties, one or
-              // two as a rule, compared in FP64 (lowest index on equal
-              // distances).  All 17 in FP64, a division each, were most of
-              // this kernel's arithmetic: MEASUREDWIN
-              constexpr int NW = 2 * COUP_WIN + 1;  // segments of the window
-              const float4* stab = md.stab + b;
-              const float* sinv = md.sinv + b;
-              const float fcx = (float)(px - cx), fcy = (float)(py - cy);
-              int q0 = (sk - COUP_WIN) % n;
-              if (q0 < 0) q0 += n;
-              float f[NW], bf = 3.0e38f;
-              int q = q0;
+              // the kept segment and COUP_WIN on each side (lowest index on
+              // equal distances, whatever the order), walked along the ring;
+              // each vertex is loaded two segments before it is needed, so
+              // the loads of three vertices are in flight at once
+              constexpr int NW = 2 * COUP_WIN + 2;  // vertices of the window
+              auto nxt = [&](int v) { return (v + 1 == n) ? 0 : v + 1; };
+              int q = (sk - COUP_WIN) % n;
+              if (q < 0) q += n;
+              int q1 = nxt(q), q2 = nxt(q1);
+              double ax = X[3 * q], ay = X[3 * q + 1];
+              double b1x = X[3 * q1], b1y = X[3 * q1 + 1];
+              double b2x = X[3 * q2], b2y = X[3 * q2 + 1];
 #pragma unroll
-              for (int k = 0; k < NW; k++) {
-                f[k] = seg_d2f(fcx, fcy, stab[q], sinv[q]);
-                bf = fminf(bf, f[k]);
-                q = (q + 1 == n) ? 0 : q + 1;
-              }
-              const float tol = bf + (2e-3f + 2e-5f * bf);
-              unsigned ties = 0;
-#pragma unroll
-              for (int k = 0; k < NW; k++) ties |= (f[k] > tol ? 0u : 1u) << k;
-#pragma unroll 1
-              while (ties) {
-                q = (q0 + __ffs((int)ties) - 1) % n;
-                ties &= ties - 1u;
-                const int q1 = (q + 1 == n) ? 0 : q + 1;
+              for (int k = 0; k + 1 < NW; k++) {
+                // vertex k + 3 (the last ones load their predecessor again)
+                const int q3 = k + 3 < NW ? nxt(q2) : q2;
+                const double b3x = X[3 * q3], b3y = X[3 * q3 + 1];
                 double tt;
-                const double d2 = seg_d2(px, py, X[3 * q], X[3 * q + 1], X[3 * q1], X[3 * q1 + 1], tt);
+                const double d2 = seg_d2(px, py, ax, ay, b1x, b1y, tt);
                 if (d2 < d2b || (d2 == d2b && q < sb)) {
                   d2b = d2;
                   sb = q;
                   tb = tt;
                 }
+                q = q1;
+                q1 = q2;
+                q2 = q3;
+                ax = b1x;
+                ay = b1y;
+                b1x = b2x;
+                b1y = b2y;
+                b2x = b3x;
+                b2y = b3y;
               }
               ok = sqrt(d2b) < thr;
             }
