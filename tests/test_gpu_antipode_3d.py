@@ -50,3 +50,41 @@ def test_renewed_entries_bitwise(subdiv, r_cut, steps):
         for q in ma:
             assert np.array_equal(ma[q], mb[q]), (n, q)
     assert a.check() == 0
+
+
+def _globe(nlon, nlat):
+    """Unit sphere of meridians and parallels, outward: nlon triangles around
+    each pole, which get thin as nlon grows."""
+    V = [(0.0, 0.0, -1.0)]
+    for i in range(1, nlat):
+        t = np.pi * i / nlat
+        V += [(np.sin(t) * np.cos(p), np.sin(t) * np.sin(p), -np.cos(t)) for p in 2 * np.pi * np.arange(nlon) / nlon]
+    V.append((0.0, 0.0, 1.0))
+    at = lambda i, j: 1 + (i - 1) * nlon + j % nlon
+    T = []
+    for j in range(nlon):
+        T.append((0, at(1, j + 1), at(1, j)))
+        for i in range(1, nlat - 1):
+            T += [(at(i, j), at(i, j + 1), at(i + 1, j + 1)), (at(i, j), at(i + 1, j + 1), at(i + 1, j))]
+        T.append((at(nlat - 1, j), at(nlat - 1, j + 1), len(V) - 1))
+    return np.array(V), np.array(T, dtype=np.int32)
+
+
+@pytest.mark.parametrize("nlon,nlat", [(14, 9), (16, 9), (160, 8)])
+def test_many_and_thin_triangles_around_a_vertex(orc, nlon, nlat):
+    """Vertices whose triangles overflow a row of the one-ring table (above 15
+    neighbours), and triangles too thin for an FP32 normal: FP64 against the
+    oracle over steps that hold, renew and search entries, 1e-9 as above."""
+    w = W.capsule3d(n=34, R=6.5, subdiv=1, two=False, bridge=False, r_cut=4.0, shift=(0.3, -0.2, 0.1))
+    c = w["membranes"][0]["X"].mean(axis=0)
+    V, T = _globe(nlon, nlat)
+    w["membranes"][0].update(X=6.5 * V + c, tris=T)
+    o = run_oracle(orc, w)
+    g = run_gpu(w, "fp64")
+    for k in (1, 6):
+        o.step(k - o.steps_done)
+        g.step(k - g.steps_done)
+        for q, v in compare(g, o, D=3).items():
+            assert v < 1e-9, (k, q, v)
+        assert marker_err(g, o, 1) < 1e-10
+    assert g.check() == 0
