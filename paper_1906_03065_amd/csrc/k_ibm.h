@@ -540,7 +540,7 @@ __device__ __forceinline__ void coupling2d_tile(const MemDev& md, const TileMap&
     }
     // (from Macro2 a wave takes in the 10 x 10 nodes its populations come from
     // once, 8 loads per lane; pulled one by one they were 40, and half of the
-    // kernel: 54 us against 33 at 2048 x 2048 with two capsules)
+    // kernel: 54 us against 33 at 2048 x 2048 with 16 capsules)
     R hmov[8], mh[2][3];
     double hrest = 0.0, mpsi[2];
     if constexpr (St::kMacro) {

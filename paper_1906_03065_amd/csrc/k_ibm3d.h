@@ -1297,9 +1297,10 @@ struct Renew3 {
 // the first size below; a second pass over the tiles with renewed entries instead
 // of the node's whole work in k_renew3d took 0.48 ms there).  Per step, this
 // kernel, k_renew3d and the search, against a search of every tile:
-//   256^3, two 5120-triangle capsules, some 7200 tiles: 0.77 + 0.35 + 0.02 ms,
-//     before 1.86
-//   64^3, the same meshes: 166 + 106 + 8 us, before 2.47 ms
+//   256^3, two capsules of 5120 triangles, some 7200 tiles: 0.52 + 0.21 + 0.01
+//     ms, before 1.86 (0.77 + 0.35 with six float4 per triangle and every
+//     triangle around a near-tie in FP64)
+//   64^3, two capsules of 1280 triangles: 100 + 79 + 8 us, before 2.47 ms
 template <class St, typename R, int NT>
 __global__ __launch_bounds__(NT, 2) void k_coupling3d_kept(MemDev md, MeshDev mh, TileMap tm, Coup3Args ca,
                                                            double* __restrict__ Ifield, St cur,

@@ -779,24 +779,6 @@ __device__ __forceinline__ void step2d_run(const Src& src, const Dst& dst, const
           r0 = kh0[SA];
           collide9(P, qf, qg, qh, q0, r0, (double)md[SA], (double)mjx[SA], (double)mjy[SA], mphi[SA], cq[SA][2], mpC,
                    msC, Fx, Fy);
-          if constexpr (St::kQuantized) {
-            // moving populations are stored rounded; the rest population of the
-            // same set takes the rounding so the node's mass per set is exact
-            R ef = 0, eg = 0, eh = 0;
-#pragma unroll
-            for (int i = 1; i < 9; i++) {
-              const R vf = dst.quantize(qf[i]), vg = dst.quantize(qg[i]), vh = dst.quantize(qh[i]);
-              ef += qf[i] - vf;
-              eg += qg[i] - vg;
-              eh += qh[i] - vh;
-              qf[i] = vf;
-              qg[i] = vg;
-              qh[i] = vh;
-            }
-            qf[0] += ef;
-            q0 += (double)eg;
-            r0 += (double)eh;
-          }
         } else {
           const double ir = recip(P.rho0 + (double)md[SA]);
           const double jxd = (double)mjx[SA], jyd = (double)mjy[SA];

@@ -27,6 +27,7 @@
 #include "k_ibm3d.h"
 #include "k_lb.h"
 #include "k_eq3d.h"
+#include "k_lb2d_ring.h"
 #include "k_lb3d.h"
 #include "k_misc.h"
 #include "store.h"
@@ -440,7 +441,11 @@ int resident_blocks(const void* k, int threads) {
   return per_cu * ncu;
 }
 
-constexpr long long EQ3_WIDE = 1500000;  // nodes from which the D3Q19 tile is the wide one
+// Nodes from which k_lb3d_eq's tile is the wide one.  The narrow one gives a
+// small lattice's CUs a workgroup each, the wide one forms fewer rims: whole
+// steps without membranes take 87 us wide and 83 narrow at 96^3, 107 and 122 at
+// 112^3, 291 and 321 at 160^3.
+constexpr long long EQ3_WIDE = 1100000;
 constexpr int MIN_SEG2 = 4;  // fewest rows of a D2Q9 segment chosen automatically
 
 template <class St, typename R>
@@ -581,9 +586,40 @@ struct Engine2D final : lbib_sim {
                        src, dst, P, (const int*)at<int>(L.tflag), (const int*)at<int>(L.tstate),
                        (const double*)at<double>(L.Ifield), at<long long>(L.fib), at<double>(L.force));
   }
+  // the same for the 16-bit formats, a workgroup per region
+  template <int FORM>
+  void launch_ring(St src, St dst, hipStream_t s, int mode) {
+    constexpr int BX = RING_LANES, WPE = FORM ? 2 : 3;
+    const int W = BX - 4;
+    int& v = lb_slots[FORM][0][0][1];
+    if (!v) v = resident_blocks((const void*)&k_lb2d_ring<St, R, BX, 3, WPE, FORM>, BX);
+    P.nstrip = (p.nx + W - 1) / W;
+    P.seg = pick_seg(P.nstrip, v);
+    P.nseg = (p.ny + P.seg - 1) / P.seg;
+    P.nxcd = nxcd > 0 ? nxcd : 8;
+    P.mode = mode;
+    P.npiece = mode == 2 ? (P.seg + 5) / 6 : 1;
+    P.seg2 = (P.seg + P.npiece - 1) / P.npiece;
+    const dim3 grid(P.nstrip * P.nseg * P.npiece);
+    const int *tf = at<int>(L.tflag), *ts = at<int>(L.tstate);
+    const double* If = at<double>(L.Ifield);
+    long long* fib = at<long long>(L.fib);
+    double* frc = at<double>(L.force);
+    if (mode == 0)
+      hipLaunchKernelGGL((k_lb2d_ring<St, R, BX, 3, WPE, FORM>), grid, dim3(BX), 0, s, src, dst, P, tf, ts, If, fib, frc);
+    else
+      hipLaunchKernelGGL((k_lb2d_ring_part<St, R, BX, 3, WPE, FORM>), grid, dim3(BX), 0, s, src, dst, P, tf, ts, If, fib,
+                         frc);
+  }
   template <class Src, class Dst>
   void launch_lb(const Src& src, const Dst& dst, hipStream_t s, int mode) {
-    if constexpr (!Src::kMacro && !Dst::kMacro)
+    if constexpr (St::kQuantized) {
+      if (force_form)
+        launch_ring<1>(src, dst, s, mode);
+      else
+        launch_ring<0>(src, dst, s, mode);
+      return;
+    } else if constexpr (!Src::kMacro && !Dst::kMacro)
       if (relaxes()) {
         if (force_form)
           launch_form<1, Src, Dst, true>(src, dst, s, mode);
