@@ -859,7 +859,7 @@ __device__ __forceinline__ bool region_active(const LBParams& P, const int* __re
 // instructions a row of which 200 are FP64, are then busy for 60 to 70 us of
 // it.  227 registers leave two waves per SIMD.  A relaxing step keeps three
 // rows of populations as well (249 registers): 46 -> 42 us at 1000 x 777 in the
-// potential form, 243 -> 227 us at 2048^2 in FP16.
+// potential form.
 //
 // P.mode: 0
 // every region; the same step in two passes: 1 the regions that read no
