@@ -17,9 +17,10 @@ replayed from a hipGraph, lattice-kernel shapes from the autotuner), against
 the same 64 simulations stepped one after another.
 
 Prints one JSON line: whole-step MLUPS, the lattice update's HBM roofline
-fraction (algorithmic bytes / kernel time from HIP events on the library's
-stream over the timed region; 216 B per update for D2Q9 FP32, the bytes the
-storage format actually moves reported beside it) and the CPU oracle's rate
+fraction (bytes moved per update / kernel time from HIP events on the library's
+stream over the timed region; 88 B per update for D2Q9 FP32, whose steps inside
+a call pass on 44 B per node instead of populations; the bytes of populations
+read and written once reported beside it) and the CPU oracle's rate
 on a bounded sample of the same workload, on all host threads and on one.
 D2Q9 runs take the divergence form of the force (the library's default)
 unless --force-form 0 asks for the potential form.
@@ -77,6 +78,18 @@ def stored_bytes_per_lup(storage: str, Q: int = 9) -> int:
     if storage == "fp64":
         return 2 * 3 * Q * 8
     return 2 * (3 * (Q - 1) * 2 + 4 + 2 * 8)
+
+
+def inner_bytes_per_lup(storage: str, Q: int = 9) -> int:
+    """Bytes per lattice update of a step inside a call, every relaxation time
+    1 (as in these workloads): the numbers a node's populations are functions
+    of, in and out (D2Q9: 7, and phi and psi in FP64; D3Q19: 9 and 2, and the
+    moment field's 4 and 2 between its two kernels).  The 16-bit formats move
+    their populations."""
+    if storage not in ("fp32", "fp64"):
+        return stored_bytes_per_lup(storage, Q)
+    b = 4 if storage == "fp32" else 8
+    return 2 * (7 * b + 16) if Q == 9 else 2 * (9 * b + 16) + 2 * (4 * b + 16)
 
 
 def host_info() -> dict:
@@ -213,8 +226,9 @@ def main():
     mlups = N * args.steps / el / 1e6
     lb_ms = tm["lb"] / max(tm["steps"], 1)
     Q = 19 if d3 else 9
-    bpl = alg_bytes_per_lup(args.storage, Q)
+    bpl = inner_bytes_per_lup(args.storage, Q)
     stored = stored_bytes_per_lup(args.storage, Q)
+    inner = args.storage in ("fp32", "fp64")
     achieved = bpl * N / (lb_ms * 1e-3) / 1e9
     out = {
         "metric": "MLUPS & % HBM roofline; wall time to equilibrium, warm-start vs plain",
@@ -241,10 +255,12 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": None if d3 else measured_traffic(args.storage, size, form),
-                     "kernel": "k_mom3d + k_lb3d" if d3 else "k_lb2d", "kernel_ms": round(lb_ms, 5),
+                     "kernel": (("k_mom3d_eq + k_lb3d_eq" if inner else "k_mom3d + k_lb3d") if d3 else
+                                ("k_lb2d" if inner else "k_lb2d_ring")),
+                     "kernel_ms": round(lb_ms, 5),
                      "bytes_per_lup": bpl,
+                     "population_bytes_per_lup": alg_bytes_per_lup(args.storage, Q),
                      "stored_bytes_per_lup": stored,
-                     "achieved_stored": round(stored * N / (lb_ms * 1e-3) / 1e9, 1),
                      "kernel_share_of_step": round(lb_ms / (el * 1e3 / args.steps), 4),
                      "launch": g.get_launch()},
     }
@@ -315,7 +331,7 @@ def bench_batch(args):
     el_seq = time.perf_counter() - t0
     mlups = NT * args.steps / el / 1e6
     mlups_seq = NT * args.steps / el_seq / 1e6
-    bpl = alg_bytes_per_lup("fp32")
+    bpl = inner_bytes_per_lup("fp32")
     achieved = bpl * NT / (el / args.steps) / 1e9
     out = {
         "metric": "MLUPS & % HBM roofline; wall time to equilibrium, warm-start vs plain",
