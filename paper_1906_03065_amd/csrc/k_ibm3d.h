@@ -543,27 +543,12 @@ __device__ __forceinline__ float geo_margin(float b, float px, float py, float p
   return 1e-3f + 1e-5f * b + 2e-6f * (fabsf(px) + fabsf(py) + fabsf(pz)) * (1.0f + b);
 }
 
-// The closest triangle to P over the whole mesh by one wave (FP64, lowest index
-// on ties) and a lower bound on the distance of every triangle that shares no
-// vertex with it, at most COUP3_PAD1 above its own distance.  near: a squared
-// distance known to be reached (3e38: none).  One FP32 scan of the clusters that
-// come within reach, two at a time, one triangle per lane; each lane keeps its
-// three nearest, among which the near-ties are compared in FP64 and the bound is
-// found (a lane whose three all share a vertex with the closest triangle bounds
-// its others by the third).
-__device__ __forceinline__ void wave_closest3(const MemDev& md, const MeshDev& mh, const float4* __restrict__ cls,
-                                              int ncl, int t0m, int nt, const double* bx, const double* P, float near,
-                                              double& d2, int& t, double& lb) {
-  const int lane = threadIdx.x & 63;
-  const float mg = 0.02f;
-  const float px = (float)(P[0] - 0.5 * (bx[0] + bx[3])), py = (float)(P[1] - 0.5 * (bx[1] + bx[4])),
-              pz = (float)(P[2] - 0.5 * (bx[2] + bx[5]));
-  float ul = sqrtf(near);
-  for (int k = lane; k < ncl; k += 64) ul = fminf(ul, sph_dist(px, py, pz, cls[k]) + cls[k].w);
-  const float reach = wave_minf(ul) + mg + COUP3_PAD1;
-  float k0 = 3.0e38f, k1 = 3.0e38f, k2 = 3.0e38f;  // this lane's nearest, ascending
+// the three nearest of the triangles shown to it, ascending (q: -1 where there
+// are fewer; a distance that is not finite is none)
+struct Nearest3 {
+  float k0 = 3.0e38f, k1 = 3.0e38f, k2 = 3.0e38f;
   int q0 = -1, q1 = -1, q2 = -1;
-  auto add = [&](float d, int q) {
+  LB_HOST_DEVICE void add(float d, int q) {
     if (d < k2) {
       k2 = d;
       q2 = q;
@@ -584,7 +569,32 @@ __device__ __forceinline__ void wave_closest3(const MemDev& md, const MeshDev& m
       k1 = f;
       q1 = i;
     }
-  };
+  }
+  // how many of them there are within tol
+  LB_HOST_DEVICE int within(float tol) const {
+    return q0 >= 0 && k0 <= tol ? (q1 >= 0 && k1 <= tol ? (q2 >= 0 && k2 <= tol ? 3 : 2) : 1) : 0;
+  }
+};
+
+// The closest triangle to P over the whole mesh by one wave (FP64, lowest index
+// on ties; -1 if none has a finite distance, as on a mesh that has diverged) and a lower bound on the distance of every triangle that shares no
+// vertex with it, at most COUP3_PAD1 above its own distance.  near: a squared
+// distance known to be reached (3e38: none).  One FP32 scan of the clusters that
+// come within reach, two at a time, one triangle per lane; each lane keeps its
+// three nearest, among which the near-ties are compared in FP64 and the bound is
+// found (a lane whose three all share a vertex with the closest triangle bounds
+// its others by the third).
+__device__ __forceinline__ void wave_closest3(const MemDev& md, const MeshDev& mh, const float4* __restrict__ cls,
+                                              int ncl, int t0m, int nt, const double* bx, const double* P, float near,
+                                              double& d2, int& t, double& lb) {
+  const int lane = threadIdx.x & 63;
+  const float mg = 0.02f;
+  const float px = (float)(P[0] - 0.5 * (bx[0] + bx[3])), py = (float)(P[1] - 0.5 * (bx[1] + bx[4])),
+              pz = (float)(P[2] - 0.5 * (bx[2] + bx[5]));
+  float ul = sqrtf(near);
+  for (int k = lane; k < ncl; k += 64) ul = fminf(ul, sph_dist(px, py, pz, cls[k]) + cls[k].w);
+  const float reach = wave_minf(ul) + mg + COUP3_PAD1;
+  Nearest3 near3;  // this lane's
   const float4* geo = mh.geo + C3_GEOT * (size_t)t0m;
   const int* perm = mh.perm + t0m;
   auto scan = [&](auto visit) {
@@ -594,7 +604,8 @@ __device__ __forceinline__ void wave_closest3(const MemDev& md, const MeshDev& m
         const float4 cs = cls[c0 + lane];
         lo = sph_dist(px, py, pz, cs) - cs.w;
       }
-      unsigned long long todo = __ballot(lo <= reach);
+      // (a cluster with a non-finite marker has no sphere and is visited)
+      unsigned long long todo = __ballot(c0 + lane < ncl && !(lo > reach));
       while (todo) {
         const int ka = __ffsll((long long)todo) - 1;
         todo &= todo - 1ull;
@@ -614,21 +625,24 @@ __device__ __forceinline__ void wave_closest3(const MemDev& md, const MeshDev& m
       }
     }
   };
-  scan(add);
-  const float bf = wave_minf(k0), tol = bf + geo_margin(bf, px, py, pz);
+  scan([&](float d, int q) { near3.add(d, q); });
+  const float bf = wave_minf(near3.k0), tol = bf + geo_margin(bf, px, py, pz);
   d2 = 1e300;
   t = -1;
   auto exact = [&](int q) {
     double w[3];
     argmin_merge(d2, t, tri_d2_id(md, mh, t0m + q, P, w), q);
   };
-  if (k0 <= tol) exact(q0);  // the least of all among them
-  if (k1 <= tol) exact(q1);
-  if (__ballot(k2 <= tol))  // more near-ties than a lane keeps: every one again
+  const int ties = near3.within(tol);  // (the least of all among them)
+  if (ties > 0) exact(near3.q0);
+  if (ties > 1) exact(near3.q1);
+  if (__ballot(ties > 2))  // more near-ties than a lane keeps: every one again
     scan([&](float d, int q) {
       if (d <= tol) exact(q);
     });
   wave_argmin(d2, t);
+  lb = 0.0;
+  if (t < 0) return;  // uniform: no triangle of the mesh has a finite distance
   const int* tv = mh.tri + 3 * (t0m + t);
   const int v0 = tv[0], v1 = tv[1], v2 = tv[2];
   auto shares = [&](int q) {
@@ -640,11 +654,11 @@ __device__ __forceinline__ void wave_closest3(const MemDev& md, const MeshDev& m
   };
   const float lim = fminf(reach, (float)sqrt(d2) + COUP3_PAD1);
   float o2 = lim * lim;
-  if (q0 >= 0 && k0 < o2) {
-    if (!shares(q0))
-      o2 = k0;
-    else if (q1 >= 0 && k1 < o2)
-      o2 = shares(q1) ? fminf(o2, k2) : k1;  // (k2 whether it shares or not: a lower bound)
+  if (near3.q0 >= 0 && near3.k0 < o2) {
+    if (!shares(near3.q0))
+      o2 = near3.k0;
+    else if (near3.q1 >= 0 && near3.k1 < o2)
+      o2 = shares(near3.q1) ? fminf(o2, near3.k2) : near3.k1;  // (k2 whether it shares or not: a lower bound)
   }
   o2 = wave_minf(o2);
   lb = sqrt(fmax((double)(o2 - geo_margin(o2, px, py, pz)), 0.0));
@@ -905,7 +919,7 @@ __global__ __launch_bounds__(NT) void k_coupling3d(MemDev md, MeshDev mh, TileMa
           if (lane == ln) {
             d2b = rd2;
             tb = rt;
-            entry3(md, mh, m, t0m, tb, d2b, rlb, g.pp, o, ca.r_cut, keyw, lbw);
+            if (tb >= 0) entry3(md, mh, m, t0m, tb, d2b, rlb, g.pp, o, ca.r_cut, keyw, lbw);
           }
         }
       } else {
@@ -1423,7 +1437,7 @@ __global__ __launch_bounds__(NT, 2) void k_coupling3d_kept(MemDev md, MeshDev mh
 #pragma unroll 1
               for (int e = mh.vtoff[tv[k]]; e < mh.vtoff[tv[k] + 1]; e++) exact(mh.vt[e]);
           }
-          ok = sqrt(d2b) < thr;
+          ok = tb >= 0 && sqrt(d2b) < thr;
         }
       }
       search |= in && !has;
@@ -1508,15 +1522,17 @@ __global__ __launch_bounds__(256) void k_renew3d(MemDev md, MeshDev mh, const in
       int t;
       wave_closest3(md, mh, ctab + mh.coff[m], mh.coff[m + 1] - mh.coff[m], t0m, mh.toff[m + 1] - t0m, bx, P, r.near[c],
                     d2, t, lb);
-      d2 = tri_d2_id(md, mh, t0m + t, P, w);
-      Itot += node_profile3(md, mh, t0m + t, w, P, d2, bx[6], ca.alpha, ca.r_cut, bd[c]);
+      int key = -1;  // none found: no entry, no band
+      double bound = 0.0;
+      if (t >= 0) {  // uniform over the wave
+        d2 = tri_d2_id(md, mh, t0m + t, P, w);
+        Itot += node_profile3(md, mh, t0m + t, w, P, d2, bx[6], ca.alpha, ca.r_cut, bd[c]);
+        if (lane == 0) entry3(md, mh, m, t0m, t, d2, lb, P, bx[6], ca.r_cut, key, bound);
+      }
       if (lane == 0) {
-        int key;
-        double bound;
-        entry3(md, mh, m, t0m, t, d2, lb, P, bx[6], ca.r_cut, key, bound);
         const long long e = (long long)c * ca.N + r.node;
         ca.ckey[e] = key;
-        ca.clb[e] = bound3(bound, bx[7], image3(P, xi, dims));
+        ca.clb[e] = key >= 0 ? bound3(bound, bx[7], image3(P, xi, dims)) : 0.0f;
       }
     }
     if (lane == 0) Ifield[r.node] = Itot;
