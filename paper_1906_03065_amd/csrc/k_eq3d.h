@@ -403,8 +403,7 @@ __global__ __launch_bounds__((TX * (TY + 2) + 2 * (TY + 2) + 63) / 64 * 64) void
   const int x0 = (tl % ntilex) * TX, y0 = (tl / ntilex) * TY;
   const int z0 = sgm * P.seg, z1 = min(z0 + P.seg, P.nz);
   const int K = (z1 - z0) + 4;
-  const int dir = (sgm & 1) ? -1 : 1;
-  const int zbase = dir > 0 ? z0 - 2 : z1 + 1;
+  const int zbase = z0 - 2;
   const int stamp = tstate[1];
   // this thread's node of the potentials' region
   const int e = tid - TX * TYU;
@@ -442,7 +441,7 @@ __global__ __launch_bounds__((TX * (TY + 2) + 2 * (TY + 2) + 63) / 64 * 64) void
   double ax[3] = {}, px[3] = {}, ay[3] = {}, py[3] = {}, t1[3] = {}, t2[3] = {};
 
   auto stage = [&](int k) {
-    const long long zr = (long long)halo_row(zbase + dir * k, P.nz, P.wall_z) * plane;
+    const long long zr = (long long)halo_row(zbase + k, P.nz, P.wall_z) * plane;
 #pragma unroll
     for (int r = 0; r < NH; r++) {
       nd[r] = (M.d + zr)[hoff[r]];
@@ -488,13 +487,13 @@ __global__ __launch_bounds__((TX * (TY + 2) + 2 * (TY + 2) + 63) / 64 * 64) void
     __builtin_amdgcn_sched_barrier(0);
     // ---- loads of the next iteration
     {
-      const long long zi = (long long)halo_row(zbase + dir * (k - 1), P.nz, P.wall_z) * plane;
+      const long long zi = (long long)halo_row(zbase + k - 1, P.nz, P.wall_z) * plane;
       Inx = 0.0;
       if (k >= 2 && live && fl0 == stamp) Inx = (Ifield + zi)[here];
-      const int cz = min(max(zbase + dir * (k - 2), 0), P.nz - 1);
+      const int cz = min(max(zbase + k - 2, 0), P.nz - 1);
       const long long cn = cz * plane;
       cact = own && k >= 4 && k < K && fl1 == stamp;
-      const int zf = halo_row(zbase + dir * k, P.nz, P.wall_z);
+      const int zf = halo_row(zbase + k, P.nz, P.wall_z);
       fl1 = fl0;
       fl0 = tflag[tile3(P, xw, yw, zf)];
       cd = (M.d + cn)[here];
@@ -538,7 +537,7 @@ __global__ __launch_bounds__((TX * (TY + 2) + 2 * (TY + 2) + 63) / 64 * 64) void
       const double ne = u[TXU + 1], nw = u[TXU - 1], se = u[-TXU + 1], sw = u[-TXU - 1];
       const double dx = E - W, dy = Nn - S;
       const double t = fma_(2.0, u[0], (E + W) + (Nn + S));
-      const double gx = ax[f] + dx, gy = ay[f] + dy, gz = dir > 0 ? t - t2[f] : t2[f] - t;
+      const double gx = ax[f] + dx, gy = ay[f] + dy, gz = t - t2[f];
       F[0] = f == 2 ? psi * gx : fma_(f == 1 ? phi : rho, gx, F[0]);
       F[1] = f == 2 ? psi * gy : fma_(f == 1 ? phi : rho, gy, F[1]);
       F[2] = f == 2 ? psi * gz : fma_(f == 1 ? phi : rho, gz, F[2]);
@@ -553,7 +552,7 @@ __global__ __launch_bounds__((TX * (TY + 2) + 2 * (TY + 2) + 63) / 64 * 64) void
     }
     // ---- the collision of plane k - 3
     if (k >= 5) {
-      const int cz = zbase + dir * (k - 3);
+      const int cz = zbase + k - 3;
       const long long node = cz * plane + here;
 #pragma unroll
       for (int a = 0; a < 3; a++) F[a] = fma_(-1.0 / 12.0, F[a], P.fext[a]);
