@@ -181,7 +181,9 @@ int lbib_device_view(lbib_sim* s, int field, void** dev_ptr, size_t* elems);
 /* Checkpoint: lbib_save(s, NULL, &bytes) reports the size; with a buffer of
    at least that size it writes a header (a tag, the step counter, the marker
    and membrane counts, nx, ny, nz, Q, the storage format, the force form and
-   the population bytes), then the populations and the markers' X, U, F.
+   the population bytes), then the populations, the markers' X, U, F and what
+   the alignment of the last plane puts past the population bytes (with another
+   tag when there is any; a checkpoint without it loads as before).
    lbib_load restores a checkpoint taken from a simulation created with the
    same parameters and membranes; LBIB_EINVAL (and the handle unchanged) when
    any header word but the step counter differs from the handle's, or the

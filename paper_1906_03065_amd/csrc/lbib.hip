@@ -1902,8 +1902,21 @@ int lbib_device_view(lbib_sim* s, int field, void** ptr, size_t* elems) {
 
 // checkpoint header: a tag and the parameters a checkpoint must match
 namespace {
-constexpr long long CKPT_TAG = 0x31504b4342494c42LL;  // "BLIBCKP1" read as little-endian bytes
+constexpr long long CKPT_TAG = 0x31504b4342494c42LL;   // "BLIBCKP1" read as little-endian bytes
+constexpr long long CKPT_TAG2 = 0x32504b4342494c42LL;  // "BLIBCKP2": with the populations' end (below)
 constexpr int CKPT_WORDS = 12;
+// Bytes of a population buffer past pop_bytes.  The planes of each type start on
+// an aligned address, so where the planes before do not fill their last line,
+// the last plane (h_0) ends that much later; these bytes come last in a
+// checkpoint.  One with the first tag lacks them.
+size_t ckpt_tail(const lbib_sim* s) {
+  const size_t N = (size_t)s->N;
+  if (s->p.storage == LBIB_FP64) return 0;
+  const size_t end = s->p.storage == LBIB_FP32
+                         ? align_up((size_t)(3 * s->Q - 2) * N * 4) + 16 * N
+                         : align_up((size_t)(3 * (s->Q - 1)) * N * 2) + align_up(N * 4) + 16 * N;
+  return end - s->L.pop_bytes;
+}
 void ckpt_header(const lbib_sim* s, long long* h) {
   const int form = s->owner ? s->owner->force_form : s->force_form;
   // last word: the component densities' bit patterns mixed (0 when all are 1)
@@ -1914,7 +1927,7 @@ void ckpt_header(const lbib_sim* s, long long* h) {
       memcpy(&bits, &s->mw[k], 8);
       dh = (dh ^ bits) * 0x100000001b3ULL + 0x9e3779b97f4a7c15ULL;
     }
-  const long long v[CKPT_WORDS] = {CKPT_TAG, s->steps, (long long)s->M, (long long)s->K, s->p.nx, s->p.ny,
+  const long long v[CKPT_WORDS] = {ckpt_tail(s) ? CKPT_TAG2 : CKPT_TAG, s->steps, (long long)s->M, (long long)s->K, s->p.nx, s->p.ny,
                                    s->p.nz, (long long)s->Q, (long long)s->p.storage, (long long)form,
                                    (long long)s->L.pop_bytes, (long long)dh};
   for (int k = 0; k < CKPT_WORDS; k++) h[k] = v[k];
@@ -1926,7 +1939,7 @@ int lbib_save(lbib_sim* s, void* buf, size_t* bytes) {
   if (!s || !bytes) return LBIB_EINVAL;
   if (!s->ready) return LBIB_ESTATE;
   const size_t H = CKPT_WORDS * 8;
-  const size_t need = H + s->L.pop_bytes + (size_t)s->M * 24 * 3;
+  const size_t old = H + s->L.pop_bytes + (size_t)s->M * 24 * 3, tail = ckpt_tail(s), need = old + tail;
   if (!buf) {
     *bytes = need;
     return LBIB_OK;
@@ -1941,6 +1954,8 @@ int lbib_save(lbib_sim* s, void* buf, size_t* bytes) {
   for (int k = 0; k < 3; k++)
     HIPCHK(hipMemcpyAsync(o + H + s->L.pop_bytes + (size_t)k * s->M * 24, s->ws + offs[k],
                           (size_t)s->M * 24, hipMemcpyDeviceToHost, s->stream));
+  if (tail)
+    HIPCHK(hipMemcpyAsync(o + old, s->ws + s->L.pops[s->cur] + s->L.pop_bytes, tail, hipMemcpyDeviceToHost, s->stream));
   HIPCHK(hipStreamSynchronize(s->stream));
   *bytes = need;
   return LBIB_OK;
@@ -1950,12 +1965,15 @@ int lbib_load(lbib_sim* s, const void* buf, size_t bytes) {
   if (s && s->is_batch()) return LBIB_EINVAL;  // per-member calls go to the members
   if (!s || !buf) return LBIB_EINVAL;
   const size_t H = CKPT_WORDS * 8;
-  const size_t need = H + s->L.pop_bytes + (size_t)s->M * 24 * 3;
-  if (bytes < need) return LBIB_EINVAL;
+  const size_t old = H + s->L.pop_bytes + (size_t)s->M * 24 * 3;
+  if (bytes < old) return LBIB_EINVAL;
   const char* o = (const char*)buf;
   long long hdr[CKPT_WORDS], want[CKPT_WORDS];
   memcpy(hdr, o, H);
   ckpt_header(s, want);
+  const size_t tail = hdr[0] == CKPT_TAG ? 0 : ckpt_tail(s);
+  if (bytes < old + tail) return LBIB_EINVAL;
+  if (!tail) want[0] = CKPT_TAG;
   // every word but the step count must match: tag, markers, membranes,
   // lattice size, Q, storage, force form, population bytes and densities
   for (int k = 0; k < CKPT_WORDS; k++)
@@ -1966,6 +1984,8 @@ int lbib_load(lbib_sim* s, const void* buf, size_t bytes) {
   for (int k = 0; k < 3; k++)
     HIPCHK(hipMemcpyAsync(s->ws + offs[k], o + H + s->L.pop_bytes + (size_t)k * s->M * 24,
                           (size_t)s->M * 24, hipMemcpyHostToDevice, s->stream));
+  if (tail)
+    HIPCHK(hipMemcpyAsync(s->ws + s->L.pops[s->cur] + s->L.pop_bytes, o + old, tail, hipMemcpyHostToDevice, s->stream));
   HIPCHK(hipStreamSynchronize(s->stream));
   s->steps = hdr[1];
   s->ready = true;
