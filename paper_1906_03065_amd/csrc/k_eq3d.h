@@ -373,6 +373,41 @@ __global__ __launch_bounds__(64 * MOM3_WAVES, sizeof(R) == 4 ? 3 : 2) void k_mom
   }
 }
 
+// a node's populations, to the store dst
+template <class Dst, typename R>
+__device__ __forceinline__ void put_pops19(const Dst& dst, R rho0, double p0, double p1, const Macro3<R>& o,
+                                           long long node) {
+#pragma clang fp contract(off)
+  const R sp = p0 != 0.0 || p1 != 0.0 ? eq_shift<R>(p0, p1, o.phi, o.psi) : R(0);
+  const R rr = rho0 + o.dr, drs = o.dr + sp, q = speed19(o.w);
+  dst.template store<R>(0, 0, node, eq19_f0(rr, o.dr, sp, q));
+  R f[19];
+#pragma unroll
+  for (int i = 1; i < 19; i += 2) {
+    eq_pair_f(R(Lattice<19>::w(i)), rr, drs, q, along19(i, o.w[0], o.w[1], o.w[2]), f[i], f[i + 1]);
+    dst.template store<R>(0, i, node, f[i]);
+    dst.template store<R>(0, i + 1, node, f[i + 1]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  double g0;
+#pragma unroll
+  for (int set = 1; set < 3; set++) {
+    __builtin_amdgcn_sched_barrier(0);
+    eq19_gall(set == 1 ? o.phi : o.psi, set == 1 ? o.gm : o.hm, o.v, f, g0);
+    dst.store_rest(set, node, g0);
+#pragma unroll
+    for (int i = 1; i < 19; i++) dst.template store<R>(set, i, node, f[i]);
+  }
+}
+
+// the populations of the state that Macro3 holds (a call that fails between two
+// steps leaves populations, as every call does)
+template <class St, typename R>
+__global__ __launch_bounds__(256) void k_expand3d(MacroStore3<R> src, St dst) {
+  const unsigned n = blockIdx.x * blockDim.x + threadIdx.x;
+  if (n < src.N) put_pops19(dst, (R)src.rho0, src.p0, src.p1, src.node(n), (long long)n);
+}
+
 // The chemical potentials, the force (eqs. ForcingTermLBE, ForceFE + the spread
 // membrane force) and the collision, from the moment field.  A workgroup owns a
 // TX x TY column of nodes and marches along z; one thread per node of the
@@ -588,26 +623,7 @@ __global__ __launch_bounds__((TX * (TY + 2) + 2 * (TY + 2) + 63) / 64 * 64) void
       if constexpr (Dst::kMacro) {
         dst.set_node(own ? (unsigned)node : 0xffffffffu, o);  // past the buffer: dropped
       } else if (own) {
-        const R sp = P.psh[0] != 0.0 || P.psh[1] != 0.0 ? eq_shift<R>(P.psh[0], P.psh[1], o.phi, o.psi) : R(0);
-        const R rr = (R)P.rho0 + d, drs = d + sp, q = speed19(o.w);
-        dst.template store<R>(0, 0, node, eq19_f0(rr, d, sp, q));
-        R f[19];
-#pragma unroll
-        for (int i = 1; i < 19; i += 2) {
-          eq_pair_f(R(Lattice<19>::w(i)), rr, drs, q, along19(i, o.w[0], o.w[1], o.w[2]), f[i], f[i + 1]);
-          dst.template store<R>(0, i, node, f[i]);
-          dst.template store<R>(0, i + 1, node, f[i + 1]);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        double g0;
-#pragma unroll
-        for (int set = 1; set < 3; set++) {
-          __builtin_amdgcn_sched_barrier(0);
-          eq19_gall(set == 1 ? o.phi : o.psi, set == 1 ? o.gm : o.hm, o.v, f, g0);
-          dst.store_rest(set, node, g0);
-#pragma unroll
-          for (int i = 1; i < 19; i++) dst.template store<R>(set, i, node, f[i]);
-        }
+        put_pops19(dst, (R)P.rho0, P.psh[0], P.psh[1], o, node);
       }
     }
   }

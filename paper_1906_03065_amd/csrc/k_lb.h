@@ -894,4 +894,24 @@ __global__ __launch_bounds__(64, (step2d_waves<R, RELAX>())) void k_lb2d(Src src
   step2d_run<St, R, FORM, Src, Dst, RELAX>(src, dst, P, strip, y0, y1, tflag, tstate, Ifield, fib, force);
 }
 
+// the populations of the state that Macro2 holds (a call that fails between two
+// steps leaves populations, as every call does)
+template <class St, typename R>
+__global__ __launch_bounds__(256) void k_expand2d(MacroStore2<R> src, St dst) {
+  const unsigned n = blockIdx.x * blockDim.x + threadIdx.x;
+  if (n >= src.N) return;
+  R f[9], g[9], h[9];
+  double g0, h0;
+  macro_pops<R>((R)src.rho0, src.p0, src.p1, src.node(n), f, g, h, g0, h0);
+  dst.template store<R>(0, 0, n, f[0]);
+  dst.store_rest(1, n, g0);
+  dst.store_rest(2, n, h0);
+#pragma unroll
+  for (int i = 1; i < 9; i++) {
+    dst.template store<R>(0, i, n, f[i]);
+    dst.template store<R>(1, i, n, g[i]);
+    dst.template store<R>(2, i, n, h[i]);
+  }
+}
+
 }  // namespace lb

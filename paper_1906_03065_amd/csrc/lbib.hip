@@ -673,6 +673,7 @@ struct Engine2D final : lbib_sim {
       tend(3, t2);
     }
     cur = 1 - cur;
+    cur_macro = Dst::kMacro;
     steps++;
     if (timing) {
       timed_steps++;
@@ -682,6 +683,19 @@ struct Engine2D final : lbib_sim {
       }
     }
     return hipGetLastError() == hipSuccess ? LBIB_OK : LBIB_EHIP;
+  }
+
+  // a call that failed between two steps: back to populations
+  bool cur_macro = false;  // buffer cur holds Macro2
+  void expand() {
+    if constexpr (!St::kQuantized)
+      if (cur_macro) {
+        if (side) (void)hipStreamSynchronize(side);
+        hipLaunchKernelGGL((k_expand2d<St, R>), dim3((unsigned)((N + 255) / 256)), dim3(256), 0, stream, macro(cur),
+                           store(1 - cur));
+        cur = 1 - cur;
+        cur_macro = false;
+      }
   }
 
   // the first step of a call reads populations, the last one writes them;
@@ -696,7 +710,10 @@ struct Engine2D final : lbib_sim {
         rc = in ? (out ? step(macro(cur), macro(1 - cur)) : step(macro(cur), store(1 - cur)))
                 : (out ? step(store(cur), macro(1 - cur)) : step(store(cur), store(1 - cur)));
       }
-      if (rc) return rc;
+      if (rc) {
+        expand();
+        return rc;
+      }
     }
     return LBIB_OK;
   }
@@ -963,6 +980,18 @@ struct Engine3D final : lbib_sim {
     }
   }
 
+  // a call that failed between two steps: back to populations
+  bool cur_macro = false;  // buffer cur holds Macro3
+  void expand() {
+    if constexpr (!St::kQuantized)
+      if (cur_macro) {
+        hipLaunchKernelGGL((k_expand3d<St, R>), dim3((unsigned)((N + 255) / 256)), dim3(256), 0, stream, macro(cur),
+                           store(1 - cur));
+        cur = 1 - cur;
+        cur_macro = false;
+      }
+  }
+
   // the first step of a call reads populations, the last one writes them;
   // those between pass on Macro3 where they can (the population buffers hold it)
   int advance(int n) override {
@@ -975,7 +1004,10 @@ struct Engine3D final : lbib_sim {
         rc = in ? (out ? step(macro(cur), macro(1 - cur)) : step(macro(cur), store(1 - cur)))
                 : (out ? step(store(cur), macro(1 - cur)) : step(store(cur), store(1 - cur)));
       }
-      if (rc) return rc;
+      if (rc) {
+        expand();
+        return rc;
+      }
     }
     return LBIB_OK;
   }
@@ -1011,6 +1043,7 @@ struct Engine3D final : lbib_sim {
       tend(3, t2);
     }
     cur = 1 - cur;
+    cur_macro = Dst::kMacro;
     steps++;
     if (timing) {
       timed_steps++;
@@ -1267,6 +1300,7 @@ struct BatchEngine2D final : lbib_sim {
     }
     for (auto m : mem) {
       m->cur = 1 - m->cur;
+      m->cur_macro = DM;
       m->steps++;
     }
     steps++;
@@ -1282,7 +1316,10 @@ struct BatchEngine2D final : lbib_sim {
     for (int k = 0; k < n; k++) {
       const bool in = mac && k > 0, out = mac && k + 1 < n;
       const int rc = in ? (out ? step<true, true>() : step<true, false>()) : (out ? step<false, true>() : step<false, false>());
-      if (rc) return rc;
+      if (rc) {
+        for (auto m : mem) m->expand();
+        return rc;
+      }
     }
     return LBIB_OK;
   }
