@@ -128,15 +128,19 @@ __global__ void kb_interp2d(const BMember<St, R>* T, const int* __restrict__ mpr
 }
 
 // one wave per (strip, segment) item of the members listed in cm (bpre: item
-// prefix, ncm + 1 entries)
-template <class St, typename R, int FORM, bool SM, bool DM, bool RELAX>
-__global__ __launch_bounds__(64, (step2d_waves<R, RELAX>())) void kb_lb2d(const BMember<St, R>* T,
-                                                                         const int* __restrict__ cm,
-                                                                         const int* __restrict__ bpre, int ncm,
-                                                                         int parity) {
+// prefix, ncm + 1 entries); NW as in k_lb2d
+template <class St, typename R, int FORM, bool SM, bool DM, bool RELAX, int NW>
+__global__ __launch_bounds__(64 * NW, step2d_waves<R>()) void kb_lb2d(const BMember<St, R>* T,
+                                                                      const int* __restrict__ cm,
+                                                                      const int* __restrict__ bpre, int ncm,
+                                                                      int parity) {
   // items dealt to the eight XCDs in contiguous runs, so the neighbouring
   // segments of a member share their halo rows in one L2
-  const int item = dealt_index((int)blockIdx.x, (int)gridDim.x, 8);
+  int item = dealt_index((int)blockIdx.x, (int)gridDim.x, 8) * NW;
+  if constexpr (NW > 1) {
+    item += __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (item >= bpre[ncm]) return;
+  }
   const int q = prefix_find(bpre, ncm, item);
   const int i = cm[q];
   const LBParams P = T[i].P;
@@ -150,8 +154,8 @@ __global__ __launch_bounds__(64, (step2d_waves<R, RELAX>())) void kb_lb2d(const 
   int strip, sgm;
   strip_segment(item - bpre[q], T[i].nstrip[SM], P.nseg, 1, strip, sgm);
   const int y0 = sgm * P.seg, y1 = min(y0 + P.seg, P.ny);
-  step2d_run<St, R, FORM, decltype(src), decltype(dst), RELAX>(src, dst, P, strip, y0, y1, tflag, tstate,
-                                                               Ifield, fib, force);
+  step2d_run<St, R, FORM, decltype(src), decltype(dst), RELAX, (NW > 1)>(src, dst, P, strip, y0, y1, tflag, tstate,
+                                                                         Ifield, fib, force);
 }
 
 }  // namespace lb

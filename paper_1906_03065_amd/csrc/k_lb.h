@@ -464,10 +464,24 @@ constexpr int strip_halo() {
   return Src::kMacro ? 3 : 2;
 }
 // waves per SIMD the register budget is sized for
-template <typename R, bool RELAX>
+template <typename R>
 constexpr int step2d_waves() {
-  return sizeof(R) == 8 ? 1 : (RELAX ? 2 : 2);
+  return sizeof(R) == 8 ? 1 : 2;
 }
+// Waves of a workgroup that paces them (neighbouring strips, a barrier per row):
+// as many as a CU holds.  From populations to populations on a lattice whose
+// buffers exceed the last-level cache, waves on their own drift apart, and the
+// lines that the strips of 60 columns share are fetched and written back for
+// each of them.  Per step, on their own / paced, FP32 at tau = 1: 1000^2 49 / 50 us,
+// 1400^2 124 / 112, 2048^2 272 / 229, 3000^2 579 / 472, 4500^2 1356 / 1083
+// (four waves 110, 233, 482, 1155); FP64 700^2 43 / 43, 1000^2 113 / 102, 2048^2
+// 460 / 389 (its eight waves would not fit a CU at these registers).  Inside the
+// cache a barrier only costs: FP32 300^2 13.4 / 20 us.
+template <typename R>
+constexpr int step2d_paced() {
+  return 4 * step2d_waves<R>();
+}
+constexpr size_t PACED_FROM = (size_t)256 << 20;  // bytes of both buffers
 
 // One (strip, rows [y0, y1)) of the lattice: the whole march of a wave.
 // FORM 0: the force of eq. ForceFE in its potential form, -sum q grad mu_q
@@ -476,8 +490,9 @@ constexpr int step2d_waves() {
 // of Appendix A (the two forms agree up to the discretisation error).
 // Src, Dst: St (populations) or MacroStore2.  RELAX: a collision needs the
 // populations that came in (some tau differs from 1, or the storage rounds
-// them to 16 bits); Src and Dst are St.
-template <class St, typename R, int FORM, class Src, class Dst, bool RELAX>
+// them to 16 bits); Src and Dst are St.  PACED: the waves of the workgroup keep
+// to the same row.
+template <class St, typename R, int FORM, class Src, class Dst, bool RELAX, bool PACED>
 __device__ __forceinline__ void step2d_run(const Src& src, const Dst& dst, const LBParams& P,
                                            int strip, int y0, int y1, const int* __restrict__ tflag,
                                            const int* __restrict__ tstate, const double* __restrict__ Ifield,
@@ -542,6 +557,7 @@ __device__ __forceinline__ void step2d_run(const Src& src, const Dst& dst, const
     constexpr int S = PH % 3, SB = (PH + 2) % 3, SA = (PH + 1) % 3;  // slots of rows m, m - 1 (U), m - 2 (C)
     constexpr bool doM = PH >= 2 * LAG, doU = PH >= 2 + 2 * LAG, doC = PH >= 4 + 2 * LAG;
     const int r = rbase + k;
+    if constexpr (PACED) __builtin_amdgcn_s_barrier();
     if constexpr (RELAX) load_row(k);
     // ---- the row taken in
     R pf[9], pg[9], ph[9];
@@ -866,13 +882,14 @@ __device__ __forceinline__ bool region_active(const LBParams& P, const int* __re
 // membrane field, which may run beside the membrane kernels, 2 the others
 // after them, each segment cut into npiece pieces of seg2 rows so that the few
 // regions near the membranes still fill the GPU.
-template <class St, typename R, int FORM, class Src, class Dst, bool RELAX>
-__global__ __launch_bounds__(64, (step2d_waves<R, RELAX>())) void k_lb2d(Src src, Dst dst, LBParams P,
-                                                                      const int* __restrict__ tflag,
-                                                                      const int* __restrict__ tstate,
-                                                                      const double* __restrict__ Ifield,
-                                                                      long long* __restrict__ fib,
-                                                                      double* __restrict__ force) {
+// NW: waves of a workgroup, 1 or (modes 0 and 1) step2d_paced().
+template <class St, typename R, int FORM, class Src, class Dst, bool RELAX, int NW>
+__global__ __launch_bounds__(64 * NW, step2d_waves<R>()) void k_lb2d(Src src, Dst dst, LBParams P,
+                                                                     const int* __restrict__ tflag,
+                                                                     const int* __restrict__ tstate,
+                                                                     const double* __restrict__ Ifield,
+                                                                     long long* __restrict__ fib,
+                                                                     double* __restrict__ force) {
   int strip, sgm, piece = 0;
   if (P.mode == 2) {
     piece = (int)blockIdx.x % P.npiece;
@@ -880,7 +897,13 @@ __global__ __launch_bounds__(64, (step2d_waves<R, RELAX>())) void k_lb2d(Src src
     strip = rg % P.nstrip;
     sgm = rg / P.nstrip;
   } else {
-    strip_segment((int)blockIdx.x, P.nstrip, P.nseg, P.nxcd, strip, sgm);
+    int q = dealt_index((int)blockIdx.x, (int)gridDim.x, P.nxcd) * NW;
+    if constexpr (NW > 1) {
+      q += __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+      if (q >= P.nstrip * P.nseg) return;  // (the others' barriers do not wait for a wave that has ended)
+    }
+    strip = q % P.nstrip;
+    sgm = q / P.nstrip;
   }
   int y0 = sgm * P.seg, y1 = min(y0 + P.seg, P.ny);
   if (P.mode != 0) {
@@ -891,7 +914,7 @@ __global__ __launch_bounds__(64, (step2d_waves<R, RELAX>())) void k_lb2d(Src src
       y1 = min(y0 + P.seg2, y1);
     }
   }
-  step2d_run<St, R, FORM, Src, Dst, RELAX>(src, dst, P, strip, y0, y1, tflag, tstate, Ifield, fib, force);
+  step2d_run<St, R, FORM, Src, Dst, RELAX, (NW > 1)>(src, dst, P, strip, y0, y1, tflag, tstate, Ifield, fib, force);
 }
 
 // the populations of the state that Macro2 holds (a call that fails between two

@@ -549,11 +549,11 @@ struct Engine2D final : lbib_sim {
   }
 
   // waves of a lattice kernel resident at once (queried once per variant)
-  int lb_slots[2][2][2][2] = {};
-  template <int FORM, class Src, class Dst, bool RELAX>
+  int lb_slots[2][2][2][2][2] = {};
+  template <int FORM, class Src, class Dst, bool RELAX, int NW>
   int slots() {
-    int& v = lb_slots[FORM][Src::kMacro][Dst::kMacro][RELAX];
-    if (!v) v = resident_blocks((const void*)&k_lb2d<St, R, FORM, Src, Dst, RELAX>, 64);
+    int& v = lb_slots[FORM][Src::kMacro][Dst::kMacro][RELAX][NW > 1];
+    if (!v) v = NW * resident_blocks((const void*)&k_lb2d<St, R, FORM, Src, Dst, RELAX, NW>, 64 * NW);
     return v;
   }
 
@@ -572,9 +572,18 @@ struct Engine2D final : lbib_sim {
   // regions that read no membrane field (1) or the others in pieces (2)
   template <int FORM, class Src, class Dst, bool RELAX>
   void launch_form(const Src& src, const Dst& dst, hipStream_t s, int mode) {
+    if constexpr (!Src::kMacro && !Dst::kMacro)
+      if (2 * L.pop_bytes > PACED_FROM) {
+        launch_waves<FORM, Src, Dst, RELAX, step2d_paced<R>()>(src, dst, s, mode);
+        return;
+      }
+    launch_waves<FORM, Src, Dst, RELAX, 1>(src, dst, s, mode);
+  }
+  template <int FORM, class Src, class Dst, bool RELAX, int NW>
+  void launch_waves(const Src& src, const Dst& dst, hipStream_t s, int mode) {
     const int W = 64 - 2 * strip_halo<Src>();
     P.nstrip = (p.nx + W - 1) / W;
-    P.seg = pick_seg(P.nstrip, seg > 0 ? 1 : slots<FORM, Src, Dst, RELAX>());
+    P.seg = pick_seg(P.nstrip, seg > 0 ? 1 : slots<FORM, Src, Dst, RELAX, NW>());
     P.nseg = (p.ny + P.seg - 1) / P.seg;
     // automatic: eight L2 domains (the XCDs), so a segment's vertical
     // neighbours, which read the same halo rows, sit in the same L2
@@ -582,16 +591,24 @@ struct Engine2D final : lbib_sim {
     P.mode = mode;
     P.npiece = mode == 2 ? (P.seg + 5) / 6 : 1;  // pieces of about five rows
     P.seg2 = (P.seg + P.npiece - 1) / P.npiece;
-    hipLaunchKernelGGL((k_lb2d<St, R, FORM, Src, Dst, RELAX>), dim3(P.nstrip * P.nseg * P.npiece), dim3(64), 0, s,
-                       src, dst, P, (const int*)at<int>(L.tflag), (const int*)at<int>(L.tstate),
-                       (const double*)at<double>(L.Ifield), at<long long>(L.fib), at<double>(L.force));
+    const int n = P.nstrip * P.nseg * P.npiece;
+    auto launch = [&](auto nw) {
+      constexpr int V = decltype(nw)::value;
+      hipLaunchKernelGGL((k_lb2d<St, R, FORM, Src, Dst, RELAX, V>), dim3((n + V - 1) / V), dim3(64 * V), 0, s, src, dst,
+                         P, (const int*)at<int>(L.tflag), (const int*)at<int>(L.tstate),
+                         (const double*)at<double>(L.Ifield), at<long long>(L.fib), at<double>(L.force));
+    };
+    if (mode == 2)
+      launch(std::integral_constant<int, 1>{});
+    else
+      launch(std::integral_constant<int, NW>{});
   }
   // the same for the 16-bit formats, a workgroup per region
   template <int FORM>
   void launch_ring(St src, St dst, hipStream_t s, int mode) {
     constexpr int BX = RING_LANES, WPE = FORM ? 2 : 3;
     const int W = BX - 4;
-    int& v = lb_slots[FORM][0][0][1];
+    int& v = lb_slots[FORM][0][0][1][0];
     if (!v) v = resident_blocks((const void*)&k_lb2d_ring<St, R, BX, 3, WPE, FORM>, BX);
     P.nstrip = (p.nx + W - 1) / W;
     P.seg = pick_seg(P.nstrip, v);
@@ -1122,6 +1139,7 @@ struct BatchEngine2D final : lbib_sim {
   static constexpr int NLIST = 2;
   int ncm[NLIST] = {0, 0}, lgrid[NLIST][2] = {};
   bool macro = false;  // every member can pass on Macro2 between steps
+  bool paced = false;  // the members' populations exceed the last-level cache
 
   ~BatchEngine2D() override {
     drop_graphs();
@@ -1174,12 +1192,18 @@ struct BatchEngine2D final : lbib_sim {
     // one resident round of the kernel the steps inside a call run
     long long rows = 0;
     for (auto m : mem) rows += (long long)((m->p.nx + W[1] - 1) / W[1]) * m->p.ny;
-    const int slots = force_form ? resident_blocks((const void*)&kb_lb2d<St, R, 1, true, true, false>, 64)
-                                 : resident_blocks((const void*)&kb_lb2d<St, R, 0, true, true, false>, 64);
+    const int slots = force_form ? resident_blocks((const void*)&kb_lb2d<St, R, 1, true, true, false, 1>, 64)
+                                 : resident_blocks((const void*)&kb_lb2d<St, R, 0, true, true, false, 1>, 64);
     for (int c = 0; c < NCLS; c++)
       lseg[c] = cls_seg[c] > 0 ? cls_seg[c] : (int)std::max<long long>(MIN_SEG2, (rows + slots - 1) / slots);
-    long long tiles = 0;
     macro = true;
+    size_t bytes = 0;
+    for (auto m : mem) {
+      macro = macro && m->macro_steps();
+      bytes += 2 * m->L.pop_bytes;
+    }
+    paced = bytes > PACED_FROM;
+    long long tiles = 0;
     for (int l = 0; l < NLIST; l++) ncm[l] = 0;
     for (int i = 0; i < n; i++) {
       Mem* m = mem[i];
@@ -1202,7 +1226,6 @@ struct BatchEngine2D final : lbib_sim {
       for (int k = 0; k < m->K; k++) mems.push_back(make_int2(i, k));
       mpre[i + 1] = mpre[i] + m->M;
       tiles += m->L.ntiles * (m->K > 0);
-      macro = macro && m->macro_steps();
       const int l = m->relaxes() ? 1 : 0, q = ncm[l]++;
       cm[l * n + q] = i;
       for (int sm = 0; sm < 2; sm++) {
@@ -1232,18 +1255,26 @@ struct BatchEngine2D final : lbib_sim {
 
   template <int FORM, bool SM, bool DM>
   void launch_lb(int parity) {
+    if constexpr (!SM && !DM)
+      if (paced) {
+        launch_waves<FORM, SM, DM, step2d_paced<R>()>(parity);
+        return;
+      }
+    launch_waves<FORM, SM, DM, 1>(parity);
+  }
+  template <int FORM, bool SM, bool DM, int NW>
+  void launch_waves(int parity) {
     const int n = (int)mem.size();
     const BM* T = at<BM>(off_tab);
     for (int l = 0; l < NLIST; l++) {
       if (!ncm[l]) continue;
       const int* cml = at<int>(off_cm) + l * n;
       const int* bp = at<int>(off_bpre) + (l * 2 + SM) * (n + 1);
+      const dim3 grid((lgrid[l][SM] + NW - 1) / NW), block(64 * NW);
       if (l == 0)
-        hipLaunchKernelGGL((kb_lb2d<St, R, FORM, SM, DM, false>), dim3(lgrid[l][SM]), dim3(64), 0, stream, T, cml, bp,
-                           ncm[l], parity);
+        hipLaunchKernelGGL((kb_lb2d<St, R, FORM, SM, DM, false, NW>), grid, block, 0, stream, T, cml, bp, ncm[l], parity);
       else if constexpr (!SM && !DM)
-        hipLaunchKernelGGL((kb_lb2d<St, R, FORM, SM, DM, true>), dim3(lgrid[l][SM]), dim3(64), 0, stream, T, cml, bp,
-                           ncm[l], parity);
+        hipLaunchKernelGGL((kb_lb2d<St, R, FORM, SM, DM, true, NW>), grid, block, 0, stream, T, cml, bp, ncm[l], parity);
     }
   }
 
