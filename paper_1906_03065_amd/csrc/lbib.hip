@@ -1178,6 +1178,19 @@ struct BatchEngine2D final : lbib_sim {
            align_up((size_t)NLIST * 2 * (n + 1) * 4);
   }
 
+  // waves resident at once of the kernel that list l's members run inside a call
+  template <int FORM>
+  int list_slots(int l) const {
+    constexpr int NW = step2d_paced<R>();
+    const void* k = l == 1 ? (paced ? (const void*)&kb_lb2d<St, R, FORM, false, false, true, NW>
+                                    : (const void*)&kb_lb2d<St, R, FORM, false, false, true, 1>)
+                    : macro ? (const void*)&kb_lb2d<St, R, FORM, true, true, false, 1>
+                    : paced ? (const void*)&kb_lb2d<St, R, FORM, false, false, false, NW>
+                            : (const void*)&kb_lb2d<St, R, FORM, false, false, false, 1>;
+    const int waves = paced && !(l == 0 && macro) ? NW : 1;
+    return waves * resident_blocks(k, 64 * waves);
+  }
+
   // device tables and launch plan
   int prepare() {
     const int n = (int)mem.size();
@@ -1188,14 +1201,8 @@ struct BatchEngine2D final : lbib_sim {
     std::vector<int2> mems;
     std::vector<int> mpre(n + 1, 0), cm(NLIST * n, 0), bpre(NLIST * 2 * (n + 1), 0);
     const int W[2] = {64 - 2 * strip_halo<St>(), 64 - 2 * strip_halo<MacroStore2<R>>()};
-    // rows per wave: with seg 0 (automatic) all members' items together are
-    // one resident round of the kernel the steps inside a call run
-    long long rows = 0;
-    for (auto m : mem) rows += (long long)((m->p.nx + W[1] - 1) / W[1]) * m->p.ny;
-    const int slots = force_form ? resident_blocks((const void*)&kb_lb2d<St, R, 1, true, true, false, 1>, 64)
-                                 : resident_blocks((const void*)&kb_lb2d<St, R, 0, true, true, false, 1>, 64);
-    for (int c = 0; c < NCLS; c++)
-      lseg[c] = cls_seg[c] > 0 ? cls_seg[c] : (int)std::max<long long>(MIN_SEG2, (rows + slots - 1) / slots);
+    // rows per wave: with seg 0 (automatic) the items of a launch are one
+    // resident round of the kernel that the steps inside a call run
     macro = true;
     size_t bytes = 0;
     for (auto m : mem) {
@@ -1203,13 +1210,33 @@ struct BatchEngine2D final : lbib_sim {
       bytes += 2 * m->L.pop_bytes;
     }
     paced = bytes > PACED_FROM;
+    int auto_seg[NLIST];
+    for (int l = 0; l < NLIST; l++) {
+      const int slots = force_form ? list_slots<1>(l) : list_slots<0>(l), w = W[l == 0 && macro];
+      auto items = [&](int seg) {
+        long long n = 0;
+        for (auto m : mem)
+          if (m->relaxes() == (l == 1)) n += (long long)((m->p.nx + w - 1) / w) * ((m->p.ny + seg - 1) / seg);
+        return n;
+      };
+      int& rows = auto_seg[l];
+      rows = (int)std::max<long long>(MIN_SEG2, (items(1) + slots - 1) / slots);
+      // rounding the segment counts up can leave a few waves over, which then
+      // take a second round (two relaxing members of 2048^2: 711 us per step
+      // against 456); on uneven members' Macro2 a longer segment costs as much
+      if (w == W[0])
+        for (int k = rows / 8; k > 0 && items(rows) > slots; k--) rows++;
+    }
+    for (int c = 0; c < NCLS; c++) lseg[c] = cls_seg[c] > 0 ? cls_seg[c] : auto_seg[0];
     long long tiles = 0;
     for (int l = 0; l < NLIST; l++) ncm[l] = 0;
     for (int i = 0; i < n; i++) {
       Mem* m = mem[i];
       BM& B = T[i];
       B.P = m->P;
-      B.P.seg = std::min(lseg[size_class(m->p.nx)], m->p.ny);
+      const int l = m->relaxes() ? 1 : 0, c = size_class(m->p.nx);
+      lseg[c] = cls_seg[c] > 0 ? cls_seg[c] : auto_seg[l];
+      B.P.seg = std::min(lseg[c], m->p.ny);
       B.P.nseg = (m->p.ny + B.P.seg - 1) / B.P.seg;
       B.P.nxcd = 1;
       B.P.mode = 0;
@@ -1226,7 +1253,7 @@ struct BatchEngine2D final : lbib_sim {
       for (int k = 0; k < m->K; k++) mems.push_back(make_int2(i, k));
       mpre[i + 1] = mpre[i] + m->M;
       tiles += m->L.ntiles * (m->K > 0);
-      const int l = m->relaxes() ? 1 : 0, q = ncm[l]++;
+      const int q = ncm[l]++;
       cm[l * n + q] = i;
       for (int sm = 0; sm < 2; sm++) {
         B.nstrip[sm] = (m->p.nx + W[sm] - 1) / W[sm];
