@@ -202,16 +202,20 @@ int lbib_timing_enable(lbib_sim* s, int on);
 int lbib_timing_read(lbib_sim* s, double* ms, int n, int* steps);
 
 /* Launch shape of the fused lattice kernel (a tuning knob; results do not
-   depend on it): D3Q19, block_x the x extent of a
-   workgroup's tile of 256 nodes (16, 32 (the default) or 64; the y extent
-   is 256 / block_x); D2Q9, block_x one of 64, 128, 192 or 256 and ring 3 or
-   4, accepted and reported without effect (a workgroup is one wave, which
-   holds three rows); seg rows (D3Q19: planes) per workgroup, nxcd the number of L2 domains
-   workgroups are dealt to in turn.  0 keeps the current value; seg = -1 returns to the automatic choice (as many
-   workgroups as fit on the GPU at once, so none waits for a second round),
-   nxcd = -1 to the automatic dealing (eight domains, the XCDs of the
-   MI355X, so that workgroups sharing halo rows or lines meet in one L2).  A value
-   reported as 0 means automatic.  Invalid values change nothing. */
+   depend on it).  D2Q9, 16-bit storage: block_x lanes per workgroup (64, 128,
+   192 or 256; block_x - 4 interior columns) and ring, the rows held in
+   registers (3, or 4 to load the next row while the current ones are
+   computed).  D2Q9, FP32 and FP64: block_x and ring take the same values, are
+   reported and have no effect (a strip is one wave wide).  D3Q19: block_x is
+   the x extent of a workgroup's tile of 256 nodes (16, 32 (the default) or 64;
+   the y extent is 256 / block_x); with every relaxation time 1 in FP32 or FP64
+   it has no effect (that step picks its tile by the lattice's size).  seg: rows
+   (D3Q19: planes) per wave or workgroup; nxcd: the number of L2 domains
+   workgroups are dealt to in turn.  0 keeps the current value; seg = -1 returns
+   to the automatic choice (as many as fit on the GPU at once, so none waits for
+   a second round), nxcd = -1 to the automatic dealing (eight domains, the XCDs
+   of the MI355X, so that workgroups sharing halo rows or lines meet in one L2).
+   A value reported as 0 means automatic.  Invalid values change nothing. */
 int lbib_set_launch(lbib_sim* s, int block_x, int seg, int nxcd, int ring);
 int lbib_get_launch(const lbib_sim* s, int* block_x, int* seg, int* nxcd, int* ring);
 

@@ -603,13 +603,15 @@ struct Engine2D final : lbib_sim {
     else
       launch(std::integral_constant<int, NW>{});
   }
-  // the same for the 16-bit formats, a workgroup per region
-  template <int FORM>
+  // the same for the 16-bit formats, a workgroup of bx lanes per region with a
+  // ring of `ring` rows
+  int ring_slots[2][4][2] = {};  // workgroups resident at once, by force form, lanes / 64 and ring
+  template <int FORM, int BX, int NS>
   void launch_ring(St src, St dst, hipStream_t s, int mode) {
-    constexpr int BX = RING_LANES, WPE = FORM ? 2 : 3;
+    constexpr int WPE = FORM || NS == 4 ? 2 : 3;
     const int W = BX - 4;
-    int& v = lb_slots[FORM][0][0][1][0];
-    if (!v) v = resident_blocks((const void*)&k_lb2d_ring<St, R, BX, 3, WPE, FORM>, BX);
+    int& v = ring_slots[FORM][BX / 64 - 1][NS - 3];
+    if (!v) v = resident_blocks((const void*)&k_lb2d_ring<St, R, BX, NS, WPE, FORM>, BX);
     P.nstrip = (p.nx + W - 1) / W;
     P.seg = pick_seg(P.nstrip, v);
     P.nseg = (p.ny + P.seg - 1) / P.seg;
@@ -623,18 +625,32 @@ struct Engine2D final : lbib_sim {
     long long* fib = at<long long>(L.fib);
     double* frc = at<double>(L.force);
     if (mode == 0)
-      hipLaunchKernelGGL((k_lb2d_ring<St, R, BX, 3, WPE, FORM>), grid, dim3(BX), 0, s, src, dst, P, tf, ts, If, fib, frc);
+      hipLaunchKernelGGL((k_lb2d_ring<St, R, BX, NS, WPE, FORM>), grid, dim3(BX), 0, s, src, dst, P, tf, ts, If, fib, frc);
     else
-      hipLaunchKernelGGL((k_lb2d_ring_part<St, R, BX, 3, WPE, FORM>), grid, dim3(BX), 0, s, src, dst, P, tf, ts, If, fib,
+      hipLaunchKernelGGL((k_lb2d_ring_part<St, R, BX, NS, WPE, FORM>), grid, dim3(BX), 0, s, src, dst, P, tf, ts, If, fib,
                          frc);
+  }
+  template <int FORM, int NS>
+  void launch_ring_lanes(St src, St dst, hipStream_t s, int mode) {
+    if (bx == 64) launch_ring<FORM, 64, NS>(src, dst, s, mode);
+    else if (bx == 128) launch_ring<FORM, 128, NS>(src, dst, s, mode);
+    else if (bx == 192) launch_ring<FORM, 192, NS>(src, dst, s, mode);
+    else launch_ring<FORM, 256, NS>(src, dst, s, mode);
+  }
+  template <int FORM>
+  void launch_ring_form(St src, St dst, hipStream_t s, int mode) {
+    if (ring == 4)
+      launch_ring_lanes<FORM, 4>(src, dst, s, mode);
+    else
+      launch_ring_lanes<FORM, 3>(src, dst, s, mode);
   }
   template <class Src, class Dst>
   void launch_lb(const Src& src, const Dst& dst, hipStream_t s, int mode) {
     if constexpr (St::kQuantized) {
       if (force_form)
-        launch_ring<1>(src, dst, s, mode);
+        launch_ring_form<1>(src, dst, s, mode);
       else
-        launch_ring<0>(src, dst, s, mode);
+        launch_ring_form<0>(src, dst, s, mode);
       return;
     } else if constexpr (!Src::kMacro && !Dst::kMacro)
       if (relaxes()) {
