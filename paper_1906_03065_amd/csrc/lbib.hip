@@ -573,7 +573,7 @@ struct Engine2D final : lbib_sim {
   template <int FORM, class Src, class Dst, bool RELAX>
   void launch_form(const Src& src, const Dst& dst, hipStream_t s, int mode) {
     if constexpr (!Src::kMacro && !Dst::kMacro)
-      if (2 * L.pop_bytes > PACED_FROM) {
+      if (2 * L.pop_bytes > PACED_FROM && p.nx > 64 - 2 * strip_halo<Src>()) {
         launch_waves<FORM, Src, Dst, RELAX, step2d_paced<R>()>(src, dst, s, mode);
         return;
       }

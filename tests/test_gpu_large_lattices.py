@@ -84,3 +84,13 @@ def test_step_order(tau):
         for k in p:
             assert np.array_equal(p[k], q[k]), (i, k)
     assert a.check() == b.check() == 0
+
+
+def test_one_strip():
+    """As large, but a single strip wide: waves on their own."""
+    w = _fluid(57, 173, 0, 0.8, 1)
+    a, b = lbib.from_workload(_repeat(w, 1, 121)), lbib.from_workload(w)
+    for n in (1, 2):
+        a.step(n)
+        b.step(n)
+    _same(a, b, 1, 121)
