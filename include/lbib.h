@@ -312,7 +312,8 @@ void lbib_destroy(lbib_sim* s);
    members (the lattice update one more for members with a relaxation time
    other than 1), and the step is captured once per buffer parity and form of
    the state in a hipGraph and replayed (on a stream that can be captured, i.e. not
-   the legacy default stream; otherwise the launches are enqueued directly).
+   the legacy default stream; otherwise, and for the first and last of several
+   steps when all relaxation times are 1, the launches are enqueued directly).
    Every member gives the same results, bit for bit, as the same
    simulation created alone.
    ------------------------------------------------------------------------ */
@@ -345,8 +346,8 @@ int lbib_batch_get_launch(lbib_sim* batch, int size_class, int* block_x, int* se
                           int* members);
 
 /* Graph replay on (1, the default) or off (0: direct launches); on < 0
-   leaves it.  *active (may be NULL) is 1 when the last step replayed a
-   graph. */
+   leaves it.  *active (may be NULL) is 1 when the last step's graph replay was
+   on and its stream could be captured. */
 int lbib_batch_graph(lbib_sim* batch, int on, int* active);
 
 /* ------------------------------------------------------------------------

@@ -1134,8 +1134,8 @@ struct Engine3D final : lbib_sim {
 // Many D2Q9 simulations in one workspace, stepped together (FP32 storage).
 // Members are ordinary simulations on their own slices of the workspace;
 // the batch owns them.  Each phase of a step is one launch over all members
-// (the lattice update one launch per size class), and the whole step is
-// captured once per buffer parity in a hipGraph and replayed.
+// (the lattice update one more for members that relax), and the whole step is
+// captured in a hipGraph per buffer parity and form of the state, and replayed.
 struct BatchEngine2D final : lbib_sim {
   using St = MixStore<9>;
   using R = float;
@@ -1146,9 +1146,8 @@ struct BatchEngine2D final : lbib_sim {
   // accepted and reported; a strip is one wave wide whatever they are
   int cls_bx[NCLS] = {64, 128, 256}, cls_ring[NCLS] = {3, 3, 3};
   bool use_graph = true, dirty = true, graph_ok = false;
-  // one graph per buffer parity and form of the state read and written,
-  // captured when a step first needs it
-  hipGraphExec_t gexec[2][2][2] = {};
+  // one graph per buffer parity and form of the state (read and written alike)
+  hipGraphExec_t gexec[2][2] = {};
   size_t off_tab = 0, off_mems = 0, off_mpre = 0, off_cm = 0, off_bpre = 0;
   int nmems = 0, Mtot = 0, cgrid = 1, lseg[NCLS] = {0, 0, 0};
   // lattice launches: members that do not relax, and those that do
@@ -1163,12 +1162,11 @@ struct BatchEngine2D final : lbib_sim {
   }
   void drop_graphs() {
     for (auto& a : gexec)
-      for (auto& b : a)
-        for (auto& e : b)
-          if (e) {
-            (void)hipGraphExecDestroy(e);
-            e = nullptr;
-          }
+      for (auto& e : a)
+        if (e) {
+          (void)hipGraphExecDestroy(e);
+          e = nullptr;
+        }
   }
   bool is_batch() const override { return true; }
   void mark_dirty() override { dirty = true; }
@@ -1292,6 +1290,13 @@ struct BatchEngine2D final : lbib_sim {
     HIPCHK(hipStreamSynchronize(st));
     drop_graphs();
     graph_ok = use_graph;
+    if (graph_ok) {  // can the stream be captured?
+      hipGraph_t g = nullptr;
+      graph_ok = hipStreamBeginCapture(st, hipStreamCaptureModeRelaxed) == hipSuccess &&
+                 hipStreamEndCapture(st, &g) == hipSuccess;
+      if (g) (void)hipGraphDestroy(g);
+      if (!graph_ok) (void)hipGetLastError();
+    }
     dirty = false;
     return LBIB_OK;
   }
@@ -1344,31 +1349,40 @@ struct BatchEngine2D final : lbib_sim {
                          mpre, n, parity);
   }
 
-  // one step, replayed from its graph (captured at its first use; a stream
-  // that cannot be captured launches directly)
+  // the step's launches at a parity as a graph; after a failure all steps launch
+  // directly (graphs that may be running stay until the tables are rebuilt)
+  template <bool MACRO>
+  void capture(int parity) {
+    hipGraphExec_t& ge = gexec[parity][MACRO];
+    hipGraph_t g = nullptr;
+    if (!graph_ok || ge) return;
+    if (hipStreamBeginCapture(stream, hipStreamCaptureModeRelaxed) != hipSuccess) {
+      graph_ok = false;
+    } else {
+      launch_all<MACRO, MACRO>(parity);
+      if (hipStreamEndCapture(stream, &g) != hipSuccess || !g ||
+          hipGraphInstantiate(&ge, g, nullptr, nullptr, 0) != hipSuccess) {
+        ge = nullptr;
+        graph_ok = false;
+      }
+      if (g) (void)hipGraphDestroy(g);
+    }
+    if (!graph_ok) (void)hipGetLastError();
+  }
+
+  // One step.  The forms that steps repeat are captured for both parities at
+  // their first use, some 24 us each: two graphs in a batch's first call and none
+  // in later calls of its kind.  The first and last of a call of several steps
+  // launch directly, which takes as long as a replay.
   template <bool SM, bool DM>
   int step() {
     const int parity = mem[0]->cur;
-    hipGraphExec_t& ge = gexec[parity][SM][DM];
-    if (graph_ok && !ge) {
-      hipGraph_t g = nullptr;
-      if (hipStreamBeginCapture(stream, hipStreamCaptureModeRelaxed) != hipSuccess) {
-        graph_ok = false;
-      } else {
-        launch_all<SM, DM>(parity);
-        if (hipStreamEndCapture(stream, &g) != hipSuccess || !g ||
-            hipGraphInstantiate(&ge, g, nullptr, nullptr, 0) != hipSuccess)
-          graph_ok = false;
-        if (g) (void)hipGraphDestroy(g);
-      }
-      if (!graph_ok) {
-        ge = nullptr;
-        drop_graphs();
-        (void)hipGetLastError();
-      }
+    if (SM == DM && graph_ok && !gexec[parity][SM]) {
+      capture<SM>(parity);
+      capture<SM>(1 - parity);
     }
-    if (graph_ok) {
-      if (hipGraphLaunch(ge, stream) != hipSuccess) return LBIB_EHIP;
+    if (SM == DM && graph_ok) {
+      if (hipGraphLaunch(gexec[parity][SM], stream) != hipSuccess) return LBIB_EHIP;
     } else {
       launch_all<SM, DM>(parity);
     }
