@@ -5,8 +5,9 @@ wider) it times candidate shapes of the batched lattice kernel -- the rows per
 work item -- for about twenty steps
 on a throwaway batch of the same workloads, one class at a time with the
 other classes fixed, and keeps the fastest.  Results are cached as JSON keyed
-by GPU architecture, lattice, storage and size class, so a later batch on the
-same hardware reuses them without timing.
+by GPU architecture, lattice, storage, size class and the lattice kernel they
+were timed with, so a later batch on the same hardware reuses them without
+timing and shapes of another kernel are not applied to it.
 """
 from __future__ import annotations
 
@@ -18,6 +19,8 @@ from . import lbib
 
 # a strip is one wave wide whatever the lanes and the ring: the rows decide
 CANDIDATES = [(64, seg, 3) for seg in (-1, 4, 8, 12, 16, 24, 32, 48)]
+# the kernel the shapes are for: named anew when its strips or its march change
+KERNEL = "wave58"
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "lbib", "autotune.json")
 
 
@@ -32,7 +35,7 @@ def arch(device="cuda:0") -> str:
 
 
 def key(arch_name: str, cls: int, lattice="D2Q9", storage="fp32") -> str:
-    return f"{arch_name}|{lattice}|{storage}|class{cls}"
+    return f"{arch_name}|{lattice}|{storage}|class{cls}|{KERNEL}"
 
 
 def load(path=DEFAULT_CACHE) -> dict:
@@ -52,7 +55,7 @@ def save(cache: dict, path=DEFAULT_CACHE):
 
 
 def _time_steps(b: lbib.Batch, steps: int) -> float:
-    b.step(2)  # rebuilds the tables and graphs for the new shape
+    b.step(4)  # rebuilds the tables, and the graphs of the steps inside a call, for the new shape
     b.synchronize()
     t0 = time.perf_counter()
     b.step(steps)
