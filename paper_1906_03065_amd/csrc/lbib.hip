@@ -1950,11 +1950,12 @@ int lbib_energy(lbib_sim* s, lbib_energies* out) {
   if (rc) return rc;
   double* sums = s->at<double>(s->L.memE);
   // rows of w values to w sums; many rows in two levels, the first one's
-  // sums in the moment readout's place (read no more)
+  // sums in the moment readout's place (read no more), which holds 8 N values: a
+  // few nodes with very many markers take one level
   auto sum_rows = [&](const double* in, long long rows, int w, double* out) {
     constexpr long long CHUNK = 4096;
     const long long g = (rows + CHUNK - 1) / CHUNK;
-    if (g > 1) {
+    if (g > 1 && g * w <= 8 * s->N) {
       hipLaunchKernelGGL(k_sum_rows<1024>, dim3((unsigned)g), dim3(1024), 0, s->stream, in, rows, w, CHUNK, stage);
       in = stage;
       rows = g;
