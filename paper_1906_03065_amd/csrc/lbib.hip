@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -956,28 +957,28 @@ struct Engine3D final : lbib_sim {
     int& slots = eq_slots[Dst::kMacro][TX == 64];
     if (!slots) slots = resident_blocks((const void*)&k_lb3d_eq<Dst, R, TX, TY>, NT);
     // planes per workgroup: the fewest plane iterations (5 of each workgroup's
-    // are its halo) over the rounds of resident workgroups
-    int best = p.nz;
-    if (seg > 0) {
-      best = std::min(seg, p.nz);
-    } else {
+    // are its halo) over the rounds of resident workgroups (found once: a long
+    // lattice has many to choose from)
+    int& found = eq_planes[Dst::kMacro][TX == 64];
+    if (!found) {
       long long cost = LLONG_MAX;
       for (int n = 1; n <= p.nz; n++) {
         const int s = (p.nz + n - 1) / n;
         const long long rounds = ((long long)ntx * nty * ((p.nz + s - 1) / s) + slots - 1) / slots;
         if (rounds * (s + 5) < cost) {
           cost = rounds * (s + 5);
-          best = s;
+          found = s;
         }
       }
     }
+    const int best = seg > 0 ? std::min(seg, p.nz) : found;
     P.seg = best;
     P.nseg = (p.nz + best - 1) / best;
     hipLaunchKernelGGL((k_lb3d_eq<Dst, R, TX, TY>), dim3(ntx * nty, P.nseg), dim3(NT), 0, stream, dst, P, m3,
                        (const int*)at<int>(L.tflag), (const int*)at<int>(L.tstate),
                        (const double*)at<double>(L.Ifield), at<long long>(L.fib), at<double>(L.force), ntx);
   }
-  int eq_slots[2][2] = {};
+  int eq_slots[2][2] = {}, eq_planes[2][2] = {};
 
   template <class Src, class Dst>
   void launch_lb(Src src, Dst dst) {
