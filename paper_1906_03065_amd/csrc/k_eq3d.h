@@ -8,14 +8,15 @@
 //   k_lb3d_eq   the chemical potentials, the force and the collision from the
 //               moment field alone, to Macro3 or (a call's last step) to
 //               populations.
-// A call's first step takes its moments from the populations (k_mom3d).  Every
+// A call's first step takes its moments from the populations (k_mom3d_pull).  Every
 // value that decides a result is formed by the same operations on both routes
 // (explicit fma, contraction off), so a call's division into steps leaves the
 // bits alone.
 //
-// 256^3 with two capsules, per step: 2245 + 843 us with populations between all
-// steps; now 620 (k_mom3d_eq) + 599 (k_lb3d_eq), in a call's first step 870 + 599,
-// in its last 620 + 1316.  64^3: 63 + 12 before, 21 + 25 now.
+// 256^3 with two capsules, moments + update per step: 843 + 2245 us with
+// populations between all steps; now 622 (k_mom3d_eq) + 583 (k_lb3d_eq), in a
+// call's first step 877 + 583, in its last 622 + 1325.  64^3: 12 + 63 before, 22 +
+// 25 now.
 #pragma once
 #include "common.h"
 #include "k_lb.h"
@@ -421,8 +422,9 @@ __global__ __launch_bounds__(256) void k_expand3d(MacroStore3<R> src, St dst) {
 //
 // What bounds it: memory (1.0 GB read, 1.0 GB written at 256^3, 416 us at the rate
 // of a copy) and the barrier, with one workgroup per CU at the wide tile (11 waves
-// at 168 registers): 599 us, to populations 1316 us (0.9 + 4.2 GB).  The narrow
-// tile gives a small lattice's CUs a workgroup each: see EQ3_WIDE.
+// at 168 registers, 8 of which spill, 22 to populations; FP64 14 and 62): 583 us,
+// to populations 1325 us (0.9 + 4.2 GB).  The narrow tile gives a small lattice's
+// CUs a workgroup each and spills nothing: see EQ3_WIDE.
 template <class Dst, typename R, int TX, int TY>
 __global__ __launch_bounds__((TX * (TY + 2) + 2 * (TY + 2) + 63) / 64 * 64) void k_lb3d_eq(
     Dst dst, LBParams P, Moments3<R> M, const int* __restrict__ tflag, const int* __restrict__ tstate,

@@ -42,7 +42,12 @@ constexpr float COUP3_BEYOND = 1.0f;
 // hundred renewals take there)
 constexpr int COUP3_RENEW = 96;
 static_assert(COUP3_KEEP == COUP3_CACHE, "a node with entries keeps its band data");
-constexpr int C3_RING = 16;         // entries of a triangle's row in the ring table
+// Entries of a triangle's row in the ring table: the count and up to 15 triangles
+// in one line of 64 B.  A triangle whose vertices have the usual valence of six
+// shares them with 12 others; beyond 15 the vertex lists are walked.  Calls of two
+// capsules at 64^3 and 256^3: 2.98 and 8.85 ms; with 8 entries (every list walked)
+// 3.36 and 9.53, with 32 3.06 and 8.94.
+constexpr int C3_RING = 16;
 constexpr int C3_KEYB = 20;         // key = membrane << 20 | triangle (or a beyond code)
 constexpr int C3_IN = 0xFFFFE, C3_OUT = 0xFFFFD;
 

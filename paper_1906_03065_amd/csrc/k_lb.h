@@ -394,7 +394,6 @@ struct MacroStore2 {
   double rho0, p0, p1;
   static constexpr bool kMacro = true;
   static constexpr int kR = 7;
-  static constexpr long long bytes_per_node() { return kR * (long long)sizeof(R) + 16; }
   __device__ __forceinline__ __amdgpu_buffer_rsrc_t rp() const {
     return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)(kR * N * (unsigned)sizeof(R)), 0x00020000);
   }
@@ -871,16 +870,17 @@ __device__ __forceinline__ bool region_active(const LBParams& P, const int* __re
 // What bounds it, at 2048^2 with 16 capsules in FP32, divergence form: 232 B
 // per node from populations to populations took 246 us in a march of four
 // waves through LDS rings (two barriers a row, two waves per SIMD), against
-// 201 us for copying those bytes.  From Macro2 to Macro2 it moves 88 B per node
-// (76 us at the rate of a copy) and takes 114 us; the vector units, some 450
-// instructions a row of which 200 are FP64, are then busy for 60 to 70 us of
-// it.  227 registers leave two waves per SIMD.  A relaxing step keeps three
-// rows of populations as well (249 registers): 46 -> 42 us at 1000 x 777 in the
-// potential form.
+// 201 us for copying those bytes; it takes 240 us here, paced (step2d_paced).
+// From Macro2 to Macro2 it moves 88 B per node (76 us at the rate of a copy) and
+// takes 111 us; the vector units, some 450 instructions a row of which 200 are
+// FP64, are then busy for 60 to 70 us of it.  227 registers leave two waves per
+// SIMD.  A relaxing step keeps three rows of populations as well, 249 registers in
+// the potential form and 256 with 11 spilled in the divergence form: without
+// membranes 46 -> 42 us at 1000 x 777 and 246 -> 220 at 2048^2 in the former, 45 ->
+// 43 and 233 -> 229 in the latter.
 //
-// P.mode: 0
-// every region; the same step in two passes: 1 the regions that read no
-// membrane field, which may run beside the membrane kernels, 2 the others
+// P.mode: 0 every region; the same step in two passes: 1 the regions that read
+// no membrane field, which may run beside the membrane kernels, 2 the others
 // after them, each segment cut into npiece pieces of seg2 rows so that the few
 // regions near the membranes still fill the GPU.
 // NW: waves of a workgroup, 1 or (modes 0 and 1) step2d_paced().

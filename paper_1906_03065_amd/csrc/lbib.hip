@@ -447,7 +447,12 @@ int resident_blocks(const void* k, int threads) {
 // steps without membranes take 87 us wide and 83 narrow at 96^3, 107 and 122 at
 // 112^3, 291 and 321 at 160^3.
 constexpr long long EQ3_WIDE = 1100000;
-constexpr int MIN_SEG2 = 4;  // fewest rows of a D2Q9 segment chosen automatically
+// Fewest rows of a D2Q9 segment chosen automatically: each wave forms 2 H rows
+// more than it stores, which costs where the waves fill the GPU.  Steps inside a
+// call, FP32, without membranes, with 2 / 4 / 8 rows: 128^2 8.4 / 10.4 / 14.5 us
+// (a wave's chain of rows decides), 300^2 9.4 / 11.3 / 15.1, 509 x 251 12.0 / 11.6 /
+// 15.6.
+constexpr int MIN_SEG2 = 4;
 
 template <class St, typename R>
 struct Engine2D final : lbib_sim {
