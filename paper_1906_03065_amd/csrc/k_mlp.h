@@ -51,7 +51,9 @@ __device__ __forceinline__ f32x4 mma(float a, float b, f32x4 c) {
 // Rows [16 q, 16 q + 16) for q = blockIdx.x, + gridDim.x, ...: 256 threads,
 // wave w the hidden columns [32 w, 32 w + 32) (two tiles).  Rows past B are
 // zero and neither stored nor counted.  Y may be null when training.
-template <bool TRAIN>
+// STAGED (one workgroup): all inputs are taken into LDS first, for an output
+// array that lies over them.
+template <bool TRAIN, bool STAGED = false>
 __global__ __launch_bounds__(256) void k_mlp(const float* __restrict__ prm, const float* __restrict__ X,
                                              const float* __restrict__ T, int B, float invB,
                                              float* __restrict__ Y, float* __restrict__ part,
@@ -62,17 +64,25 @@ __global__ __launch_bounds__(256) void k_mlp(const float* __restrict__ prm, cons
   __shared__ float sG1[TRAIN ? MLP_ROWS : 1][LH], sG2[TRAIN ? MLP_ROWS : 1][LH];  // GELU', then dZ
   __shared__ float sDY[TRAIN ? MLP_ROWS : 1][LO];
   __shared__ double sL[4];
+  extern __shared__ float sAll[];  // STAGED: B * MLP_IN
   const float *W1 = prm, *b1 = prm + MLP_B1, *W2 = prm + MLP_W2, *b2 = prm + MLP_B2, *W3 = prm + MLP_W3,
               *b3 = prm + MLP_B3;
   const int t = threadIdx.x, w = t >> 6, l = t & 63, li = l & 15, lg = l >> 4;
   f32x4 g2[TRAIN ? 2 : 1][8] = {}, g3[2][2] = {}, g1[2] = {};
   float gb1 = 0.0f, gb2 = 0.0f, gb3 = 0.0f;
   double loss = 0.0;
+  if constexpr (STAGED) {
+    for (int i = t; i < B * MLP_IN; i += 256) sAll[i] = X[i];
+    __syncthreads();
+  }
   for (int q = blockIdx.x; q * MLP_ROWS < B; q += gridDim.x) {
     const int r0 = q * MLP_ROWS;
     {
       const int i = t >> 4, c = t & 15;
-      sX[i][c] = (c < MLP_IN && r0 + i < B) ? X[(long long)(r0 + i) * MLP_IN + c] : 0.0f;
+      float x = 0.0f;
+      if (c < MLP_IN && r0 + i < B)
+        x = STAGED ? sAll[(r0 + i) * MLP_IN + c] : X[(long long)(r0 + i) * MLP_IN + c];
+      sX[i][c] = x;
     }
     __syncthreads();
     // layer 1

@@ -2319,7 +2319,9 @@ size_t mlp_layout(lbib_mlp* h, int B) {
   Carver c{nullptr};
   const size_t np = (size_t)MLP_NPARAM * 4;
   const size_t o_p = c.take(np), o_g = c.take(np), o_m = c.take(np), o_v = c.take(np);
-  const size_t o_part = c.take((size_t)mlp_parts(B) * np), o_lpart = c.take((size_t)mlp_parts(B) * 8);
+  // partial gradients, or a copy of the inputs of a forward pass whose outputs
+  // lie over them
+  const size_t o_part = c.take(std::max((size_t)mlp_parts(B) * np, (size_t)B * MLP_IN * 4)), o_lpart = c.take((size_t)mlp_parts(B) * 8);
   if (h) {
     h->off_p = o_p;
     h->off_g = o_g;
@@ -2329,6 +2331,13 @@ size_t mlp_layout(lbib_mlp* h, int B) {
     h->off_lpart = o_lpart;
   }
   return c.off;
+}
+
+// do the outputs lie over some of the inputs?  Workgroups write their rows while
+// others still read theirs, so such inputs are read in full first
+bool mlp_overlap(const float* X, int B, const float* Y) {
+  const uintptr_t x = (uintptr_t)X, y = (uintptr_t)Y, n = (uintptr_t)B;
+  return x < y + n * MLP_OUT * 4 && y < x + n * MLP_IN * 4;
 }
 
 void mlp_forward(const float* prm, const float* X, int B, float* Y, hipStream_t st) {
@@ -2416,6 +2425,11 @@ int lbib_mlp_get_params(lbib_mlp* h, float* host) {
 
 int lbib_mlp_forward(lbib_mlp* h, const float* x_dev, int B, float* y_dev) {
   if (!h || !x_dev || !y_dev || B < 1 || B > h->bmax) return LBIB_EINVAL;
+  if (mlp_overlap(x_dev, B, y_dev)) {
+    float* x = h->at<float>(h->off_part);
+    HIPCHK(hipMemcpyAsync(x, x_dev, (size_t)B * MLP_IN * 4, hipMemcpyDeviceToDevice, h->stream));
+    x_dev = x;
+  }
   mlp_forward(h->at<float>(h->off_p), x_dev, B, y_dev, h->stream);
   return hipGetLastError() == hipSuccess ? LBIB_OK : LBIB_EHIP;
 }
@@ -2460,6 +2474,10 @@ extern "C" int lbib_mlp_forward_noalloc(const float* params_dev, const float* x_
                                         void* hip_stream) {
   if (!params_dev || !x_dev || !y_dev || B < 1) return LBIB_EINVAL;
   if (B > MLP_NOALLOC_ROWS) return LBIB_ENOMEM;
-  mlp_forward(params_dev, x_dev, B, y_dev, (hipStream_t)hip_stream);
+  if (mlp_overlap(x_dev, B, y_dev))
+    hipLaunchKernelGGL((k_mlp<false, true>), dim3(1), dim3(256), (size_t)B * MLP_IN * 4, (hipStream_t)hip_stream,
+                       params_dev, x_dev, (const float*)nullptr, B, 0.0f, y_dev, (float*)nullptr, (double*)nullptr);
+  else
+    mlp_forward(params_dev, x_dev, B, y_dev, (hipStream_t)hip_stream);
   return hipGetLastError() == hipSuccess ? LBIB_OK : LBIB_EHIP;
 }
