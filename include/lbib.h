@@ -309,8 +309,7 @@ void lbib_destroy(lbib_sim* s);
 /* ------------------------------------------------------------------------
    Batches: n independent D2Q9 simulations (FP32 storage, n <= 256) in one
    workspace, stepped together.  Each phase of a step is one launch over all
-   members (the lattice update one more for members with a relaxation time
-   other than 1), and the step is captured once per buffer parity and form of
+   members, and the step is captured once per buffer parity and form of
    the state in a hipGraph and replayed (on a stream that can be captured, i.e. not
    the legacy default stream; otherwise, and for the first and last of several
    steps when all relaxation times are 1, the launches are enqueued directly).

@@ -5,8 +5,8 @@
 // (strip, segment) of a lattice) spread over the members, finds the member
 // of each item by binary search over prefix sums, and runs the same device
 // code the single-simulation kernels run.  The lattice kernel has one (strip,
-// segment) item per wave; members that relax (some tau not 1) run in a launch
-// of their own.  All members advance with the same buffer parity and hold the
+// segment) item per wave, and one launch for all members, whether they relax
+// (some tau not 1) or not.  All members advance with the same buffer parity and hold the
 // same form of the state (populations, or Macro2 between the steps of a call).
 #pragma once
 #include "common.h"
@@ -20,6 +20,7 @@ constexpr int BATCH_MAX = 256;  // members per batch
 template <class St, typename R>
 struct BMember {
   LBParams P;     // segments for the member's size class
+  int relax;      // some relaxation time differs from 1
   int nstrip[2];  // strips when the step reads populations, and when it reads Macro2
   St a, b;        // population buffers (parity 0 reads a, writes b)
   MacroStore2<R> ma, mb;  // the same memory between the steps of a call
@@ -127,22 +128,25 @@ __global__ void kb_interp2d(const BMember<St, R>* T, const int* __restrict__ mpr
   interp2d_run<decltype(cur), R>(md, cur, P, force, live ? gf - mpre[i] : 0, k, live);
 }
 
-// one wave per (strip, segment) item of the members listed in cm (bpre: item
-// prefix, ncm + 1 entries); NW as in k_lb2d
-template <class St, typename R, int FORM, bool SM, bool DM, bool RELAX, int NW>
+// kinds of batches: no member relaxes, all do, or some
+enum { KIND_EQ = 0, KIND_RELAX = 1, KIND_MIXED = 2 };
+
+// one wave per (strip, segment) item of the members (bpre: item prefix, n + 1
+// entries); NW as in k_lb2d.  A mixed batch takes one launch too, each wave
+// branching on its member: with a launch per kind a step of 15 members of 240 x
+// 120, five of which relax, took 120 us instead of 108.
+template <class St, typename R, int FORM, bool SM, bool DM, int KIND, int NW>
 __global__ __launch_bounds__(64 * NW, step2d_waves<R>()) void kb_lb2d(const BMember<St, R>* T,
-                                                                      const int* __restrict__ cm,
-                                                                      const int* __restrict__ bpre, int ncm,
+                                                                      const int* __restrict__ bpre, int n,
                                                                       int parity) {
   // items dealt to the eight XCDs in contiguous runs, so the neighbouring
   // segments of a member share their halo rows in one L2
   int item = dealt_index((int)blockIdx.x, (int)gridDim.x, 8) * NW;
   if constexpr (NW > 1) {
     item += __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    if (item >= bpre[ncm]) return;
+    if (item >= bpre[n]) return;
   }
-  const int q = prefix_find(bpre, ncm, item);
-  const int i = cm[q];
+  const int i = prefix_find(bpre, n, item);
   const LBParams P = T[i].P;
   const auto src = batch_buffer<SM>(T[i], parity != 0);
   const auto dst = batch_buffer<DM>(T[i], parity == 0);
@@ -152,10 +156,20 @@ __global__ __launch_bounds__(64 * NW, step2d_waves<R>()) void kb_lb2d(const BMem
   long long* fib = T[i].fib;
   double* force = T[i].force;
   int strip, sgm;
-  strip_segment(item - bpre[q], T[i].nstrip[SM], P.nseg, 1, strip, sgm);
+  strip_segment(item - bpre[i], T[i].nstrip[SM], P.nseg, 1, strip, sgm);
   const int y0 = sgm * P.seg, y1 = min(y0 + P.seg, P.ny);
-  step2d_run<St, R, FORM, decltype(src), decltype(dst), RELAX, (NW > 1)>(src, dst, P, strip, y0, y1, tflag, tstate,
-                                                                         Ifield, fib, force);
+  auto run = [&](auto relax) {
+    step2d_run<St, R, FORM, decltype(src), decltype(dst), decltype(relax)::value, (NW > 1)>(
+        src, dst, P, strip, y0, y1, tflag, tstate, Ifield, fib, force);
+  };
+  if constexpr (KIND == KIND_MIXED) {
+    if (T[i].relax)
+      run(std::true_type{});
+    else
+      run(std::false_type{});
+  } else {
+    run(std::integral_constant<bool, KIND == KIND_RELAX>{});
+  }
 }
 
 }  // namespace lb

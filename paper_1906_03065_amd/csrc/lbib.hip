@@ -1139,9 +1139,9 @@ struct Engine3D final : lbib_sim {
 
 // Many D2Q9 simulations in one workspace, stepped together (FP32 storage).
 // Members are ordinary simulations on their own slices of the workspace;
-// the batch owns them.  Each phase of a step is one launch over all members
-// (the lattice update one more for members that relax), and the whole step is
-// captured in a hipGraph per buffer parity and form of the state, and replayed.
+// the batch owns them.  Each phase of a step is one launch over all members,
+// and the whole step is captured in a hipGraph per buffer parity and form of the
+// state, and replayed.
 struct BatchEngine2D final : lbib_sim {
   using St = MixStore<9>;
   using R = float;
@@ -1154,11 +1154,9 @@ struct BatchEngine2D final : lbib_sim {
   bool use_graph = true, dirty = true, graph_ok = false;
   // one graph per buffer parity and form of the state (read and written alike)
   hipGraphExec_t gexec[2][2] = {};
-  size_t off_tab = 0, off_mems = 0, off_mpre = 0, off_cm = 0, off_bpre = 0;
+  size_t off_tab = 0, off_mems = 0, off_mpre = 0, off_bpre = 0;
   int nmems = 0, Mtot = 0, cgrid = 1, lseg[NCLS] = {0, 0, 0};
-  // lattice launches: members that do not relax, and those that do
-  static constexpr int NLIST = 2;
-  int ncm[NLIST] = {0, 0}, lgrid[NLIST][2] = {};
+  int kind = KIND_EQ, lgrid[2] = {0, 0};  // which members relax; items from populations and from Macro2
   bool macro = false;  // every member can pass on Macro2 between steps
   bool paced = false;  // the members' populations exceed the last-level cache
 
@@ -1194,21 +1192,30 @@ struct BatchEngine2D final : lbib_sim {
   using BM = BMember<St, R>;
   static size_t table_bytes(int n, int kmax) {
     return align_up((size_t)n * sizeof(BM)) + align_up((size_t)std::max(kmax, 1) * sizeof(int2)) +
-           align_up((size_t)(n + 1) * 4) + align_up((size_t)NLIST * n * 4) +
-           align_up((size_t)NLIST * 2 * (n + 1) * 4);
+           align_up((size_t)(n + 1) * 4) + align_up((size_t)2 * (n + 1) * 4);
   }
 
-  // waves resident at once of the kernel that list l's members run inside a call
+  // f(kernel, NW) for the lattice kernel of a step
+  template <int FORM, bool SM, bool DM, class F>
+  auto lattice_kernel(F&& f) const {
+    if constexpr (SM || DM) {  // (no member relaxes)
+      return f(&kb_lb2d<St, R, FORM, SM, DM, KIND_EQ, 1>, 1);
+    } else {
+      constexpr int NW = step2d_paced<R>();
+      if (kind == KIND_EQ)
+        return paced ? f(&kb_lb2d<St, R, FORM, SM, DM, KIND_EQ, NW>, NW) : f(&kb_lb2d<St, R, FORM, SM, DM, KIND_EQ, 1>, 1);
+      if (kind == KIND_RELAX)
+        return paced ? f(&kb_lb2d<St, R, FORM, SM, DM, KIND_RELAX, NW>, NW)
+                     : f(&kb_lb2d<St, R, FORM, SM, DM, KIND_RELAX, 1>, 1);
+      return paced ? f(&kb_lb2d<St, R, FORM, SM, DM, KIND_MIXED, NW>, NW)
+                   : f(&kb_lb2d<St, R, FORM, SM, DM, KIND_MIXED, 1>, 1);
+    }
+  }
+  // waves resident at once of the kernel that the steps inside a call run
   template <int FORM>
-  int list_slots(int l) const {
-    constexpr int NW = step2d_paced<R>();
-    const void* k = l == 1 ? (paced ? (const void*)&kb_lb2d<St, R, FORM, false, false, true, NW>
-                                    : (const void*)&kb_lb2d<St, R, FORM, false, false, true, 1>)
-                    : macro ? (const void*)&kb_lb2d<St, R, FORM, true, true, false, 1>
-                    : paced ? (const void*)&kb_lb2d<St, R, FORM, false, false, false, NW>
-                            : (const void*)&kb_lb2d<St, R, FORM, false, false, false, 1>;
-    const int waves = paced && !(l == 0 && macro) ? NW : 1;
-    return waves * resident_blocks(k, 64 * waves);
+  int lattice_slots() const {
+    auto slots = [](auto k, int nw) { return nw * resident_blocks((const void*)k, 64 * nw); };
+    return macro ? lattice_kernel<FORM, true, true>(slots) : lattice_kernel<FORM, false, false>(slots);
   }
 
   // device tables and launch plan
@@ -1219,44 +1226,40 @@ struct BatchEngine2D final : lbib_sim {
       if (!m->ready || m->cur != mem[0]->cur) return LBIB_ESTATE;
     std::vector<BM> T(n);
     std::vector<int2> mems;
-    std::vector<int> mpre(n + 1, 0), cm(NLIST * n, 0), bpre(NLIST * 2 * (n + 1), 0);
+    std::vector<int> mpre(n + 1, 0), bpre(2 * (n + 1), 0);
     const int W[2] = {64 - 2 * strip_halo<St>(), 64 - 2 * strip_halo<MacroStore2<R>>()};
-    // rows per wave: with seg 0 (automatic) the items of a launch are one
-    // resident round of the kernel that the steps inside a call run
     macro = true;
     size_t bytes = 0;
+    int nrelax = 0;
     for (auto m : mem) {
       macro = macro && m->macro_steps();
       bytes += 2 * m->L.pop_bytes;
+      nrelax += m->relaxes();
     }
     paced = bytes > PACED_FROM;
-    int auto_seg[NLIST];
-    for (int l = 0; l < NLIST; l++) {
-      const int slots = force_form ? list_slots<1>(l) : list_slots<0>(l), w = W[l == 0 && macro];
-      auto items = [&](int seg) {
-        long long n = 0;
-        for (auto m : mem)
-          if (m->relaxes() == (l == 1)) n += (long long)((m->p.nx + w - 1) / w) * ((m->p.ny + seg - 1) / seg);
-        return n;
-      };
-      int& rows = auto_seg[l];
-      rows = (int)std::max<long long>(MIN_SEG2, (items(1) + slots - 1) / slots);
-      // rounding the segment counts up can leave a few waves over, which then
-      // take a second round (two relaxing members of 2048^2: 711 us per step
-      // against 456); on uneven members' Macro2 a longer segment costs as much
-      if (w == W[0])
-        for (int k = rows / 8; k > 0 && items(rows) > slots; k--) rows++;
-    }
-    for (int c = 0; c < NCLS; c++) lseg[c] = cls_seg[c] > 0 ? cls_seg[c] : auto_seg[0];
+    kind = nrelax == 0 ? KIND_EQ : (nrelax == n ? KIND_RELAX : KIND_MIXED);
+    // rows per wave: with seg 0 (automatic) all members' items are one resident
+    // round of the kernel that the steps inside a call run
+    const int slots = force_form ? lattice_slots<1>() : lattice_slots<0>();
+    auto items = [&](int seg) {
+      long long q = 0;
+      for (auto m : mem) q += (long long)((m->p.nx + W[macro] - 1) / W[macro]) * ((m->p.ny + seg - 1) / seg);
+      return q;
+    };
+    int rows = (int)std::max<long long>(MIN_SEG2, (items(1) + slots - 1) / slots);
+    // rounding the segment counts up can leave a few waves over, which then
+    // take a second round (two relaxing members of 2048^2: 711 us per step
+    // against 456); on uneven members' Macro2 a longer segment costs as much
+    if (!macro)
+      for (int k = rows / 8; k > 0 && items(rows) > slots; k--) rows++;
+    for (int c = 0; c < NCLS; c++) lseg[c] = cls_seg[c] > 0 ? cls_seg[c] : rows;
     long long tiles = 0;
-    for (int l = 0; l < NLIST; l++) ncm[l] = 0;
     for (int i = 0; i < n; i++) {
       Mem* m = mem[i];
       BM& B = T[i];
       B.P = m->P;
-      const int l = m->relaxes() ? 1 : 0, c = size_class(m->p.nx);
-      lseg[c] = cls_seg[c] > 0 ? cls_seg[c] : auto_seg[l];
-      B.P.seg = std::min(lseg[c], m->p.ny);
+      B.relax = m->relaxes();
+      B.P.seg = std::min(lseg[size_class(m->p.nx)], m->p.ny);
       B.P.nseg = (m->p.ny + B.P.seg - 1) / B.P.seg;
       B.P.nxcd = 1;
       B.P.mode = 0;
@@ -1273,25 +1276,21 @@ struct BatchEngine2D final : lbib_sim {
       for (int k = 0; k < m->K; k++) mems.push_back(make_int2(i, k));
       mpre[i + 1] = mpre[i] + m->M;
       tiles += m->L.ntiles * (m->K > 0);
-      const int q = ncm[l]++;
-      cm[l * n + q] = i;
       for (int sm = 0; sm < 2; sm++) {
         B.nstrip[sm] = (m->p.nx + W[sm] - 1) / W[sm];
-        int* pre = bpre.data() + (l * 2 + sm) * (n + 1);
-        pre[q + 1] = pre[q] + B.nstrip[sm] * B.P.nseg;
+        int* pre = bpre.data() + sm * (n + 1);
+        pre[i + 1] = pre[i] + B.nstrip[sm] * B.P.nseg;
       }
     }
     nmems = (int)mems.size();
     Mtot = mpre[n];
     cgrid = (int)std::max<long long>(1, std::min<long long>(tiles, 4096));
-    for (int l = 0; l < NLIST; l++)
-      for (int sm = 0; sm < 2; sm++) lgrid[l][sm] = bpre[(l * 2 + sm) * (n + 1) + ncm[l]];
+    for (int sm = 0; sm < 2; sm++) lgrid[sm] = bpre[sm * (n + 1) + n];
     hipStream_t st = stream;
     HIPCHK(hipMemcpyAsync(ws + off_tab, T.data(), T.size() * sizeof(BM), hipMemcpyHostToDevice, st));
     if (!mems.empty())
       HIPCHK(hipMemcpyAsync(ws + off_mems, mems.data(), mems.size() * sizeof(int2), hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(ws + off_mpre, mpre.data(), mpre.size() * 4, hipMemcpyHostToDevice, st));
-    HIPCHK(hipMemcpyAsync(ws + off_cm, cm.data(), cm.size() * 4, hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(ws + off_bpre, bpre.data(), bpre.size() * 4, hipMemcpyHostToDevice, st));
     HIPCHK(hipStreamSynchronize(st));
     drop_graphs();
@@ -1309,27 +1308,10 @@ struct BatchEngine2D final : lbib_sim {
 
   template <int FORM, bool SM, bool DM>
   void launch_lb(int parity) {
-    if constexpr (!SM && !DM)
-      if (paced) {
-        launch_waves<FORM, SM, DM, step2d_paced<R>()>(parity);
-        return;
-      }
-    launch_waves<FORM, SM, DM, 1>(parity);
-  }
-  template <int FORM, bool SM, bool DM, int NW>
-  void launch_waves(int parity) {
-    const int n = (int)mem.size();
-    const BM* T = at<BM>(off_tab);
-    for (int l = 0; l < NLIST; l++) {
-      if (!ncm[l]) continue;
-      const int* cml = at<int>(off_cm) + l * n;
-      const int* bp = at<int>(off_bpre) + (l * 2 + SM) * (n + 1);
-      const dim3 grid((lgrid[l][SM] + NW - 1) / NW), block(64 * NW);
-      if (l == 0)
-        hipLaunchKernelGGL((kb_lb2d<St, R, FORM, SM, DM, false, NW>), grid, block, 0, stream, T, cml, bp, ncm[l], parity);
-      else if constexpr (!SM && !DM)
-        hipLaunchKernelGGL((kb_lb2d<St, R, FORM, SM, DM, true, NW>), grid, block, 0, stream, T, cml, bp, ncm[l], parity);
-    }
+    lattice_kernel<FORM, SM, DM>([&](auto k, int nw) {
+      hipLaunchKernelGGL(k, dim3((lgrid[SM] + nw - 1) / nw), dim3(64 * nw), 0, stream, (const BM*)at<BM>(off_tab),
+                         (const int*)(at<int>(off_bpre) + SM * (mem.size() + 1)), (int)mem.size(), parity);
+    });
   }
 
   template <bool SM, bool DM>
@@ -2220,8 +2202,7 @@ int lbib_batch_create(int n, const lbib_params* params, void* ws, size_t ws_byte
   b->off_tab = 0;
   b->off_mems = align_up((size_t)n * sizeof(BatchEngine2D::BM));
   b->off_mpre = b->off_mems + align_up((size_t)std::max(kmax, 1) * sizeof(int2));
-  b->off_cm = b->off_mpre + align_up((size_t)(n + 1) * 4);
-  b->off_bpre = b->off_cm + align_up((size_t)BatchEngine2D::NLIST * n * 4);
+  b->off_bpre = b->off_mpre + align_up((size_t)(n + 1) * 4);
   size_t off = BatchEngine2D::table_bytes(n, kmax);
   for (int i = 0; i < n; i++) {
     Layout L = make_layout(&params[i]);
